@@ -85,93 +85,68 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_finalize(const FilterD
     if (blockIdx.x == 0 && threadIdx.x < nq) queues[threadIdx.x] = 0;
 }
 
-// x_bar_i = x_{k_i} for one particle (fused gather epilogue).
-__device__ __forceinline__ void gather_row(const FilterDev& F, uint32_t i, int32_t k, uint32_t d)
-{
-    if (!F.states || d == 0) return;
-    // outputs are streamed past the L2 (written once, never read here)
-    if (F.rows4) {
-        const float4* src = reinterpret_cast<const float4*>(F.states);
-        float4* dst = reinterpret_cast<float4*>(F.out);
-        const uint32_t d4 = d / 4u;
-        for (uint32_t c = 0; c < d4; ++c) {
-            const float4 v = k >= 0 ? src[(uint64_t)k * d4 + c] : make_float4(NAN, NAN, NAN, NAN);
-            float4* o = &dst[(uint64_t)i * d4 + c];
-            __builtin_nontemporal_store(v.x, &o->x);
-            __builtin_nontemporal_store(v.y, &o->y);
-            __builtin_nontemporal_store(v.z, &o->z);
-            __builtin_nontemporal_store(v.w, &o->w);
-        }
-    } else {
-        for (uint32_t c = 0; c < d; ++c)
-            __builtin_nontemporal_store(k >= 0 ? F.states[(uint64_t)k * d + c] : NAN, &F.out[(uint64_t)i * d + c]);
-    }
-}
-
+// One tile: the chains of the block's BT * P particles from `start` on, then
+// the ancestors and the particle copy x_bar_i = x_{k_i}.
 template <int V, int BT, int P>
 __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats* __restrict__ st, uint32_t start,
                                              uint32_t d)
 {
     const uint32_t n = F.n;
     const uint32_t B = st->B;
-    if (st->status != MGP_OK) {
+    const RowCopy rc{d ? F.states : nullptr, F.out, d, F.rows4};
+    uint32_t idx[P];
+    int32_t k[P];
+    bool live[P];
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const uint32_t i = start + threadIdx.x + BT * p;
-            if (i < n) {
-                F.anc[i] = -1;
-                gather_row(F, i, -1, d);
-            }
-        }
-        return;
+    for (int p = 0; p < P; ++p) {
+        idx[p] = start + threadIdx.x + BT * p;
+        live[p] = idx[p] < n;
+        k[p] = -1;
     }
-    if constexpr (V == kMegopolis) {
-        const uint32_t i0 = start + threadIdx.x;
-        uint32_t k[P];
-        megopolis_mirror_chain<P, BT>(reinterpret_cast<const char*>(F.mirror), F.offsets, n, B, F.key0, F.key1,
-                                      F.stream_id, i0, k);
+    if (st->status == MGP_OK) {
+        if constexpr (V == kMegopolis) {
+            uint32_t kc[P];
+            megopolis_mirror_chain<P, BT>(global_ptr(reinterpret_cast<const char*>(F.mirror)), offset_ptr(F.offsets),
+                                          n, B, F.key0, F.key1, F.stream_id, start + threadIdx.x, kc);
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const uint32_t i = i0 + BT * p;
-            if (i < n) {
-                F.anc[i] = (int32_t)k[p];
-                gather_row(F, i, (int32_t)k[p], d);
-            }
-        }
-    } else {
-        // every lane runs a chain (lanes past n as n - 1, whose group is that
-        // of the real lanes of its half-wave: tiles start on multiples of 64),
-        // so that C2 shares each group's partition draws across the half-wave
-        const LoopParams L{F.w, F.offsets, n, B, F.key0, F.key1, F.stream_id, F.n_w, F.n_part};
+            for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
+        } else {
+            // every lane runs a chain (lanes past n as n - 1, whose group is
+            // that of the real lanes of its half-wave: tiles start on
+            // multiples of 64), so that C2 shares each group's partition
+            // draws across the half-wave
+            const LoopParams<GlobalPtr<const float>> L{global_ptr(F.w), offset_ptr(F.offsets), n, B, F.key0, F.key1,
+                                                       F.stream_id, F.n_w, F.n_part};
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const uint32_t i = start + threadIdx.x + BT * p;
-            const uint32_t ic = i < n ? i : n - 1u;
-            const uint32_t k = run_chain<V, true, true>(L, ic);
-            if (i < n) {
-                F.anc[i] = (int32_t)k;
-                gather_row(F, i, (int32_t)k, d);
-            }
+            for (int p = 0; p < P; ++p) k[p] = (int32_t)run_chain<V, true, true>(L, live[p] ? idx[p] : n - 1u);
         }
     }
+    const GlobalPtr<int32_t> anc = global_ptr(F.anc);
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (live[p]) anc[idx[p]] = k[p];
+    if (rc.states) copy_rows<P>(rc, idx, k, live);
 }
 
 // Minimum waves per SIMD asked of the compiler for the grid-scheduled
 // accept loop. C2's shared partition draws raise its register count to 78
 // (6 waves); asked for 7 it schedules the loop into 70 registers without
-// spilling: 7% and 13% faster at B = 32 and 64, equal at B = 16. The others,
-// and the persistent kernel (whose queue logic adds registers), are left to
-// the compiler: asked for 7 they would spill.
-template <int V>
+// spilling: 7% and 13% faster at B = 32 and 64, equal at B = 16. Megopolis
+// with eight particles per thread takes 89 registers (5 waves) unless asked
+// for 7: 717 against 778 us on the 512-filter batch. The others are left to the compiler: C1, Metropolis and the
+// persistent kernel (whose queue logic adds registers) would spill at 7, and
+// Megopolis with four particles, 73 registers or 6 waves, spills when asked
+// for 8 and is then 1-2% slower (the 512-filter batch: 699 against 689 us).
+template <int V, int P>
 struct LoopWaves {
-    static constexpr int value = V == kC2 ? 7 : 1;
+    static constexpr int value = V == kC2 ? 7 : P == 8 ? 7 : 1;
 };
 
 // One block per tile, tiles ordered so that block b runs on XCD b mod 8.
 template <int V, int BT, int P>
-__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(LoopWaves<V>::value))) void k_batch_loop_grid(const FilterDev* __restrict__ fd,
-                                                        const mgp_stats* __restrict__ stats,
-                                                        const LTile* __restrict__ tiles, uint32_t d)
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(LoopWaves<V, P>::value)))
+void k_batch_loop_grid(const FilterDev* __restrict__ fd, const mgp_stats* __restrict__ stats,
+                       const LTile* __restrict__ tiles, uint32_t d)
 {
     const LTile t = tiles[blockIdx.x];
     if (t.f == kNoFilter) return;

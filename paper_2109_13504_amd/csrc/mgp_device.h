@@ -139,22 +139,50 @@ __device__ __forceinline__ uint32_t partition_index(uint32_t p, uint32_t jword, 
     return start + uniform_index(jword, width);
 }
 
+// Pointers read from a record in memory (a batch's filters) carry no address
+// space, and the compiler then uses FLAT accesses, 64-bit vector addresses
+// and, for the wave-uniform offsets, one vector load per lane. These types
+// say where the data lie: HBM for weights, states and ancestors, and memory
+// that is read-only during the launch, which uniform indices read through the
+// scalar unit, for the offsets. On the 512-filter batch (20.7 M particles,
+// 1.37e9 particle-steps) a run went from 718 to 668 us.
+template <typename T>
+using GlobalPtr = __attribute__((address_space(1))) T*;
+using OffsetPtr = const __attribute__((address_space(4))) uint32_t*;
+
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> global_ptr(T* p)
+{
+    return (GlobalPtr<T>)(uintptr_t)p;
+}
+
+__device__ __forceinline__ OffsetPtr offset_ptr(const uint32_t* p) { return (OffsetPtr)(uintptr_t)p; }
+
 // Loads w[j]. With `Narrow` the byte offset fits 32 bits (n <= 2^30), which
 // lets the compiler use the scalar-base + 32-bit vector-offset form.
 template <bool Narrow>
-__device__ __forceinline__ float load_weight(const float* __restrict__ w, uint32_t j)
+__device__ __forceinline__ float load_weight(GlobalPtr<const float> w, uint32_t j)
 {
     if constexpr (Narrow) {
-        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(w) + (j << 2));
+        return *(GlobalPtr<const float>)((GlobalPtr<const char>)w + (j << 2));
     } else {
         return w[(size_t)j];
     }
 }
 
-// Per-call parameters of the accept loop (all wave-uniform).
+// The same from weights kept in LDS.
+template <bool Narrow>
+__device__ __forceinline__ float load_weight(const float* w, uint32_t j)
+{
+    return w[j];
+}
+
+// Per-call parameters of the accept loop (all wave-uniform). Weights is
+// GlobalPtr<const float>, or const float* for weights kept in LDS.
+template <typename Weights>
 struct LoopParams {
-    const float* w;
-    const uint32_t* offsets;  // Megopolis offsets o_0..o_{B-1}, each < n
+    Weights w;
+    OffsetPtr offsets;  // Megopolis offsets o_0..o_{B-1}, each < n
     uint32_t n;
     uint32_t B;
     uint32_t key0, key1;
@@ -166,7 +194,8 @@ struct LoopParams {
 
 // o_b, clamped below n so that a workspace not written by this call's
 // reduction can never steer a load out of bounds (wave-uniform, scalar unit).
-__device__ __forceinline__ uint32_t offset_at(const LoopParams& P, uint32_t b)
+template <typename W>
+__device__ __forceinline__ uint32_t offset_at(const LoopParams<W>& P, uint32_t b)
 {
     const uint32_t o = P.offsets[b];
     return o < P.n ? o : P.n - 1u;
@@ -210,13 +239,12 @@ __device__ __forceinline__ uint32_t pinned(uint32_t x)
 // block's loads are in flight together; then the serial accept steps.
 // Partial skips the steps past cnt (cnt is wave-uniform), including their
 // generator calls and loads.
-template <int V, bool Narrow, bool Shared, bool Partial>
-__device__ __forceinline__ void chain_block(const LoopParams& P, const ChainFixed& F, uint32_t q, uint32_t cnt,
+template <int V, bool Narrow, bool Shared, bool Partial, typename W>
+__device__ __forceinline__ void chain_block(const LoopParams<W>& P, const ChainFixed& F, uint32_t q, uint32_t cnt,
                                             ChainState& c)
 {
     constexpr uint32_t U = Unroll<V>::value;
     constexpr bool kShare = Shared && V == kC2;
-    const float* __restrict__ w = P.w;
     UBlock ub;
     Words jb{}, pb{}, pmine{};
     uint32_t jj[U];
@@ -258,7 +286,7 @@ __device__ __forceinline__ void chain_block(const LoopParams& P, const ChainFixe
             }
         }
         jj[s] = j;
-        wj[s] = load_weight<Narrow>(w, j);
+        wj[s] = load_weight<Narrow>(P.w, j);
     }
 #pragma unroll
     for (uint32_t s = 0; s < U; ++s) {
@@ -286,8 +314,8 @@ __device__ __forceinline__ void chain_block(const LoopParams& P, const ChainFixe
 // once per four steps, lane k of the half-wave makes the call of the k-th
 // four-step block of the block's twenty steps and the others read its words
 // with a cross-lane permute: one call per lane per twenty steps.
-template <int V, bool Narrow, bool Shared = false>
-__device__ __forceinline__ uint32_t run_chain(const LoopParams& P, uint32_t i, uint32_t pos)
+template <int V, bool Narrow, bool Shared = false, typename W>
+__device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i, uint32_t pos)
 {
     ChainFixed F;
     F.i = i;
@@ -308,8 +336,8 @@ __device__ __forceinline__ uint32_t run_chain(const LoopParams& P, uint32_t i, u
     return c.k;
 }
 
-template <int V, bool Narrow, bool Shared = false>
-__device__ __forceinline__ uint32_t run_chain(const LoopParams& P, uint32_t i)
+template <int V, bool Narrow, bool Shared = false, typename W>
+__device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i)
 {
     return run_chain<V, Narrow, Shared>(P, i, i);
 }
@@ -331,76 +359,85 @@ __device__ __forceinline__ uint32_t run_chain(const LoopParams& P, uint32_t i)
 constexpr uint32_t kMirrorPad = 2048;             // >= 256 P + 32 for P <= 4
 constexpr uint32_t kMirrorMaxN = (1u << 29) - 4096;
 
+// What the rounds of a thread's chains share (wave-uniform but the last two).
+struct MirrorLoop {
+    GlobalPtr<const char> M;
+    OffsetPtr offs;
+    uint32_t n, key0, key1, stream_id, seg_mask;
+    uint32_t ia4, il4;  // byte offset of the thread's segment, and of its place in it
+};
+
+// Steps b0 .. b0 + 4 (Partial: b0 .. b0 + cnt - 1) of the chains of particles
+// p0 .. p0 + G - 1 of a thread: candidate loads first, then the draws, then
+// the serial accept steps.
+template <int P, int BT, int G, bool Partial>
+__device__ __forceinline__ void mirror_round(const MirrorLoop& L, uint32_t b0, uint32_t cnt, uint32_t i0, int p0,
+                                             uint32_t (&kk)[P], float (&wk)[P])
+{
+    constexpr uint32_t kStrideBytes = 4u * BT;  // particle p sits BT particles after p - 1
+    uint32_t jb[5];
+    float wj[5][G];
+#pragma unroll
+    for (uint32_t s = 0; s < 5; ++s) {
+        if (Partial && s >= cnt) continue;
+        uint32_t o = L.offs[b0 + s];
+        o = o < L.n ? o : L.n - 1u;
+        const uint32_t oa4 = (o & ~L.seg_mask) * 4u;
+        const uint32_t t4 = (L.il4 + (o & L.seg_mask) * 4u) & (L.seg_mask * 4u);
+        const uint32_t voff = L.ia4 | t4;
+        const GlobalPtr<const char> base = L.M + oa4;
+#pragma unroll
+        for (int q = 0; q < G; ++q) wj[s][q] = *(GlobalPtr<const float>)(base + voff + kStrideBytes * (p0 + q));
+        jb[s] = voff + oa4;
+    }
+    UBlock ub[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q)
+        ub[q] = u_block(philox(b0 / 5u, kTagU, L.stream_id, i0 + BT * (p0 + q), L.key0, L.key1));
+#pragma unroll
+    for (uint32_t s = 0; s < 5; ++s) {
+        if (Partial && s >= cnt) continue;
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const float prod = ub[q].u[s] * wk[p0 + q];
+            const bool acc = prod <= wj[s][q];
+            kk[p0 + q] = acc ? jb[s] : kk[p0 + q];
+            wk[p0 + q] = acc ? wj[s][q] : wk[p0 + q];
+        }
+    }
+}
+
 template <int P, int BT = 256>
-__device__ __forceinline__ void megopolis_mirror_chain(const char* __restrict__ M, const uint32_t* __restrict__ offs,
-                                                       uint32_t n, uint32_t B, uint32_t key0, uint32_t key1,
-                                                       uint32_t stream_id, uint32_t i0, uint32_t (&anc_out)[P],
-                                                       uint32_t seg_mask = kSegment - 1u)
+__device__ __forceinline__ void megopolis_mirror_chain(GlobalPtr<const char> M, OffsetPtr offs, uint32_t n, uint32_t B,
+                                                       uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t i0,
+                                                       uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u)
 {
     static_assert(BT % 64 == 0 && BT * P + 64 <= kMirrorPad, "particles of a thread must fit the padding");
     static_assert(4 * BT * (P - 1) < 4096, "the immediate offset of the last particle must fit 12 bits");
-    constexpr uint32_t kStrideBytes = 4u * BT;  // particle p sits BT particles after p - 1
-    const uint32_t ia4 = (i0 & ~seg_mask) * 4u;
-    const uint32_t il4 = (i0 & seg_mask) * 4u;
+    constexpr int G = P < 4 ? P : 4;  // particles whose loads are in flight together
+    const MirrorLoop L{M, offs, n, key0, key1, stream_id, seg_mask, (i0 & ~seg_mask) * 4u, (i0 & seg_mask) * 4u};
     uint32_t kk[P];  // ancestor as the slot-0 byte offset into M
     float wk[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         kk[p] = i0 * 4u;
-        wk[p] = *reinterpret_cast<const float*>(M + i0 * 4u + kStrideBytes * p);
+        wk[p] = *(GlobalPtr<const float>)(M + i0 * 4u + 4u * BT * p);
     }
-    const uint32_t nblk = B / 5u;
-    for (uint32_t q = 0; q < nblk; ++q) {
-        uint32_t jb[5];
-        float wj[5][P];
+    uint32_t b0 = 0;
+    for (; b0 + 5u <= B; b0 += 5u) {
 #pragma unroll
-        for (uint32_t s = 0; s < 5; ++s) {
-            uint32_t o = offs[q * 5u + s];
-            o = o < n ? o : n - 1u;
-            const uint32_t oa4 = (o & ~seg_mask) * 4u;
-            const uint32_t t4 = (il4 + (o & seg_mask) * 4u) & (seg_mask * 4u);
-            const uint32_t voff = ia4 | t4;
-            const char* base = M + oa4;
-#pragma unroll
-            for (int p = 0; p < P; ++p) wj[s][p] = *reinterpret_cast<const float*>(base + voff + kStrideBytes * p);
-            jb[s] = voff + oa4;
-        }
-        UBlock ub[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p) ub[p] = u_block(philox(q, kTagU, stream_id, i0 + BT * p, key0, key1));
-#pragma unroll
-        for (uint32_t s = 0; s < 5; ++s) {
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const float prod = ub[p].u[s] * wk[p];
-                const bool acc = prod <= wj[s][p];
-                kk[p] = acc ? jb[s] : kk[p];
-                wk[p] = acc ? wj[s][p] : wk[p];
-            }
+        for (int p0 = 0; p0 < P; p0 += G) {
+            mirror_round<P, BT, G, false>(L, b0, 5u, i0, p0, kk, wk);
+            // keep the next particles' loads and draws out of these ones'
+            // registers (eight at once would take 190, two waves per SIMD)
+            if (P > G) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    // remaining B mod 5 steps
-    if (nblk * 5u < B) {
-        UBlock ub[P];
+    if (b0 < B) {
 #pragma unroll
-        for (int p = 0; p < P; ++p) ub[p] = u_block(philox(nblk, kTagU, stream_id, i0 + BT * p, key0, key1));
-        for (uint32_t b = nblk * 5u; b < B; ++b) {
-            uint32_t o = offs[b];
-            o = o < n ? o : n - 1u;
-            const uint32_t oa4 = (o & ~seg_mask) * 4u;
-            const uint32_t t4 = (il4 + (o & seg_mask) * 4u) & (seg_mask * 4u);
-            const uint32_t voff = ia4 | t4;
-            const char* base = M + oa4;
-            const uint32_t r = b - nblk * 5u;
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const float wjv = *reinterpret_cast<const float*>(base + voff + kStrideBytes * p);
-                const float u = r == 0 ? ub[p].u[0] : r == 1 ? ub[p].u[1] : r == 2 ? ub[p].u[2] : ub[p].u[3];
-                const float prod = u * wk[p];
-                const bool acc = prod <= wjv;
-                kk[p] = acc ? voff + oa4 : kk[p];
-                wk[p] = acc ? wjv : wk[p];
-            }
+        for (int p0 = 0; p0 < P; p0 += G) {
+            mirror_round<P, BT, G, true>(L, b0, B - b0, i0, p0, kk, wk);
+            if (P > G) __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
@@ -498,37 +535,32 @@ struct RowCopy {
     uint32_t vec4;        // d % 4 == 0 and both buffers 16-byte aligned: float4 moves
 };
 
-__device__ __forceinline__ void store_stream(float4* p, const float4& v)
-{
-    __builtin_nontemporal_store(v.x, &p->x);
-    __builtin_nontemporal_store(v.y, &p->y);
-    __builtin_nontemporal_store(v.z, &p->z);
-    __builtin_nontemporal_store(v.w, &p->w);
-}
+using Row4 = float __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ Row4 nan_row4() { return Row4{NAN, NAN, NAN, NAN}; }
 
 // Output row i from input row k, one lane, any d: up to four vectors (or
 // four floats) loaded before the first of them is stored, so a row of up to
 // 16 floats costs one round trip.
 __device__ __forceinline__ void copy_row(const RowCopy& g, uint32_t i, int32_t k)
 {
-    const float4 nan4 = make_float4(NAN, NAN, NAN, NAN);
     const uint64_t kr = k < 0 ? 0u : (uint64_t)k;
     if (g.vec4) {
         const uint32_t d4 = g.d >> 2;
-        const float4* src = reinterpret_cast<const float4*>(g.states) + kr * d4;
-        float4* dst = reinterpret_cast<float4*>(g.out) + (uint64_t)i * d4;
+        const GlobalPtr<const Row4> src = global_ptr(reinterpret_cast<const Row4*>(g.states)) + kr * d4;
+        const GlobalPtr<Row4> dst = global_ptr(reinterpret_cast<Row4*>(g.out)) + (uint64_t)i * d4;
         for (uint32_t c = 0; c < d4; c += 4u) {
-            float4 v[4];
+            Row4 v[4];
 #pragma unroll
             for (uint32_t u = 0; u < 4u; ++u)
-                if (c + u < d4) v[u] = k < 0 ? nan4 : src[c + u];
+                if (c + u < d4) v[u] = k < 0 ? nan_row4() : src[c + u];
 #pragma unroll
             for (uint32_t u = 0; u < 4u; ++u)
-                if (c + u < d4) store_stream(dst + c + u, v[u]);
+                if (c + u < d4) __builtin_nontemporal_store(v[u], dst + c + u);
         }
     } else {
-        const float* src = g.states + kr * g.d;
-        float* dst = g.out + (uint64_t)i * g.d;
+        const GlobalPtr<const float> src = global_ptr(g.states) + kr * g.d;
+        const GlobalPtr<float> dst = global_ptr(g.out) + (uint64_t)i * g.d;
         for (uint32_t c = 0; c < g.d; c += 4u) {
             float v[4];
 #pragma unroll
@@ -541,28 +573,79 @@ __device__ __forceinline__ void copy_row(const RowCopy& g, uint32_t i, int32_t k
     }
 }
 
-// The rows of P outputs of one lane with D4 float4s per row known at compile
-// time (g.vec4 set): every load of the P rows is issued before the first
-// store. Outputs with live[p] false are skipped.
-template <int P, int D4>
+// The rows of P outputs of one lane, D4 float4s per row known at compile time
+// (g.vec4 set): the loads of G rows are issued before the first of their
+// stores. Outputs with live[p] false are skipped.
+template <int P, int D4, int G = P>
 __device__ __forceinline__ void copy_rows_vec4(const RowCopy& g, const uint32_t (&i)[P], const int32_t (&k)[P],
                                                const bool (&live)[P])
 {
-    const float4* __restrict__ src = reinterpret_cast<const float4*>(g.states);
-    float4* __restrict__ dst = reinterpret_cast<float4*>(g.out);
-    float4 v[P][D4];
+    static_assert(P % G == 0, "whole groups");
+    const GlobalPtr<const Row4> src = global_ptr(reinterpret_cast<const Row4*>(g.states));
+    const GlobalPtr<Row4> dst = global_ptr(reinterpret_cast<Row4*>(g.out));
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const uint64_t kr = k[p] < 0 ? 0u : (uint64_t)k[p];
+    for (int p0 = 0; p0 < P; p0 += G) {
+        Row4 v[G][D4];
 #pragma unroll
-        for (int c = 0; c < D4; ++c)
-            if (live[p]) v[p][c] = k[p] < 0 ? make_float4(NAN, NAN, NAN, NAN) : src[kr * D4 + c];
+        for (int q = 0; q < G; ++q) {
+            const int p = p0 + q;
+            const uint64_t kr = k[p] < 0 ? 0u : (uint64_t)k[p];
+#pragma unroll
+            for (int c = 0; c < D4; ++c)
+                if (live[p]) v[q][c] = k[p] < 0 ? nan_row4() : src[kr * D4 + c];
+        }
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int p = p0 + q;
+#pragma unroll
+            for (int c = 0; c < D4; ++c)
+                if (live[p]) __builtin_nontemporal_store(v[q][c], dst + (uint64_t)i[p] * D4 + c);
+        }
     }
+}
+
+// The rows of P outputs of one lane, row shape known at run time, in groups
+// of at most four rows and eight vectors in flight, kept apart by scheduling
+// barriers: eight particles' rows at once would take 190 registers, two waves
+// per SIMD for the whole kernel.
+template <int P>
+__device__ __forceinline__ void copy_rows(const RowCopy& g, const uint32_t (&i)[P], const int32_t (&k)[P],
+                                          const bool (&live)[P])
+{
+    constexpr int G = P < 4 ? P : 4;
+    const GlobalPtr<const float> src = global_ptr(g.states);
+    const GlobalPtr<float> dst = global_ptr(g.out);
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
+    for (int p0 = 0; p0 < P; p0 += G) {
+        uint32_t ii[G];
+        int32_t kg[G];
+        bool lg[G];
 #pragma unroll
-        for (int c = 0; c < D4; ++c)
-            if (live[p]) store_stream(dst + (uint64_t)i[p] * D4 + c, v[p][c]);
+        for (int q = 0; q < G; ++q) {
+            ii[q] = i[p0 + q];
+            kg[q] = k[p0 + q];
+            lg[q] = live[p0 + q];
+        }
+        if (g.vec4 && g.d == 4u) {
+            copy_rows_vec4<G, 1>(g, ii, kg, lg);
+        } else if (g.vec4 && g.d == 8u) {
+            copy_rows_vec4<G, 2>(g, ii, kg, lg);
+        } else if (g.d == 1u) {
+            float v[G];
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+                if (lg[q]) v[q] = kg[q] < 0 ? NAN : src[(uint32_t)kg[q]];
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+                if (lg[q]) __builtin_nontemporal_store(v[q], dst + ii[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                if (lg[q]) copy_row(g, ii[q], kg[q]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (P > G) __builtin_amdgcn_sched_barrier(0);
     }
 }
 

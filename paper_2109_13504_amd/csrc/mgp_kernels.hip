@@ -101,7 +101,8 @@ __global__ __launch_bounds__(kLoopThreads) void k_resample(const float* __restri
         // every lane runs a chain, also past m (C2 shares each group's
         // partition draws across its half-wave): output i starts at input
         // i mod n, i itself when i < n
-        LoopParams P{w, offsets, n, B, key0, key1, stream_id, n_w, n_part, seg_mask};
+        const LoopParams<GlobalPtr<const float>> P{global_ptr(w), offset_ptr(offsets), n, B, key0, key1, stream_id,
+                                                   n_w, n_part, seg_mask};
         const uint32_t pos = i < n ? i : i % n;
         k = (int32_t)run_chain<V, Narrow, true>(P, i, pos);
     }
@@ -137,8 +138,8 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_mirror(const float* 
         // every lane runs, also past m (m <= n here): the mirror's padding
         // keeps those loads in bounds, and only real outputs store
         uint32_t kc[P];
-        megopolis_mirror_chain<P>(reinterpret_cast<const char*>(mirror), offsets, n, B, key0, key1, stream_id, i0,
-                                  kc, seg_mask);
+        megopolis_mirror_chain<P>(global_ptr(reinterpret_cast<const char*>(mirror)), offset_ptr(offsets), n, B, key0,
+                                  key1, stream_id, i0, kc, seg_mask);
 #pragma unroll
         for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
     }
@@ -501,7 +502,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_resample_small(const float* __
     if (B > 0) {
         // every lane runs a chain (lanes past n from n - 1's group, whose
         // partition draws C2 shares across the half-wave)
-        const LoopParams P{M, nullptr, n, B, a.key0, a.key1, a.stream_id, n_w, n_part};
+        const LoopParams<const float*> P{M, nullptr, n, B, a.key0, a.key1, a.stream_id, n_w, n_part};
         const uint32_t ic = i < n ? i : n - 1u;
         k = (int32_t)run_chain<V, true, true>(P, ic, ic);
     }
