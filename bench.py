@@ -589,7 +589,7 @@ def m_neq_n_section(torch, mgp, inputs):
         ms = median_call_ms(torch, lambda k: r.resample_m(w, m, "megopolis", epsilon=0.01, seed=k, out=anc))
         B = r.last_stats()["B"]
         out[f"n2^{ln}_m2^{lm}"] = {"ms": ms, "B": B, "outputs_per_s": m / (ms * 1e-3),
-                                   "kernel": "mirrored" if m <= n else "generic",
+                                   "kernel": "windows" if m <= n else "generic",
                                    "effective_GBs": 4.0 * m * (B + 2) / (ms * 1e-3) / 1e9}
         del w, anc, r
     return {"workload": "Megopolis, Gaussian-likelihood weights y=4, eps=0.01; N inputs -> M outputs", "runs": out}
@@ -737,7 +737,7 @@ def main():
     if ceil and n % 1024 == 0 and B >= 5:
         ceil["megopolis_pattern_read"] = pattern_ceiling(torch, mgp, n, 5 * (B // 5))
         pat = ceil["megopolis_pattern_read"]["GBs"]
-    kernel = {"megopolis": f"k_megopolis_mirror<4, {d // 4 if d % 4 == 0 and d <= 16 else -1}>",
+    kernel = {"megopolis": f"k_megopolis<4, 5, {d // 4 if d % 4 == 0 and d <= 16 else -1}>",
               }.get(args.variant, f"k_resample<{args.variant}>")
 
     result = {
@@ -766,7 +766,7 @@ def main():
         "roofline": {
             "kernel": f"{kernel} (accept loop with the particle copy as its epilogue)",
             "bound": "hbm",
-            "level": "memory side of the fabric: the 128 MB weight mirror streams from the 256 MB Infinity Cache "
+            "level": "memory side of the fabric: the 64 MB of weights stream from the 256 MB Infinity Cache "
                      "in front of HBM; the state rows come from and go to HBM",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
@@ -786,7 +786,7 @@ def main():
             "traffic_what": "bytes past the L2 (TCC to fabric: Infinity Cache or HBM), calibrated FETCH_SIZE + "
                             "WRITE_SIZE per launch",
         },
-        "loop_only": {"kernel": "k_megopolis_mirror<4, 0> (accept loop, unfused step)" if args.variant == "megopolis"
+        "loop_only": {"kernel": "k_megopolis<4, 5, 0> (accept loop, unfused step)" if args.variant == "megopolis"
                       else f"k_resample<{args.variant}>",
                       "ms": loop_ms, "bytes_formula": "4NB candidate weights", "bytes": loop_bytes,
                       "GBs": loop_bytes / (loop_ms * 1e-3) / 1e9,

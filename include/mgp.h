@@ -119,7 +119,7 @@ int mgp_resample(const float* w_dev, int32_t n, const mgp_params* params, int32_
  * device current.
  * Sizes: mgp_workspace_size(n, params) must fit the scratch, else MGP_ERANGE
  * and nothing is enqueued. With the default b_max that is n up to about
- * 8.3 million for MGP_MEGOPOLIS (whose workspace holds the 8n-byte mirror)
+ * 8.3 million for MGP_MEGOPOLIS (whose workspace sets 8n bytes aside)
  * and any n for the other variants.
  * Every call on a device shares that device's scratch and leaves its
  * contents there: calls that overlap on one device (different streams
@@ -138,7 +138,7 @@ int mgp_resample_noalloc(const float* w_dev, int32_t n, const mgp_params* params
  * m == n the result equals mgp_resample's.
  * w_dev: n fp32 weights; ancestors_dev: m int32, each in [0, n); workspace:
  * mgp_workspace_size(n, params) bytes; stats_dev, stream: as mgp_resample.
- * Megopolis with m <= n runs the mirrored kernel; m > n the generic one. */
+ * Megopolis with m <= n runs the window kernels; m > n the generic one. */
 int mgp_resample_m(const float* w_dev, int32_t n, int32_t m, const mgp_params* params, int32_t* ancestors_dev,
                    mgp_stats* stats_dev, void* workspace_dev, size_t workspace_bytes, void* stream);
 
@@ -156,7 +156,7 @@ int mgp_compute_B(const float* w_dev, int32_t n, const mgp_params* params, mgp_s
  * (n, variant, seed, stream_id) written by mgp_compute_B, and on a mismatch
  * (or invalid weights) writes -1 to every ancestor. w_dev must hold the same
  * weights as in that call: with MGP_MEGOPOLIS (n <= 2^29 - 4096) the loop
- * reads the mirrored copy of them that mgp_compute_B left in the workspace,
+ * reads the copy of them that mgp_compute_B left in the workspace,
  * not w_dev, so weights changed in between are not seen. */
 int mgp_resample_prepared(const float* w_dev, int32_t n, const mgp_params* params, int32_t* ancestors_dev,
                           void* workspace_dev, size_t workspace_bytes, void* stream);
@@ -245,7 +245,7 @@ typedef struct mgp_batch_info {
 typedef struct mgp_batch_plan mgp_batch_plan;
 
 /* Builds a plan: validates the descriptors, allocates the plan's device
- * memory (per-filter stats, partials, offsets, mirrors, tile tables), runs
+ * memory (per-filter stats, partials, offsets, seams or copies of weights, tile tables), runs
  * the reduction once on `stream` to estimate each filter's B (for load
  * balance only), picks the launch shape (autotuning when asked) and captures
  * the run into a hipGraph. Synchronises `stream`. Caller keeps the filters'
@@ -525,7 +525,7 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
 /* ---- memory-system probes ------------------------------------------------
  * The streaming-read rate of the device at one buffer size: the benchmark
  * reports it as the memory ceiling beside the accept loop's achieved rate
- * (the loop streams its mirrored weights from whichever level holds them).
+ * (the loop streams its weights from whichever level holds them).
  * One launch of `blocks` blocks of 256 threads reads every 16-byte vector of
  * buf_dev[0, bytes) `passes` times (grid-stride, four loads in flight per
  * thread; each pass starts its sweep about 38% of the buffer further on, so
@@ -537,8 +537,8 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
 int mgp_probe_stream_read(const void* buf_dev, size_t bytes, int32_t passes, int32_t blocks, float* sink_dev,
                           void* stream);
 
-/* The Megopolis accept loop's read pattern without its arithmetic: the
- * ceiling the loop's own access pattern sets. n particles, four per thread in
+/* The Megopolis accept loop's read pattern without its arithmetic, over a
+ * mirrored array: the ceiling that access pattern sets. n particles, four per thread in
  * blocks of 256 threads (n / 1024 blocks), read at each of `steps` steps the
  * candidate that Algorithm 5's segment arithmetic gives for the step's offset
  * offsets_dev[b] (steps uint32 values, device; values >= n are clamped to

@@ -2,8 +2,8 @@
 //
 // A run is three kernels:
 //   1. k_batch_reduce   one block per (filter, chunk): fp32 max, fp64 sum and
-//                       validation of the chunk, plus the Megopolis mirror
-//                       M[k] = w[k mod n] of the filter;
+//                       validation of the chunk, plus the seam (or copy) that
+//                       the filter's Megopolis loop reads;
 //   2. k_batch_finalize one block per filter: B from eq. (proposition), the
 //                       stats record and the Megopolis offsets;
 //   3. the accept loop  over (filter, tile) work items, each tile BT * P
@@ -17,7 +17,7 @@
 // plan assigns whole filters to XCDs by longest-processing-time first (cost
 // N_f * B_f, with B_f from one reduction at plan time) and orders the tile
 // table so that every tile of a filter lands on its XCD: a filter's weights
-// (at most 2 MB mirrored for N_f = 2^18) are fetched into one L2 only.
+// (at most 1 MB for N_f = 2^18) are fetched into one L2 only.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -55,11 +55,13 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_reduce(const FilterDev
     float mx = 0.0f;
     double s = 0.0;
     uint32_t bad = 0;
+    const float* w = in_hbm(F.w);
+    float* copy = F.copy ? in_hbm(F.copy) : nullptr;
     if (F.vec)
-        reduce_range<true>(F.w, F.n, start, end, F.mirror, mx, s, bad);
+        reduce_range<true>(w, start, end, copy, mx, s, bad);
     else
-        reduce_range<false>(F.w, F.n, start, end, F.mirror, mx, s, bad);
-    if (F.mirror && t.c == 0) mirror_pad(F.w, F.n, F.mirror);
+        reduce_range<false>(w, start, end, copy, mx, s, bad);
+    if (t.c == 0) write_window_ends(w, F.n, copy, F.seam ? in_hbm(F.seam) : nullptr);
     block_reduce(mx, s, bad);
     if (threadIdx.x == 0) parts[F.part_base + t.c] = Partial{s, mx, bad};
 }
@@ -106,8 +108,7 @@ __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats
     if (st->status == MGP_OK) {
         if constexpr (V == kMegopolis) {
             uint32_t kc[P];
-            megopolis_mirror_chain<P, BT>(global_ptr(reinterpret_cast<const char*>(F.mirror)), offset_ptr(F.offsets),
-                                          n, B, F.key0, F.key1, F.stream_id, start + threadIdx.x, kc);
+            megopolis_chain<P, BT, 5>(F.windows, offset_ptr(F.offsets), n, B, F.key0, F.key1, F.stream_id, start, kc);
 #pragma unroll
             for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
         } else {
@@ -131,20 +132,17 @@ __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats
 // Minimum waves per SIMD asked of the compiler for the grid-scheduled
 // accept loop. C2's shared partition draws raise its register count to 78
 // (6 waves); asked for 7 it schedules the loop into 70 registers without
-// spilling: 7% and 13% faster at B = 32 and 64, equal at B = 16. Megopolis
-// with eight particles per thread takes 89 registers (5 waves) unless asked
-// for 7: 717 against 778 us on the 512-filter batch. The others are left to the compiler: C1, Metropolis and the
-// persistent kernel (whose queue logic adds registers) would spill at 7, and
-// Megopolis with four particles, 73 registers or 6 waves, spills when asked
-// for 8 and is then 1-2% slower (the 512-filter batch: 699 against 689 us).
-template <int V, int P>
+// spilling: 7% and 13% faster at B = 32 and 64, equal at B = 16. The others,
+// and the persistent kernel (whose queue logic adds registers), are left to
+// the compiler: asked for 7 or 8 they would spill.
+template <int V>
 struct LoopWaves {
-    static constexpr int value = V == kC2 ? 7 : P == 8 ? 7 : 1;
+    static constexpr int value = V == kC2 ? 7 : 1;
 };
 
 // One block per tile, tiles ordered so that block b runs on XCD b mod 8.
 template <int V, int BT, int P>
-__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(LoopWaves<V, P>::value)))
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(LoopWaves<V>::value)))
 void k_batch_loop_grid(const FilterDev* __restrict__ fd, const mgp_stats* __restrict__ stats,
                        const LTile* __restrict__ tiles, uint32_t d)
 {
@@ -501,6 +499,35 @@ int validate(const mgp_filter_desc* f, int32_t count, const mgp_batch_config* cf
     return MGP_OK;
 }
 
+// Which filters' weights the Megopolis loop may read in place: 128-byte
+// aligned, and overlapped by no output of any filter of the batch (a copy is
+// made before the first output is written).
+std::vector<bool> filters_in_place(const mgp_filter_desc* f, int32_t count, uint32_t d)
+{
+    std::vector<std::pair<uintptr_t, uintptr_t>> outs;  // [begin, end) of every output
+    auto add = [&](const void* at, uint64_t bytes) {
+        if (at && bytes) outs.push_back({(uintptr_t)at, (uintptr_t)at + bytes});
+    };
+    for (int32_t i = 0; i < count; ++i) {
+        const uint64_t n = (uint64_t)f[i].n;
+        add(f[i].ancestors_dev, 4u * n);
+        if (f[i].states_dev) add(f[i].out_states_dev, 4u * n * d);
+        add(f[i].stats_dev, sizeof(mgp_stats));
+    }
+    std::sort(outs.begin(), outs.end());
+    // the furthest end among the outputs that begin no later than each one
+    std::vector<uintptr_t> reach(outs.size());
+    for (size_t k = 0; k < outs.size(); ++k) reach[k] = std::max(outs[k].second, k ? reach[k - 1] : 0);
+    std::vector<bool> ok(count);
+    for (int32_t i = 0; i < count; ++i) {
+        const uintptr_t w0 = (uintptr_t)f[i].w_dev, w1 = w0 + 4u * (uint64_t)f[i].n;
+        // outputs that begin before the weights end; the furthest of them
+        const size_t k = std::lower_bound(outs.begin(), outs.end(), std::make_pair(w1, (uintptr_t)0)) - outs.begin();
+        ok[i] = in_place(f[i].w_dev, (uint32_t)f[i].n, nullptr, 0) && !(k && reach[k - 1] > w0);
+    }
+    return ok;
+}
+
 std::string cache_key(const mgp_batch_plan* p, const char* arch)
 {
     // size class of the batch: filter count, total particles and mean B, in
@@ -704,15 +731,17 @@ int mgp_batch_plan_create(const mgp_filter_desc* filters, int32_t count, const m
     off = align256(off + sizeof(mgp_stats) * (size_t)count);
     const size_t o_q = off;
     off = align256(off + sizeof(uint32_t) * 2 * (kMaxXcd + 1));
-    std::vector<size_t> o_offs(count, 0), o_mirror(count, 0);
+    std::vector<size_t> o_offs(count, 0), o_aux(count, 0);
+    std::vector<bool> inplace;
+    if (mego) inplace = filters_in_place(filters, count, p->d);
     if (mego) {
         for (int f = 0; f < count; ++f) {
             o_offs[f] = off;
             off = align256(off + sizeof(uint32_t) * (size_t)p->b_max);
         }
         for (int f = 0; f < count; ++f) {
-            o_mirror[f] = off;
-            off = align256(off + sizeof(float) * (2 * (size_t)filters[f].n + kMirrorPad));
+            o_aux[f] = off;
+            off = align256(off + sizeof(float) * window_floats(inplace[f], (uint32_t)filters[f].n));
         }
     }
     p->dmem_bytes = off;
@@ -736,10 +765,10 @@ int mgp_batch_plan_create(const mgp_filter_desc* filters, int32_t count, const m
         F.states = x.states_dev;
         F.out = x.states_dev ? x.out_states_dev : nullptr;
         F.stats_user = x.stats_dev;
-        F.mirror = mego ? reinterpret_cast<float*>(p->dmem + o_mirror[f]) : nullptr;
         F.offsets = mego ? reinterpret_cast<uint32_t*>(p->dmem + o_offs[f]) : nullptr;
         F.eps = x.epsilon;
         F.n = (uint32_t)x.n;
+        if (mego) F.set_windows(inplace[f], reinterpret_cast<float*>(p->dmem + o_aux[f]));
         F.B_user = x.B;
         F.b_max = p->b_max;
         F.key0 = (uint32_t)x.seed;
@@ -750,7 +779,7 @@ int mgp_batch_plan_create(const mgp_filter_desc* filters, int32_t count, const m
         F.chunk = chunks[f];
         F.n_w = n_w;
         F.n_part = (uint32_t)(((uint64_t)F.n + n_w - 1u) / n_w);
-        F.vec = (((uintptr_t)x.w_dev & 15u) == 0 && (!mego || F.n % 4u == 0)) ? 1u : 0u;
+        F.vec = ((uintptr_t)x.w_dev & 15u) == 0 ? 1u : 0u;
         F.rows4 = (p->d % 4u == 0 && ((uintptr_t)x.states_dev & 15u) == 0 && ((uintptr_t)x.out_states_dev & 15u) == 0)
                       ? 1u
                       : 0u;

@@ -14,7 +14,7 @@
 namespace mgp {
 
 constexpr uint32_t kNoFilter = 0xFFFFFFFFu;
-constexpr uint32_t kBatchMaxN = kMirrorMaxN;
+constexpr uint32_t kBatchMaxN = kWindowMaxN;
 constexpr int kMaxXcd = 8;
 
 // Per-filter record in device memory (read with scalar loads).
@@ -24,7 +24,9 @@ struct FilterDev {
     const float* states;
     float* out;
     mgp_stats* stats_user;
-    float* mirror;       // Megopolis: 2n + kMirrorPad floats, else null
+    Windows windows;     // Megopolis: the accept loop's weights
+    float* copy;         // Megopolis, weights not readable in place: the copy (n + kSeam floats) the reduction makes
+    float* seam;         // Megopolis, weights read in place: their seam (2 kSeam floats), else null
     uint32_t* offsets;   // Megopolis: b_max entries, else null
     double eps;
     uint32_t n;
@@ -39,7 +41,18 @@ struct FilterDev {
     uint32_t vec;        // the reduction may use float4 loads
     uint32_t rows4;      // the gather may use float4 rows
     uint32_t pad[3];
+
+    // The Megopolis windows: w in place with its seam at `aux`, or a copy there.
+    void set_windows(bool in_place, float* aux)
+    {
+        copy = in_place ? nullptr : aux;
+        seam = in_place ? aux : nullptr;
+        windows = in_place ? windows_in_place(w, aux, n) : windows_copy(aux);
+    }
 };
+
+// Floats of a filter's window region.
+inline size_t window_floats(bool in_place, uint32_t n) { return in_place ? 2u * (size_t)kSeam : (size_t)n + kSeam; }
 
 struct RTile {
     uint32_t f, c;
@@ -64,7 +77,7 @@ void build_tile_table(const std::vector<uint32_t>& n, const std::vector<double>&
 // Enqueues one batched run: the segmented reduction, one finalize block per
 // filter, and the accept loop with the fused gather. With n_rt == 0 the
 // reduction is skipped: the producer of the weights has already written
-// every filter's partials (and, for Megopolis, its mirror).
+// every filter's partials (and, for Megopolis, its seam).
 int enqueue_batch(int variant, const LoopShape& sh, const FilterDev* d_fd, uint32_t count, const RTile* d_rt,
                   uint32_t n_rt, Partial* d_parts, mgp_stats* d_stats, const LTile* d_lt, uint32_t grid,
                   const uint32_t* d_qoff, uint32_t* d_qcount, uint32_t nxcd, uint32_t d, hipStream_t s);

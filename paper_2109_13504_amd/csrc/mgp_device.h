@@ -156,6 +156,13 @@ __device__ __forceinline__ GlobalPtr<T> global_ptr(T* p)
     return (GlobalPtr<T>)(uintptr_t)p;
 }
 
+// A pointer known to the compiler to lie in HBM.
+template <typename T>
+__device__ __forceinline__ T* in_hbm(T* p)
+{
+    return (T*)global_ptr(p);
+}
+
 __device__ __forceinline__ OffsetPtr offset_ptr(const uint32_t* p) { return (OffsetPtr)(uintptr_t)p; }
 
 // Loads w[j]. With `Narrow` the byte offset fits 32 bits (n <= 2^30), which
@@ -343,182 +350,171 @@ __device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i
 }
 
 // ---------------------------------------------------------------------------
-// Megopolis over a mirrored weight array.
+// Megopolis by windows of consecutive weights.
 //
-// M[k] = w[k mod n] for k < 2n + kMirrorPad. The candidate of Algorithm 5,
-// (i_aligned + o_aligned + (i + o) mod 32) mod N, is then simply
-// M[i_aligned + o_aligned + (i + o) mod 32]: the sum is at most 2n - 2 for a
-// real particle, so the mod N moves from every load to the one final
-// ancestor. Each thread carries P particles i0 + BT p (BT = block size);
-// they share i mod 32, so all P candidates of a step are the slot-0
-// candidate plus BT p, and the P loads differ only in their immediate byte
-// offset (4 BT p). The segment width S = seg_mask + 1 (32 or 64) divides BT,
-// so the P particles of a thread also share i mod S.
-// Byte offsets must fit 32 bits: 4 (2n + kMirrorPad) < 2^32.
+// A block's T particles start at a multiple of the segment width S, so at a
+// step with offset o their candidates (i_aligned + o_aligned + (i + o) mod S)
+// mod N (Algorithm 5) are the T consecutive positions from
+// s = (start + o_aligned) mod N on, permuted inside segments. s is the same
+// for the whole block, so the mod N is one scalar compare and subtraction per
+// step, and only a window that runs past the end of the weights needs care:
+// it is read from the seam, a copy of the last and first kSeam weights one
+// after the other, and every other window from the caller's weights as they
+// lie. Each thread carries P particles BT apart that share one vector offset;
+// their loads differ only in the immediate byte offset (4 BT p).
+//
+// The caller's weights are read in place when they are 128-byte aligned (a
+// 32-weight segment is then one cache line; elsewhere it would straddle two,
+// three lines per wave and step instead of two) and no output overlaps them.
+// Otherwise, and for mgp_compute_B (whose prepared loop must not see weights
+// changed since), the reduction makes a copy of n + kSeam weights, the first
+// kSeam repeated at the end, which serves every window. Against the earlier
+// copy M[k] = w[k mod n], k < 2n, for every call, reading in place saves 8 of
+// the reduction's 12 bytes per weight (2^24 weights: 13 against 34 us) and
+// halves what the loop's reads spread over (a run of the 512-filter batch 668
+// to 626 us, an SIR step of 64 x 2^20 particles 1106 to 1043).
+// Byte offsets must fit 32 bits: 4 (n + 2 kSeam) < 2^32.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kMirrorPad = 2048;             // >= 256 P + 32 for P <= 4
-constexpr uint32_t kMirrorMaxN = (1u << 29) - 4096;
+constexpr uint32_t kSeam = 1024;                  // particles per block at most
+constexpr uint32_t kWindowMaxN = (1u << 29) - 4096;
+constexpr uint32_t kLayoutInPlace = 1u, kLayoutCopy = 2u;  // where the windows lie
 
-// What the rounds of a thread's chains share (wave-uniform but the last two).
-struct MirrorLoop {
-    GlobalPtr<const char> M;
-    OffsetPtr offs;
-    uint32_t n, key0, key1, stream_id, seg_mask;
-    uint32_t ia4, il4;  // byte offset of the thread's segment, and of its place in it
+// Byte addresses of the weights: position k of a window that starts at s is at
+// (s + T <= n ? w : seam) + 4 k.
+struct Windows {
+    uint64_t w, seam;
 };
 
-// Steps b0 .. b0 + 4 (Partial: b0 .. b0 + cnt - 1) of the chains of particles
-// p0 .. p0 + G - 1 of a thread: candidate loads first, then the draws, then
-// the serial accept steps.
-template <int P, int BT, int G, bool Partial>
-__device__ __forceinline__ void mirror_round(const MirrorLoop& L, uint32_t b0, uint32_t cnt, uint32_t i0, int p0,
+__host__ __device__ __forceinline__ Windows windows_in_place(const float* w, const float* seam, uint32_t n)
+{
+    return Windows{(uint64_t)(uintptr_t)w, (uint64_t)(uintptr_t)seam + 4u * (uint64_t)kSeam - 4u * (uint64_t)n};
+}
+
+__host__ __device__ __forceinline__ Windows windows_copy(const float* copy)
+{
+    return Windows{(uint64_t)(uintptr_t)copy, (uint64_t)(uintptr_t)copy};
+}
+
+__device__ __forceinline__ GlobalPtr<const char> window_at(const Windows& W, uint32_t s, uint32_t n, uint32_t tile)
+{
+    return (GlobalPtr<const char>)((s + tile <= n ? W.w : W.seam) + 4u * (uint64_t)s);
+}
+
+// s = (start + o_aligned) mod n for start < n, o < n.
+__device__ __forceinline__ uint32_t window_start(uint32_t start, uint32_t o, uint32_t seg_mask, uint32_t n)
+{
+    const uint32_t s = start + (o & ~seg_mask);
+    return s >= n ? s - n : s;
+}
+
+// The seam of w: seam[k] = w[(n - kSeam + k) mod n], k < 2 kSeam (one block
+// writes it).
+__device__ __forceinline__ void write_seam(const float* __restrict__ w, uint32_t n, float* __restrict__ seam)
+{
+    const uint32_t shift = n - kSeam % n;
+    for (uint32_t k = threadIdx.x; k < 2u * kSeam; k += blockDim.x) seam[k] = w[(k + shift) % n];
+}
+
+// What the rounds of a thread's chains share (wave-uniform but the last two).
+struct WindowLoop {
+    Windows W;
+    OffsetPtr offs;
+    uint32_t n, key0, key1, stream_id, seg_mask;
+    uint32_t start;     // the block's first particle
+    uint32_t la4, ll4;  // byte offset of the thread's segment in the window, and of its place in the segment
+};
+
+// Steps b0 .. b0 + D - 1 (Partial: b0 .. b0 + cnt - 1; b0 a multiple of 5) of
+// the chains of particles p0 .. p0 + G - 1 of a thread: candidate loads first
+// (they do not depend on the chain), then the draws, then the serial accept
+// steps.
+template <int P, int BT, int G, int D, bool Partial>
+__device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t b0, uint32_t cnt, int p0,
                                              uint32_t (&kk)[P], float (&wk)[P])
 {
-    constexpr uint32_t kStrideBytes = 4u * BT;  // particle p sits BT particles after p - 1
-    uint32_t jb[5];
-    float wj[5][G];
+    static_assert(D % 5 == 0, "a round covers whole blocks of five u draws");
+    const OffsetPtr offs = L.offs + b0;
+    const uint32_t i0 = L.start + threadIdx.x;
+    uint32_t jb[D];
+    float wj[D][G];
 #pragma unroll
-    for (uint32_t s = 0; s < 5; ++s) {
+    for (uint32_t s = 0; s < D; ++s) {
         if (Partial && s >= cnt) continue;
-        uint32_t o = L.offs[b0 + s];
-        o = o < L.n ? o : L.n - 1u;
-        const uint32_t oa4 = (o & ~L.seg_mask) * 4u;
-        const uint32_t t4 = (L.il4 + (o & L.seg_mask) * 4u) & (L.seg_mask * 4u);
-        const uint32_t voff = L.ia4 | t4;
-        const GlobalPtr<const char> base = L.M + oa4;
+        uint32_t o = offs[s];
+        o = o < L.n ? o : L.n - 1u;  // a workspace not written by this call cannot steer a load out of bounds
+        const uint32_t at = window_start(L.start, o, L.seg_mask, L.n);
+        const uint32_t voff = L.la4 | ((L.ll4 + (o & L.seg_mask) * 4u) & (L.seg_mask * 4u));
+        const GlobalPtr<const char> base = window_at(L.W, at, L.n, P * BT);
 #pragma unroll
-        for (int q = 0; q < G; ++q) wj[s][q] = *(GlobalPtr<const float>)(base + voff + kStrideBytes * (p0 + q));
-        jb[s] = voff + oa4;
+        for (int q = 0; q < G; ++q) wj[s][q] = *(GlobalPtr<const float>)(base + voff + 4u * BT * (p0 + q));
+        jb[s] = voff + 4u * at;
     }
-    UBlock ub[G];
 #pragma unroll
-    for (int q = 0; q < G; ++q)
-        ub[q] = u_block(philox(b0 / 5u, kTagU, L.stream_id, i0 + BT * (p0 + q), L.key0, L.key1));
-#pragma unroll
-    for (uint32_t s = 0; s < 5; ++s) {
-        if (Partial && s >= cnt) continue;
+    for (uint32_t g = 0; g < D / 5; ++g) {
+        if (Partial && g * 5u >= cnt) continue;
+        UBlock ub[G];
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-            const float prod = ub[q].u[s] * wk[p0 + q];
-            const bool acc = prod <= wj[s][q];
-            kk[p0 + q] = acc ? jb[s] : kk[p0 + q];
-            wk[p0 + q] = acc ? wj[s][q] : wk[p0 + q];
+            const uint32_t i = (Partial && D > 5) ? pinned(i0 + BT * (p0 + q)) : i0 + BT * (p0 + q);
+            ub[q] = u_block(philox(b0 / 5u + g, kTagU, L.stream_id, i, L.key0, L.key1));
+        }
+#pragma unroll
+        for (uint32_t s = 0; s < 5; ++s) {
+            if (Partial && g * 5u + s >= cnt) continue;
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const float prod = ub[q].u[s] * wk[p0 + q];
+                const bool acc = prod <= wj[g * 5 + s][q];
+                kk[p0 + q] = acc ? jb[g * 5 + s] : kk[p0 + q];
+                wk[p0 + q] = acc ? wj[g * 5 + s][q] : wk[p0 + q];
+            }
         }
     }
 }
 
-template <int P, int BT = 256>
-__device__ __forceinline__ void megopolis_mirror_chain(GlobalPtr<const char> M, OffsetPtr offs, uint32_t n, uint32_t B,
-                                                       uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t i0,
-                                                       uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u)
+// The B-step chains of a thread's particles start + threadIdx.x + BT p, p < P
+// (lanes past n run too and return some ancestor), in rounds of D steps.
+template <int P, int BT, int D>
+__device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs, uint32_t n, uint32_t B,
+                                                uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t start,
+                                                uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u)
 {
-    static_assert(BT % 64 == 0 && BT * P + 64 <= kMirrorPad, "particles of a thread must fit the padding");
+    static_assert(BT % 64 == 0 && BT * P <= (int)kSeam, "a block's window must fit the seam");
     static_assert(4 * BT * (P - 1) < 4096, "the immediate offset of the last particle must fit 12 bits");
-    constexpr int G = P < 4 ? P : 4;  // particles whose loads are in flight together
-    const MirrorLoop L{M, offs, n, key0, key1, stream_id, seg_mask, (i0 & ~seg_mask) * 4u, (i0 & seg_mask) * 4u};
-    uint32_t kk[P];  // ancestor as the slot-0 byte offset into M
+    // Particles whose loads and draws are in flight together. Eight at once
+    // would take 190 registers (two waves per SIMD); in pairs, kept apart by
+    // scheduling barriers, 82.
+    constexpr int G = P == 8 ? 2 : P;
+    const uint32_t t = threadIdx.x;
+    const WindowLoop L{W, offs, n, key0, key1, stream_id, seg_mask, start, (t & ~seg_mask) * 4u, (t & seg_mask) * 4u};
+    uint32_t kk[P];  // ancestor as the byte offset of particle 0's position
     float wk[P];
+    const GlobalPtr<const char> own = window_at(W, start, n, P * BT);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        kk[p] = i0 * 4u;
-        wk[p] = *(GlobalPtr<const float>)(M + i0 * 4u + 4u * BT * p);
+        kk[p] = (start + t) * 4u;
+        wk[p] = *(GlobalPtr<const float>)(own + t * 4u + 4u * BT * p);
     }
     uint32_t b0 = 0;
-    for (; b0 + 5u <= B; b0 += 5u) {
+    for (; b0 + (uint32_t)D <= B; b0 += D) {
 #pragma unroll
         for (int p0 = 0; p0 < P; p0 += G) {
-            mirror_round<P, BT, G, false>(L, b0, 5u, i0, p0, kk, wk);
-            // keep the next particles' loads and draws out of these ones'
-            // registers (eight at once would take 190, two waves per SIMD)
+            window_round<P, BT, G, D, false>(L, b0, D, p0, kk, wk);
             if (P > G) __builtin_amdgcn_sched_barrier(0);
         }
     }
     if (b0 < B) {
 #pragma unroll
         for (int p0 = 0; p0 < P; p0 += G) {
-            mirror_round<P, BT, G, true>(L, b0, B - b0, i0, p0, kk, wk);
+            window_round<P, BT, G, D, true>(L, b0, B - b0, p0, kk, wk);
             if (P > G) __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        uint32_t k = kk[p] / 4u + BT * p;
+        const uint32_t k = kk[p] / 4u + BT * p;
         anc_out[p] = k >= n ? k - n : k;
     }
-}
-
-// Megopolis over the mirror, one particle per thread, with the candidate
-// weights of D steps (D a multiple of 5) loaded before the first of them is
-// used. The candidates do not depend on the accept results, so one round
-// trip to memory serves D steps; for small n, where too few waves are in
-// flight to hide the latency of the B/5 rounds of the chain above, this cuts
-// the number of round trips by D/5. The arithmetic and the random draws are
-// those of megopolis_mirror_chain, so the ancestors are identical.
-template <int D>
-__device__ __forceinline__ uint32_t megopolis_mirror_chain_deep(const char* __restrict__ M,
-                                                                const uint32_t* __restrict__ offs, uint32_t n,
-                                                                uint32_t B, uint32_t key0, uint32_t key1,
-                                                                uint32_t stream_id, uint32_t i, uint32_t seg_mask)
-{
-    static_assert(D % 5 == 0, "a round covers whole blocks of five u draws");
-    const uint32_t ia4 = (i & ~seg_mask) * 4u;
-    const uint32_t il4 = (i & seg_mask) * 4u;
-    uint32_t kk = i * 4u;
-    float wk = *reinterpret_cast<const float*>(M + i * 4u);
-    // steps [0, B5) in rounds of D, then whole blocks of 5, then the rest
-    const uint32_t nrnd = B / D;
-    for (uint32_t q = 0; q < nrnd; ++q) {
-        float wj[D];
-        uint32_t jb[D];
-#pragma unroll
-        for (uint32_t s = 0; s < D; ++s) {
-            uint32_t o = offs[q * D + s];
-            o = o < n ? o : n - 1u;
-            const uint32_t oa4 = (o & ~seg_mask) * 4u;
-            const uint32_t voff = ia4 | ((il4 + (o & seg_mask) * 4u) & (seg_mask * 4u));
-            wj[s] = *reinterpret_cast<const float*>(M + oa4 + voff);
-            jb[s] = voff + oa4;
-        }
-#pragma unroll
-        for (uint32_t g = 0; g < D / 5; ++g) {
-            const UBlock ub = u_block(philox(q * (D / 5) + g, kTagU, stream_id, i, key0, key1));
-#pragma unroll
-            for (uint32_t s = 0; s < 5; ++s) {
-                const float prod = ub.u[s] * wk;
-                const bool acc = prod <= wj[g * 5 + s];
-                kk = acc ? jb[g * 5 + s] : kk;
-                wk = acc ? wj[g * 5 + s] : wk;
-            }
-        }
-    }
-    for (uint32_t b0 = nrnd * D; b0 < B; b0 += 5u) {
-        const uint32_t cnt = B - b0 < 5u ? B - b0 : 5u;
-        float wj[5];
-        uint32_t jb[5];
-#pragma unroll
-        for (uint32_t s = 0; s < 5; ++s) {
-            if (s < cnt) {
-                uint32_t o = offs[b0 + s];
-                o = o < n ? o : n - 1u;
-                const uint32_t oa4 = (o & ~seg_mask) * 4u;
-                const uint32_t voff = ia4 | ((il4 + (o & seg_mask) * 4u) & (seg_mask * 4u));
-                wj[s] = *reinterpret_cast<const float*>(M + oa4 + voff);
-                jb[s] = voff + oa4;
-            }
-        }
-        const UBlock ub = u_block(philox(b0 / 5u, kTagU, stream_id, i, key0, key1));
-#pragma unroll
-        for (uint32_t s = 0; s < 5; ++s) {
-            if (s < cnt) {
-                const float prod = ub.u[s] * wk;
-                const bool acc = prod <= wj[s];
-                kk = acc ? jb[s] : kk;
-                wk = acc ? wj[s] : wk;
-            }
-        }
-    }
-    const uint32_t k = kk / 4u;
-    return k >= n ? k - n : k;
 }
 
 // ---------------------------------------------------------------------------

@@ -21,11 +21,17 @@ constexpr uint32_t kDefaultBMax = 65536;
 constexpr uint32_t kBMaxLimit = 1u << 24;
 
 // Workspace layout of a single-filter call (byte offsets, 256-aligned):
-//   [stats: mgp_stats][partials: kMaxPartials x Partial][offsets: b_max x u32]
-//   [mirror: (2n + kMirrorPad) x f32, Megopolis with n <= kMirrorMaxN only]
+//   [stats: mgp_stats][layout: u32][partials: kMaxPartials x Partial]
+//   [offsets: b_max x u32]
+//   [windows: (2n + 2048) x f32 reserved, Megopolis with n <= kWindowMaxN
+//    only: the seam (2 kSeam weights) or the copy (n + kSeam), as `layout`
+//    (kLayoutInPlace or kLayoutCopy) says]
 constexpr size_t kWsStatsOffset = 0;
+constexpr size_t kWsLayoutOffset = 128;
 constexpr size_t kWsPartialsOffset = 256;
-constexpr int kMegopolisPPT = 4;  // particles per thread of the mirrored Megopolis loop
+constexpr uint32_t kWindowReserve = 2048;  // of the reserved 2n + 2048: >= 2 kSeam, and >= kSeam - n
+static_assert(kWindowReserve >= 2 * kSeam, "the seam must fit the reserved region");
+constexpr int kMegopolisPPT = 4;  // particles per thread of the large Megopolis loop
 
 struct Partial {
     double w_sum;
@@ -74,11 +80,19 @@ int check_launch(const char* what);
 int normalize_params(const mgp_params* in, Params* out);
 size_t workspace_bytes(uint32_t b_max);
 size_t workspace_bytes(uint32_t n, const Params& p);
-bool uses_mirror(uint32_t n, int variant);
-size_t mirror_offset(uint32_t b_max);
+bool uses_windows(uint32_t n, int variant);
+size_t windows_offset(uint32_t b_max);
 uint32_t reduce_blocks(uint32_t n);
 uint32_t reduce_chunk(uint32_t n, uint32_t blocks);
-int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, char* ws,
+// Whether a Megopolis loop may read w in place: 128-byte aligned, and none of
+// the byte ranges [out, out + bytes) of its outputs overlaps it.
+struct OutRange {
+    const void* at;
+    uint64_t bytes;
+};
+bool in_place(const float* w, uint32_t n, const OutRange* outs, int count);
+// layout: kLayoutInPlace or kLayoutCopy (Megopolis with windows), else unused.
+int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
                             mgp_stats* st_user, hipStream_t stream);
 // The accept loop (after the reduction and finalize launches); with rc.states
 // set, the particle copy x_bar_i = x_{k_i} runs as its epilogue. anc may be

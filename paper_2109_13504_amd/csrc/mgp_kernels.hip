@@ -46,15 +46,22 @@ int check_launch(const char* what)
 //    The block decomposition depends on n only, so the fp64 sum (and B) is
 //    the same on every call.
 // ---------------------------------------------------------------------------
-// Block b reduces w[b*chunk, min(n, (b+1)*chunk)); chunk is a multiple of 4
-// and, with Vec, w is 16-byte aligned so float4 loads stay aligned (with a
-// mirror, Vec also needs n % 4 == 0). Block 0 also writes the mirror's
-// padding.
+// Block b < nparts reduces w[b*chunk, min(n, (b+1)*chunk)); chunk is a
+// multiple of 4 and, with Vec, w is 16-byte aligned so float4 loads stay
+// aligned. For a Megopolis loop (layout != null) one more block writes the
+// ends of the loop's windows, beside the others rather than after one of them,
+// and the layout that the loop finds there.
 template <bool Vec>
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restrict__ w, uint32_t n,
-                                                           uint32_t chunk, Partial* __restrict__ part,
-                                                           float* __restrict__ mirror)
+                                                           uint32_t chunk, uint32_t nparts, Partial* __restrict__ part,
+                                                           float* __restrict__ copy, float* __restrict__ seam,
+                                                           uint32_t* __restrict__ layout)
 {
+    if (blockIdx.x == nparts) {
+        write_window_ends(w, n, copy, seam);
+        if (threadIdx.x == 0) *layout = seam ? kLayoutInPlace : kLayoutCopy;
+        return;
+    }
     // trailing blocks may start at or past n when chunk was rounded up: their
     // range is empty and they contribute the neutral partial
     const uint64_t start = (uint64_t)blockIdx.x * chunk;
@@ -63,8 +70,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restri
     float mx = 0.0f;
     double s = 0.0;
     uint32_t bad = 0;
-    reduce_range<Vec>(w, n, start, end, mirror, mx, s, bad);
-    if (mirror && blockIdx.x == 0) mirror_pad(w, n, mirror);
+    reduce_range<Vec>(w, start, end, copy, mx, s, bad);
     block_reduce(mx, s, bad);
     if (threadIdx.x == 0) part[blockIdx.x] = Partial{s, mx, bad};
 }
@@ -111,18 +117,30 @@ __global__ __launch_bounds__(kLoopThreads) void k_resample(const float* __restri
     if (rc.states) copy_row(rc, i, k);
 }
 
-// Megopolis over the mirrored weights, kMegopolisPPT particles per thread.
-// Rows selects the particle copy of the epilogue: 0 none, D4 > 0 rows of D4
-// float4s, -1 any row shape (copy_row).
-template <int P, int Rows>
-__global__ __launch_bounds__(kLoopThreads) void k_megopolis_mirror(const float* __restrict__ mirror, uint32_t n,
-                                                                   uint32_t m, const mgp_stats* __restrict__ st,
-                                                                   const uint32_t* __restrict__ offsets,
-                                                                   uint32_t key0, uint32_t key1, uint32_t stream_id,
-                                                                   uint32_t tag, uint32_t b_cap, uint32_t seg_mask,
-                                                                   int32_t* __restrict__ anc, RowCopy rc)
+// Where a single filter's Megopolis loop finds its windows.
+struct WindowArgs {
+    const float* w;
+    const float* aux;        // the workspace's window region: the seam or the copy
+    const uint32_t* layout;  // which of the two, written by the reduction
+};
+
+__device__ __forceinline__ Windows load_windows(const WindowArgs& a, uint32_t n)
 {
-    const uint32_t i0 = blockIdx.x * (kLoopThreads * P) + threadIdx.x;
+    return *a.layout == kLayoutInPlace ? windows_in_place(a.w, a.aux, n) : windows_copy(a.aux);
+}
+
+// Megopolis by windows, P particles per thread, rounds of D steps. Rows
+// selects the particle copy of the epilogue: 0 none, D4 > 0 rows of D4
+// float4s, -1 any row shape (copy_row).
+template <int P, int D, int Rows>
+__global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint32_t n, uint32_t m,
+                                                            const mgp_stats* __restrict__ st,
+                                                            const uint32_t* __restrict__ offsets, uint32_t key0,
+                                                            uint32_t key1, uint32_t stream_id, uint32_t tag,
+                                                            uint32_t b_cap, uint32_t seg_mask,
+                                                            int32_t* __restrict__ anc, RowCopy rc)
+{
+    const uint32_t start = blockIdx.x * (kLoopThreads * P);
     const uint32_t B = st->B;
     const bool ok = st->status == MGP_OK && st->tag == tag && st->n == n && B <= b_cap;
     uint32_t idx[P];
@@ -130,16 +148,16 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_mirror(const float* 
     bool live[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        idx[p] = i0 + kLoopThreads * p;
+        idx[p] = start + threadIdx.x + kLoopThreads * p;
         live[p] = idx[p] < m;
         k[p] = -1;
     }
     if (ok) {
-        // every lane runs, also past m (m <= n here): the mirror's padding
+        // every lane runs, also past m (start < m <= n here): the window
         // keeps those loads in bounds, and only real outputs store
         uint32_t kc[P];
-        megopolis_mirror_chain<P>(global_ptr(reinterpret_cast<const char*>(mirror)), offset_ptr(offsets), n, B, key0,
-                                  key1, stream_id, i0, kc, seg_mask);
+        megopolis_chain<P, (int)kLoopThreads, D>(load_windows(wa, n), offset_ptr(offsets), n, B, key0, key1, stream_id,
+                                                 start, kc, seg_mask);
 #pragma unroll
         for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
     }
@@ -157,39 +175,15 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_mirror(const float* 
     }
 }
 
-// Megopolis over the mirrored weights for small n: one particle per thread,
-// kDeepSteps candidate loads per round trip (megopolis_mirror_chain_deep).
-// Used for m <= kDeepMaxM outputs, where the four-particle kernel leaves too
-// few waves in flight to hide its round trips.
+// For few outputs one particle per thread and rounds of kDeepSteps steps: up
+// to kDeepMaxM the four-particle kernel leaves too few waves in flight to hide
+// its round trips to memory.
 constexpr int kDeepSteps = 20;
 constexpr uint32_t kDeepMaxM = 1u << 18;
 
-__global__ __launch_bounds__(kLoopThreads) void k_megopolis_mirror_deep(const float* __restrict__ mirror, uint32_t n,
-                                                                        uint32_t m, const mgp_stats* __restrict__ st,
-                                                                        const uint32_t* __restrict__ offsets,
-                                                                        uint32_t key0, uint32_t key1,
-                                                                        uint32_t stream_id, uint32_t tag,
-                                                                        uint32_t b_cap, uint32_t seg_mask,
-                                                                        int32_t* __restrict__ anc, RowCopy rc)
-{
-    const uint32_t i = blockIdx.x * kLoopThreads + threadIdx.x;
-    const uint32_t B = st->B;
-    const bool ok = st->status == MGP_OK && st->tag == tag && st->n == n && B <= b_cap;
-    int32_t k = -1;
-    // lanes past m run too (the mirror's padding keeps their loads in bounds)
-    if (ok)
-        k = (int32_t)megopolis_mirror_chain_deep<kDeepSteps>(reinterpret_cast<const char*>(mirror), offsets, n, B,
-                                                             key0, key1, stream_id, i, seg_mask);
-    if (i < m) {
-        if (anc) anc[i] = k;
-        if (rc.states) copy_row(rc, i, k);
-    }
-}
-
-
 // mgp_resample of a small filter in one launch (Megopolis up to kSmallMaxN
 // particles, the other variants up to kSmallMaxNOther): every block copies
-// the weights into LDS as the mirror M[k] = w[k mod n] and repeats the
+// the weights into LDS, M[k] = w[k mod n] for k < n + kSmallPad, and repeats the
 // reduction of k_reduce and k_finalize chunk by chunk in the same order (so
 // the fp64 sum, B and the stats are bit-identical to the three-launch path,
 // B by eq. (proposition) of Section 4.1), then runs the chains of its own
@@ -197,13 +191,13 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_mirror_deep(const fl
 // (Algorithm 5), k_resample_small for Algorithms 2-4.
 constexpr uint32_t kSmallMaxN = 8192;
 constexpr uint32_t kSmallMaxNOther = 4096;  // Metropolis, C1, C2: chains without shared indices gain less
-constexpr uint32_t kSmallPad = 512;       // lanes past n: slot <= n + 255 + n - 1 + 63 < 2n + 512
+constexpr uint32_t kSmallPad = 64;        // a window of 64 particles starts below n
 constexpr uint32_t kSmallMaxParts = kSmallMaxN / kReduceChunk;
 static_assert(kSmallMaxN % kReduceChunk == 0 && kSmallMaxN <= (uint64_t)kReduceChunk * kMaxPartials,
               "the reduction of a small filter has at most kSmallMaxParts chunks");
 
-// The first steps of the one-launch kernels: the LDS mirror
-// M[k] = w[k mod n], k < 2n + kSmallPad, then the reduction and B exactly as
+// The first steps of the one-launch kernels: the weights into LDS,
+// M[k] = w[k mod n], k < n + kSmallPad, then the reduction and B exactly as
 // k_reduce and k_finalize compute them (chunks of `chunk` weights with
 // k_reduce's thread mapping: float4 folds when fold_vec). Block 0 returns the
 // stats. Returns B (0 for invalid weights) in every thread.
@@ -213,7 +207,7 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
                                                    mgp_stats* __restrict__ st_user, float* __restrict__ M,
                                                    Partial* __restrict__ parts, mgp_stats* __restrict__ st_local)
 {
-    // 1. the mirror: every load of a thread is issued before its first LDS
+    // 1. the weights: every load of a thread is issued before its first LDS
     //    store (clamped indices, no branch around a load), so the copy costs
     //    one round trip to L2, not one per element
     if (copy_vec) {  // w 16-byte aligned and n % 4 == 0
@@ -232,7 +226,6 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
             const uint32_t k4 = threadIdx.x + it * kLoopThreads;
             const uint32_t c4 = k4 < last4 ? k4 : last4;
             *reinterpret_cast<float4*>(M + 4u * c4) = v[it];
-            *reinterpret_cast<float4*>(M + 4u * c4 + n) = v[it];
         }
     } else {
         constexpr uint32_t kIt = kSmallMaxN / kLoopThreads;
@@ -247,11 +240,10 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
             const uint32_t k = threadIdx.x + it * kLoopThreads;
             const uint32_t c = k < n ? k : n - 1u;
             M[c] = v[it];
-            M[c + n] = v[it];
         }
     }
     __syncthreads();
-    for (uint32_t k = threadIdx.x; k < kSmallPad; k += kLoopThreads) M[2u * n + k] = M[k % n];
+    if (threadIdx.x < kSmallPad) M[n + threadIdx.x] = M[threadIdx.x % n];
     __syncthreads();
     // 2. the reduction, one chunk at a time with k_reduce's thread mapping
     for (uint32_t p = 0; p < nparts; ++p) {
@@ -262,16 +254,16 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
         double s = 0.0;
         uint32_t bad = 0;
         if (fold_vec)
-            reduce_range<true>(M, n, start, end, nullptr, mx, s, bad);
+            reduce_range<true>(M, start, end, nullptr, mx, s, bad);
         else
-            reduce_range<false>(M, n, start, end, nullptr, mx, s, bad);
+            reduce_range<false>(M, start, end, nullptr, mx, s, bad);
         block_reduce(mx, s, bad);
         if (threadIdx.x == 0) parts[p] = Partial{s, mx, bad};
         __syncthreads();
     }
     // 3. B and the stats; block 0 returns them. The workspace record is
     //    marked unusable for mgp_resample_prepared (n = 0): this path leaves
-    //    no offsets or mirror there.
+    //    no offsets or windows there.
     const uint32_t B = finalize_one(parts, nparts, a, st_local, blockIdx.x == 0 ? st_user : nullptr, nullptr);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         mgp_stats r = *st_local;
@@ -285,7 +277,7 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
 // The split loop's modes: the B, stats and offsets of a preceding k_finalize
 // (kSplitPrepared); the finalize step inside every block over the partials
 // of a preceding k_reduce (kSplitFinalize); or, for n <= kSmallMaxN, the whole
-// of mgp_resample in one launch with the weights in an LDS mirror
+// of mgp_resample in one launch with the weights in LDS
 // (kSplitSmall, with small_prologue).
 constexpr int kSplitPrepared = 0, kSplitFinalize = 1, kSplitSmall = 2;
 
@@ -307,29 +299,26 @@ constexpr uint32_t kSplitMaxM = 1u << 16;  // beyond, four waves per 64 particle
 // (beyond, its extra registers cost more than the launch it saves)
 constexpr uint32_t kSplitFusedMaxN = 1u << 15;
 
-// Megopolis over the mirrored weights for n up to kSplitMaxM, with each
-// particle's draws spread over four lanes. A block serves 64 particles: in each pass of
+// Megopolis by windows for n up to kSplitMaxM, with each particle's draws
+// spread over four lanes. A block serves 64 particles: in each pass of
 // kSplitPass steps its four waves compute the particles' u draws (one Philox
-// call per five steps), their candidates' mirror positions and candidate
-// weights, all independent of the chain, into LDS; then wave 0 runs the
+// call per five steps), their candidates' positions and weights, all independent of the chain, into LDS; then wave 0 runs the
 // chains, whose serial part is only the product, the compare and two selects
 // per step. Every load of a pass is issued before the first LDS store, and
 // steps past the pass write a spare row, so nothing branches around a load.
-// The arithmetic and the draws are those of megopolis_mirror_chain_deep: the
-// ancestors are identical.
+// The arithmetic and the draws are those of megopolis_chain: the ancestors are
+// identical.
 // In modes kSplitFinalize (mgp_resample, n <= kSplitFusedMaxN) and
 // kSplitSmall every block finds B itself and draws each pass's offsets into
 // LDS (waves 1-3 draw the next pass's while wave 0 runs the chains), so the
-// finalize launch goes; kSplitSmall also reads the candidates from its LDS
-// mirror.
+// finalize launch goes; kSplitSmall also reads the candidates from LDS.
 constexpr uint32_t kSplitPass = 20;  // steps per pass: a multiple of 20 (chain rounds) and of 5 (u blocks)
 constexpr uint32_t kSplitGroups = kLoopThreads / 64u;
 constexpr uint32_t kSplitBlocksPerWave = kSplitPass / (5u * kSplitGroups);
 static_assert(kSplitPass % (5u * kSplitGroups) == 0 && kSplitPass % 20u == 0, "whole u blocks per wave and rounds");
 
 template <int Mode>
-__global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(const float* __restrict__ mirror, uint32_t n,
-                                                                  uint32_t m, const mgp_stats* __restrict__ st,
+__global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa, uint32_t n, uint32_t m, const mgp_stats* __restrict__ st,
                                                                   const uint32_t* __restrict__ offsets,
                                                                   uint32_t key0, uint32_t key1, uint32_t stream_id,
                                                                   uint32_t tag, uint32_t b_cap, uint32_t seg_mask,
@@ -345,11 +334,11 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(const float* _
     const uint32_t i = blockIdx.x * 64u + lane;
     constexpr bool kOwnOffsets = Mode != kSplitPrepared;
     __shared__ uint32_t soffs[2][kOwnOffsets ? kSplitPass : 1];  // this pass's offsets and the next pass's
-    __shared__ __align__(16) float Ms[Mode == kSplitSmall ? 2 * kSmallMaxN + kSmallPad : 1];
+    __shared__ __align__(16) float Ms[Mode == kSplitSmall ? kSmallMaxN + kSmallPad : 1];
     uint32_t B;
     bool ok;
     if constexpr (Mode == kSplitSmall) {
-        // the weights into the LDS mirror, the reduction and B (small_prologue)
+        // the weights into LDS, the reduction and B (small_prologue)
         __shared__ Partial parts[kSmallMaxParts];
         __shared__ mgp_stats st_local;
         B = small_prologue(f.w, n, f.nparts, f.chunk, f.copy_vec, f.fold_vec, f.a, f.st_ws, f.st_user, Ms, parts,
@@ -380,12 +369,21 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(const float* _
         }
         return;
     }
-    // lanes past m run too (the mirror's padding keeps their loads in bounds)
-    const char* M = Mode == kSplitSmall ? reinterpret_cast<const char*>(Ms) : reinterpret_cast<const char*>(mirror);
-    const uint32_t ia4 = (i & ~seg_mask) * 4u;
-    const uint32_t il4 = (i & seg_mask) * 4u;
+    // lanes past m run too (the window keeps their loads in bounds)
+    const uint32_t start = blockIdx.x * 64u;
+    const uint32_t la4 = (lane & ~seg_mask) * 4u;
+    const uint32_t ll4 = (lane & seg_mask) * 4u;
+    Windows W{};
+    if constexpr (Mode != kSplitSmall) W = load_windows(wa, n);
+    // the weight at a window position (byte offset v of the window from position s on)
+    auto candidate = [&](uint32_t s, uint32_t v) -> float {
+        if constexpr (Mode == kSplitSmall)
+            return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ms) + 4u * s + v);
+        else
+            return *(GlobalPtr<const float>)(window_at(W, s, n, 64u) + v);
+    };
     uint32_t kk = i * 4u;
-    float wk = *reinterpret_cast<const float*>(M + i * 4u);
+    float wk = candidate(start, lane * 4u);
     // the offsets of the pass starting at step c0, drawn as k_finalize draws
     // them, by the threads t0, t0 + stride, ... of the block
     auto draw_offsets = [&](uint32_t c0, uint32_t* dst, uint32_t t0, uint32_t stride) {
@@ -417,11 +415,12 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(const float* _
             for (uint32_t r = 0; r < 5u; ++r) {
                 const uint32_t s = g * 5u + r;
                 uint32_t o = kOwnOffsets ? soffs[buf][s < cnt ? s : cnt - 1u] : offsets[b0 + (s < cnt ? s : cnt - 1u)];
+                if constexpr (kOwnOffsets) o = __builtin_amdgcn_readfirstlane(o);
                 o = o < n ? o : n - 1u;
-                const uint32_t oa4 = (o & ~seg_mask) * 4u;
-                const uint32_t voff = ia4 | ((il4 + (o & seg_mask) * 4u) & (seg_mask * 4u));
-                wj[t][r] = *reinterpret_cast<const float*>(M + oa4 + voff);
-                jb[t][r] = voff + oa4;
+                const uint32_t at = window_start(start, o, seg_mask, n);
+                const uint32_t voff = la4 | ((ll4 + (o & seg_mask) * 4u) & (seg_mask * 4u));
+                wj[t][r] = candidate(at, voff);
+                jb[t][r] = voff + 4u * at;
             }
         }
 #pragma unroll
@@ -493,7 +492,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_resample_small(const float* __
                                                                  uint32_t n_part, int32_t* __restrict__ anc,
                                                                  RowCopy rc)
 {
-    __shared__ __align__(16) float M[2 * kSmallMaxN + kSmallPad];
+    __shared__ __align__(16) float M[kSmallMaxN + kSmallPad];
     __shared__ Partial parts[kSmallMaxParts];
     __shared__ mgp_stats st_local;
     const uint32_t B = small_prologue(w, n, nparts, chunk, copy_vec, fold_vec, a, st_ws, st_user, M, parts, &st_local);
@@ -604,35 +603,68 @@ size_t workspace_bytes(uint32_t b_max)
     return kWsOffsetsOffset + (((size_t)b_max * 4u + 255u) & ~(size_t)255u);
 }
 
-bool uses_mirror(uint32_t n, int variant) { return variant == kMegopolis && n <= kMirrorMaxN; }
+bool uses_windows(uint32_t n, int variant) { return variant == kMegopolis && n <= kWindowMaxN; }
 
-size_t mirror_offset(uint32_t b_max) { return workspace_bytes(b_max); }
+size_t windows_offset(uint32_t b_max) { return workspace_bytes(b_max); }
 
 size_t workspace_bytes(uint32_t n, const Params& p)
 {
     size_t b = workspace_bytes(p.b_max);
-    if (uses_mirror(n, p.variant)) b += (((size_t)2 * n + kMirrorPad) * 4u + 255u) & ~(size_t)255u;
+    if (uses_windows(n, p.variant)) b += (((size_t)2 * n + kWindowReserve) * 4u + 255u) & ~(size_t)255u;
     return b;
 }
 
+static bool ranges_overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes)
+{
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    return a && b && a_bytes && b_bytes && a0 < b0 + b_bytes && b0 < a0 + a_bytes;
+}
+
+bool in_place(const float* w, uint32_t n, const OutRange* outs, int count)
+{
+    if (((uintptr_t)w & 127u) != 0) return false;
+    for (int k = 0; k < count; ++k)
+        if (ranges_overlap(w, 4ull * n, outs[k].at, outs[k].bytes)) return false;
+    return true;
+}
+
+// The layout for a call that resamples n weights into m ancestors (and rows).
+static uint32_t loop_layout(const float* w, uint32_t n, uint32_t m, const int32_t* anc, const mgp_stats* st_user,
+                            const RowCopy& rc)
+{
+    const OutRange outs[3] = {{anc, 4ull * m}, {rc.out, 4ull * m * rc.d}, {st_user, sizeof(mgp_stats)}};
+    return in_place(w, n, outs, 3) ? kLayoutInPlace : kLayoutCopy;
+}
+
 // The reduction launch of the three-launch path: partials (and, for
-// Megopolis with make_offsets, the mirror) in the workspace. Returns the
-// number of partials through *nparts.
-static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make_offsets, char* ws, uint32_t* nparts,
-                          hipStream_t stream)
+// Megopolis with make_offsets, the ends of the windows or the copy) in the
+// workspace. Returns the number of partials through *nparts.
+static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
+                          uint32_t* nparts, hipStream_t stream)
 {
     Partial* part = reinterpret_cast<Partial*>(ws + kWsPartialsOffset);
-    float* mirror = (make_offsets && uses_mirror(n, p.variant)) ? reinterpret_cast<float*>(ws + mirror_offset(p.b_max))
-                                                                  : nullptr;
+    const bool windows = make_offsets && uses_windows(n, p.variant);
+    float* aux = windows ? reinterpret_cast<float*>(ws + windows_offset(p.b_max)) : nullptr;
+    float* copy = layout == kLayoutCopy ? aux : nullptr;
+    float* seam = layout == kLayoutInPlace ? aux : nullptr;
+    uint32_t* layout_dev = reinterpret_cast<uint32_t*>(ws + kWsLayoutOffset);
     const uint32_t g = reduce_blocks(n);
     const uint32_t chunk = reduce_chunk(n, g);
-    const bool vec = (((uintptr_t)w & 15u) == 0) && (!mirror || n % 4u == 0);
-    if (vec)
-        hipLaunchKernelGGL(k_reduce<true>, dim3(g), dim3(kReduceThreads), 0, stream, w, n, chunk, part, mirror);
+    const dim3 grid(g + (windows ? 1u : 0u));
+    if (((uintptr_t)w & 15u) == 0)
+        hipLaunchKernelGGL(k_reduce<true>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, copy, seam,
+                           layout_dev);
     else
-        hipLaunchKernelGGL(k_reduce<false>, dim3(g), dim3(kReduceThreads), 0, stream, w, n, chunk, part, mirror);
+        hipLaunchKernelGGL(k_reduce<false>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, copy, seam,
+                           layout_dev);
     *nparts = g;
     return check_launch("reduce kernel");
+}
+
+static WindowArgs window_args(const float* w, const Params& p, char* ws)
+{
+    return WindowArgs{w, reinterpret_cast<const float*>(ws + windows_offset(p.b_max)),
+                      reinterpret_cast<const uint32_t*>(ws + kWsLayoutOffset)};
 }
 
 static FinalizeArgs finalize_args(uint32_t n, const Params& p, bool make_offsets)
@@ -650,14 +682,14 @@ static FinalizeArgs finalize_args(uint32_t n, const Params& p, bool make_offsets
     return a;
 }
 
-int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, char* ws,
+int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
                             mgp_stats* st_user, hipStream_t stream)
 {
     Partial* part = reinterpret_cast<Partial*>(ws + kWsPartialsOffset);
     mgp_stats* st = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
     uint32_t* offs = reinterpret_cast<uint32_t*>(ws + kWsOffsetsOffset);
     uint32_t g = 0;
-    int rc = enqueue_reduce(w, n, p, make_offsets, ws, &g, stream);
+    int rc = enqueue_reduce(w, n, p, make_offsets, layout, ws, &g, stream);
     if (rc) return rc;
     const FinalizeArgs a = finalize_args(n, p, make_offsets);
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kReduceThreads), 0, stream, part, g, a, st, st_user, offs);
@@ -678,14 +710,30 @@ static void launch_loop(bool narrow, dim3 grid, hipStream_t s, const float* w, u
                            n_w, n_part, tag, b_cap, seg_mask, anc, rc);
 }
 
-// The four-particle Megopolis loop with the epilogue that fits the row copy.
-template <int Rows>
-static void launch_mirror(dim3 g, hipStream_t s, const float* mirror, uint32_t n, uint32_t m, const mgp_stats* st,
-                          const uint32_t* offs, uint32_t k0, uint32_t k1, uint32_t sid, uint32_t tag, uint32_t cap,
-                          uint32_t seg_mask, int32_t* anc, const RowCopy& rc)
+// A Megopolis loop with the epilogue that fits the row copy.
+template <int P, int D>
+static void launch_megopolis(hipStream_t s, const WindowArgs& wa, uint32_t n, uint32_t m, const mgp_stats* st,
+                             const uint32_t* offs, uint32_t k0, uint32_t k1, uint32_t sid, uint32_t tag, uint32_t cap,
+                             uint32_t seg_mask, int32_t* anc, const RowCopy& rc)
 {
-    hipLaunchKernelGGL((k_megopolis_mirror<kMegopolisPPT, Rows>), g, dim3(kLoopThreads), 0, s, mirror, n, m, st, offs,
-                       k0, k1, sid, tag, cap, seg_mask, anc, rc);
+    const dim3 g((m + kLoopThreads * P - 1u) / (kLoopThreads * P));
+    const dim3 bt(kLoopThreads);
+    const uint32_t d4 = rc.vec4 ? rc.d / 4u : 0u;
+    if (!rc.states)
+        hipLaunchKernelGGL((k_megopolis<P, D, 0>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
+                           anc, rc);
+    else if (d4 == 1u)
+        hipLaunchKernelGGL((k_megopolis<P, D, 1>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
+                           anc, rc);
+    else if (d4 == 2u)
+        hipLaunchKernelGGL((k_megopolis<P, D, 2>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
+                           anc, rc);
+    else if (d4 == 4u)
+        hipLaunchKernelGGL((k_megopolis<P, D, 4>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
+                           anc, rc);
+    else
+        hipLaunchKernelGGL((k_megopolis<P, D, -1>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
+                           anc, rc);
 }
 
 int enqueue_loop(const float* w, uint32_t n, const Params& p, char* ws, int32_t* anc, hipStream_t stream,
@@ -707,35 +755,20 @@ int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, char
     const uint32_t tag = call_tag(n, p.variant, p.seed, p.stream_id);
     const uint32_t cap = p.b_max;
     const uint32_t seg_mask = p.segment - 1u;
-    if (uses_mirror(n, p.variant) && m <= n && m <= kDeepMaxM) {
-        // few waves: up to 2^16 outputs the draws spread over four lanes, above
-        // that twenty steps' loads per round trip, instead of four particles
-        // per thread
-        const float* mirror = reinterpret_cast<const float*>(ws + mirror_offset(p.b_max));
-        if (m <= kSplitMaxM) {
+    if (uses_windows(n, p.variant) && m <= n) {
+        // few outputs are few waves: up to 2^16 the draws spread over four
+        // lanes, up to 2^18 twenty steps' loads per round trip, and four
+        // particles per thread above
+        const WindowArgs wa = window_args(w, p, ws);
+        if (m <= kSplitMaxM)
             hipLaunchKernelGGL(k_megopolis_split<kSplitPrepared>, dim3((m + 63u) / 64u), dim3(kLoopThreads), 0, stream,
-                               mirror, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, SplitArgs{}, rc);
-        } else {
-            hipLaunchKernelGGL(k_megopolis_mirror_deep, grid, dim3(kLoopThreads), 0, stream, mirror, n, m, st, offs,
-                               k0, k1, p.stream_id, tag, cap, seg_mask, anc, rc);
-        }
-        return check_launch("megopolis kernel (small n)");
-    }
-    if (uses_mirror(n, p.variant) && m <= n) {
-        constexpr int P = kMegopolisPPT;
-        const float* mirror = reinterpret_cast<const float*>(ws + mirror_offset(p.b_max));
-        const dim3 g((m + kLoopThreads * P - 1u) / (kLoopThreads * P));
-        const uint32_t d4 = rc.vec4 ? rc.d / 4u : 0u;
-        if (!rc.states)
-            launch_mirror<0>(g, stream, mirror, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, rc);
-        else if (d4 == 1u)
-            launch_mirror<1>(g, stream, mirror, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, rc);
-        else if (d4 == 2u)
-            launch_mirror<2>(g, stream, mirror, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, rc);
-        else if (d4 == 4u)
-            launch_mirror<4>(g, stream, mirror, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, rc);
+                               wa, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, SplitArgs{}, rc);
+        else if (m <= kDeepMaxM)
+            launch_megopolis<1, kDeepSteps>(stream, wa, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc,
+                                            rc);
         else
-            launch_mirror<-1>(g, stream, mirror, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, rc);
+            launch_megopolis<kMegopolisPPT, 5>(stream, wa, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask,
+                                               anc, rc);
         return check_launch("megopolis kernel");
     }
     switch (p.variant) {
@@ -762,8 +795,8 @@ int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, char
 // mgp_resample with n <= kSmallMaxN (Megopolis) or kSmallMaxNOther: one
 // launch of k_megopolis_split<kSplitSmall> or k_resample_small. The reduction
 // uses the chunks, thread mapping and fold width that enqueue_reduce_finalize
-// uses for the same n, variant and weight alignment (float4 folds need a
-// 16-byte aligned w, and with a mirror n % 4 == 0).
+// uses for the same n and weight alignment (float4 folds need a 16-byte
+// aligned w).
 int enqueue_small(const float* w, uint32_t n, const Params& p, char* ws, mgp_stats* st_user, int32_t* anc,
                   hipStream_t stream, const RowCopy& rc)
 {
@@ -771,7 +804,7 @@ int enqueue_small(const float* w, uint32_t n, const Params& p, char* ws, mgp_sta
     const uint32_t chunk = reduce_chunk(n, g);
     const bool aligned = ((uintptr_t)w & 15u) == 0;
     const uint32_t copy_vec = (aligned && n % 4u == 0) ? 1u : 0u;
-    const uint32_t fold_vec = p.variant == kMegopolis ? copy_vec : (aligned ? 1u : 0u);
+    const uint32_t fold_vec = aligned ? 1u : 0u;
     const FinalizeArgs a = finalize_args(n, p, false);
     mgp_stats* st_ws = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
     const dim3 grid((n + kLoopThreads - 1u) / kLoopThreads);
@@ -787,9 +820,9 @@ int enqueue_small(const float* w, uint32_t n, const Params& p, char* ws, mgp_sta
             f.w = w;
             f.chunk = chunk;
             f.copy_vec = copy_vec;
-            f.fold_vec = copy_vec;
+            f.fold_vec = fold_vec;
             hipLaunchKernelGGL(k_megopolis_split<kSplitSmall>, dim3((n + 63u) / 64u), dim3(kLoopThreads), 0, stream,
-                               nullptr, n, n, nullptr, nullptr, a.key0, a.key1, p.stream_id, a.tag, p.b_max,
+                               WindowArgs{}, n, n, nullptr, nullptr, a.key0, a.key1, p.stream_id, a.tag, p.b_max,
                                p.segment - 1u, anc, f, rc);
             break;
         }
@@ -814,11 +847,12 @@ int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_
 {
     if (n <= (p.variant == kMegopolis ? kSmallMaxN : kSmallMaxNOther))
         return enqueue_small(w, n, p, ws, st_user, anc, stream, rc);
+    const uint32_t layout = loop_layout(w, n, n, anc, st_user, rc);
     if (p.variant == kMegopolis && n <= kSplitFusedMaxN) {
-        // two launches: the reduction (partials and mirror), then the split
+        // two launches: the reduction (partials and windows), then the split
         // accept loop with the finalize step done in every block
         uint32_t g = 0;
-        const int err = enqueue_reduce(w, n, p, true, ws, &g, stream);
+        const int err = enqueue_reduce(w, n, p, true, layout, ws, &g, stream);
         if (err) return err;
         SplitArgs f{};
         f.parts = reinterpret_cast<const Partial*>(ws + kWsPartialsOffset);
@@ -826,13 +860,12 @@ int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_
         f.a = finalize_args(n, p, false);
         f.st_ws = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
         f.st_user = st_user;
-        const float* mirror = reinterpret_cast<const float*>(ws + mirror_offset(p.b_max));
         hipLaunchKernelGGL(k_megopolis_split<kSplitFinalize>, dim3((n + 63u) / 64u), dim3(kLoopThreads), 0, stream,
-                           mirror, n, n, nullptr, nullptr, f.a.key0, f.a.key1, p.stream_id, f.a.tag, p.b_max,
+                           window_args(w, p, ws), n, n, nullptr, nullptr, f.a.key0, f.a.key1, p.stream_id, f.a.tag, p.b_max,
                            p.segment - 1u, anc, f, rc);
         return check_launch("megopolis kernel (finalize and split loop)");
     }
-    int err = enqueue_reduce_finalize(w, n, p, p.variant == kMegopolis, ws, st_user, stream);
+    int err = enqueue_reduce_finalize(w, n, p, p.variant == kMegopolis, layout, ws, st_user, stream);
     if (err) return err;
     return enqueue_loop(w, n, p, ws, anc, stream, rc);
 }
@@ -932,7 +965,8 @@ int mgp_compute_B(const float* w_dev, int32_t n, const mgp_params* params, mgp_s
     if (rc) return rc;
     rc = check_workspace(workspace_dev, workspace_bytes_, (uint32_t)n, p);
     if (rc) return rc;
-    return enqueue_reduce_finalize(w_dev, (uint32_t)n, p, p.variant == kMegopolis,
+    // a copy of the weights: the prepared loop must not see them change
+    return enqueue_reduce_finalize(w_dev, (uint32_t)n, p, p.variant == kMegopolis, kLayoutCopy,
                                    static_cast<char*>(workspace_dev), stats_dev, static_cast<hipStream_t>(stream));
 }
 
@@ -1048,7 +1082,8 @@ int mgp_resample_m(const float* w_dev, int32_t n, int32_t m, const mgp_params* p
     if (rc) return rc;
     char* ws = static_cast<char*>(workspace_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = enqueue_reduce_finalize(w_dev, (uint32_t)n, p, p.variant == kMegopolis, ws, stats_dev, s);
+    const uint32_t layout = loop_layout(w_dev, (uint32_t)n, (uint32_t)m, ancestors_dev, stats_dev, RowCopy{});
+    rc = enqueue_reduce_finalize(w_dev, (uint32_t)n, p, p.variant == kMegopolis, layout, ws, stats_dev, s);
     if (rc) return rc;
     return enqueue_loop_m(w_dev, (uint32_t)n, (uint32_t)m, p, ws, ancestors_dev, s);
 }

@@ -508,7 +508,7 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     char* ws = static_cast<char*>(workspace_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // validation, max and fp64 sum: the reduction and finalize step of the
-    // other resamplers (one explicit iteration, no offsets, no mirror)
+    // other resamplers (one explicit iteration, no offsets, no windows)
     Params p;
     p.variant = kMetropolis;
     p.B = 1;
@@ -517,7 +517,7 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     p.stream_id = stream_id;
     p.partition_bytes = 128;
     p.b_max = 1;
-    const int err = enqueue_reduce_finalize(w_dev, un, p, false, ws, stats_dev, s);
+    const int err = enqueue_reduce_finalize(w_dev, un, p, false, kLayoutInPlace, ws, stats_dev, s);
     if (err) return err;
     J.w = w_dev;
     J.stats = reinterpret_cast<const mgp_stats*>(ws + kWsStatsOffset);

@@ -1,6 +1,5 @@
 // mgp_reduce.h -- device code shared by the single-filter and batched paths:
-// the weight reduction (fp32 max, fp64 sum, validation, optional mirror
-// write) and the finalize step that turns it into B (eq. (proposition)),
+// the weight reduction (fp32 max, fp64 sum, validation, optional copy) and the finalize step that turns it into B (eq. (proposition)),
 // the stats record and the Megopolis offsets.
 #pragma once
 
@@ -52,21 +51,17 @@ __device__ __forceinline__ void block_reduce(float& mx, double& s, uint32_t& bad
     }
 }
 
-// Reduces w[start, end) into (mx, s, bad) per thread and, with a mirror,
-// writes M[i] = M[i + n] = w[i] for the range. With Vec, w + start is
-// 16-byte aligned and (with a mirror) n % 4 == 0.
+// Reduces w[start, end) into (mx, s, bad) per thread and, with a copy, writes
+// copy[i] = w[i] for the range. With Vec, w + start is 16-byte aligned.
 template <bool Vec>
-__device__ __forceinline__ void reduce_range(const float* __restrict__ w, uint32_t n, uint64_t start, uint64_t end,
-                                             float* __restrict__ mirror, float& mx, double& s, uint32_t& bad)
+__device__ __forceinline__ void reduce_range(const float* __restrict__ w, uint64_t start, uint64_t end,
+                                             float* __restrict__ copy, float& mx, double& s, uint32_t& bad)
 {
     if constexpr (Vec) {
         const uint64_t end4 = start + ((end - start) & ~(uint64_t)3);
         for (uint64_t i = start + 4ull * threadIdx.x; i < end4; i += 4ull * blockDim.x) {
             const float4 v = *reinterpret_cast<const float4*>(w + i);
-            if (mirror) {
-                *reinterpret_cast<float4*>(mirror + i) = v;
-                *reinterpret_cast<float4*>(mirror + n + i) = v;
-            }
+            if (copy) *reinterpret_cast<float4*>(copy + i) = v;
             fold(v.x, mx, s, bad);
             fold(v.y, mx, s, bad);
             fold(v.z, mx, s, bad);
@@ -74,28 +69,26 @@ __device__ __forceinline__ void reduce_range(const float* __restrict__ w, uint32
         }
         for (uint64_t i = end4 + threadIdx.x; i < end; i += blockDim.x) {
             const float v = w[i];
-            if (mirror) {
-                mirror[i] = v;
-                mirror[n + i] = v;
-            }
+            if (copy) copy[i] = v;
             fold(v, mx, s, bad);
         }
     } else {
         for (uint64_t i = start + threadIdx.x; i < end; i += blockDim.x) {
             const float v = w[i];
-            if (mirror) {
-                mirror[i] = v;
-                mirror[n + i] = v;
-            }
+            if (copy) copy[i] = v;
             fold(v, mx, s, bad);
         }
     }
 }
 
-// The padding M[2n + k] = w[k mod n], k < kMirrorPad (one block writes it).
-__device__ __forceinline__ void mirror_pad(const float* __restrict__ w, uint32_t n, float* __restrict__ mirror)
+// What a Megopolis loop needs beyond the reduction, by one block: the seam of
+// weights read in place, or the repeated first kSeam weights of a copy.
+__device__ __forceinline__ void write_window_ends(const float* __restrict__ w, uint32_t n, float* __restrict__ copy,
+                                                  float* __restrict__ seam)
 {
-    for (uint32_t k = threadIdx.x; k < kMirrorPad; k += blockDim.x) mirror[2ull * n + k] = w[k % n];
+    if (seam) write_seam(w, n, seam);
+    if (copy)
+        for (uint32_t k = threadIdx.x; k < kSeam; k += blockDim.x) copy[(uint64_t)n + k] = w[k % n];
 }
 
 // ---------------------------------------------------------------------------

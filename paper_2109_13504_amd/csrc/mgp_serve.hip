@@ -99,7 +99,7 @@ struct Req {
     int32_t status = 0;
     uint32_t B = 0;
     uint64_t out_off = 0, out_bytes = 0;  // ancestors + gathered states (kept until release)
-    uint64_t ws_off = 0, ws_bytes = 0;    // mirror + offsets (freed at completion)
+    uint64_t ws_off = 0, ws_bytes = 0;    // windows + offsets (freed at completion)
     bool has_out = false, has_ws = false;
     uint64_t anc_bytes = 0;
     double t_submit = 0, t_admit = 0, t_dispatch = 0, t_done = 0;
@@ -171,13 +171,17 @@ struct mgp_server {
 
 namespace {
 
-uint64_t mirror_bytes(uint32_t n) { return round_up(4ull * (2ull * n + kMirrorPad)); }
+// Megopolis: bytes set aside per request for the loop's windows, the seam or a
+// copy of the weights (admission counts the room of the larger of them and
+// the copy's double, so that a request's footprint does not depend on the
+// address of its weights).
+uint64_t window_bytes(uint32_t n) { return round_up(4ull * (2ull * n + kWindowReserve)); }
 
 void footprint(const mgp_server* s, const mgp_request& r, Req& q)
 {
     q.anc_bytes = round_up(4ull * (uint64_t)r.n);
     q.out_bytes = q.anc_bytes + ((r.states_dev && s->cfg.d > 0) ? round_up(4ull * (uint64_t)r.n * s->cfg.d) : 0);
-    q.ws_bytes = s->variant == kMegopolis ? mirror_bytes((uint32_t)r.n) + round_up(4ull * s->b_max) : 0;
+    q.ws_bytes = s->variant == kMegopolis ? window_bytes((uint32_t)r.n) + round_up(4ull * s->b_max) : 0;
 }
 
 bool try_admit(mgp_server* s, Req& q)
@@ -233,8 +237,10 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
         F.stats_user = nullptr;
         if (s->variant == kMegopolis) {
             char* ws = s->pool_base + q.ws_off;
-            F.mirror = reinterpret_cast<float*>(ws);
-            F.offsets = reinterpret_cast<uint32_t*>(ws + mirror_bytes(n));
+            F.n = n;
+            // outputs lie in the server's pool, which never overlaps the weights of a request it has not finished
+            F.set_windows(in_place(F.w, n, nullptr, 0), reinterpret_cast<float*>(ws));
+            F.offsets = reinterpret_cast<uint32_t*>(ws + window_bytes(n));
         }
         F.eps = q.in.epsilon;
         F.n = n;
@@ -248,7 +254,7 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
         F.part_base = nrt;
         F.n_w = s->n_w;
         F.n_part = (uint32_t)(((uint64_t)n + s->n_w - 1u) / s->n_w);
-        F.vec = (((uintptr_t)q.in.w_dev & 15u) == 0 && (s->variant != kMegopolis || n % 4u == 0)) ? 1u : 0u;
+        F.vec = ((uintptr_t)q.in.w_dev & 15u) == 0 ? 1u : 0u;
         F.rows4 = (s->cfg.d % 4 == 0 && ((uintptr_t)q.in.states_dev & 15u) == 0) ? 1u : 0u;
         for (uint32_t c = 0; c < F.nparts; ++c) sl.h_rt[nrt + c] = RTile{f, c};
         nrt += F.nparts;
@@ -539,7 +545,7 @@ int mgp_server_create(const mgp_server_config* cfg, mgp_server** out)
     s->n_w = pb / 4u;
     s->max_particles = cfg->max_batch_particles > 0 ? cfg->max_batch_particles : (int64_t)1 << 24;
     s->max_n = cfg->max_n > 0 ? (uint32_t)cfg->max_n : (1u << 22);
-    if (s->max_n > kMirrorMaxN || s->b_max > kBMaxLimit) {
+    if (s->max_n > kWindowMaxN || s->b_max > kBMaxLimit) {
         delete s;
         return fail(MGP_ERANGE, "max_n or b_max too large");
     }

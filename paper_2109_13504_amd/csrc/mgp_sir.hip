@@ -13,7 +13,7 @@
 //                                  run; fp64 arithmetic, x and w stored as
 //                                  fp32; it also writes the resampler's
 //                                  per-block partials and the Megopolis
-//                                  mirror (the reduction the batched
+//                                  seam (the reduction the batched
 //                                  resampler would otherwise run);
 //   stage 2  the batched resampler from its finalize step on (B, offsets,
 //            validation), then the accept loop with the fused gather
@@ -75,8 +75,8 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& even,
 // per particle. The kernel is bound by fp64 VALU issue, so it also does the
 // resampler's per-weight work while the weights are in registers: the
 // block's partial (fp32 max, fp64 sum, validity) for the finalize step, and
-// for Megopolis the mirror M[i] = M[i + n] = w_i (plus M[2n + k] = w_{k mod n}
-// for k < kMirrorPad). With mean_part it also writes the block's sum of its
+// for Megopolis the seam of the weights (the last and the first kSeam of
+// them). With mean_part it also writes the block's sum of its
 // input particles, the previous step's x_bar, in the order of k_sir_mean_block,
 // so that a graph of steps needs no separate pass for stage 3.
 __global__ __launch_bounds__(kSirThreads) void k_sir_predict_update(float* __restrict__ xbar, float* x,
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_predict_update(float* __res
 {
     const uint32_t r = blockIdx.y;
     const uint32_t m = blockIdx.x * kSirThreads + threadIdx.x;
-    float* mirror = fd[r].mirror;
+    float* seam = fd[r].seam;
     const uint32_t part_base = fd[r].part_base;
     // the resample of this step runs under key seed + t * 2^32
     if (blockIdx.x == 0 && threadIdx.x == 0) fd[r].key1 = key1 + t;
@@ -144,33 +144,20 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_predict_update(float* __res
             *reinterpret_cast<float4*>(x + at) = make_float4(xo[0], xo[1], xo[2], xo[3]);
             const float4 w4 = make_float4(wo[0], wo[1], wo[2], wo[3]);
             *reinterpret_cast<float4*>(w + at) = w4;
-            if (mirror && (n & 3u) == 0) {
-                *reinterpret_cast<float4*>(mirror + i0) = w4;
-                *reinterpret_cast<float4*>(mirror + n + i0) = w4;
-            } else if (mirror) {
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    mirror[i0 + k] = wo[k];
-                    mirror[n + i0 + k] = wo[k];
-                }
-            }
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k) fold(wo[k], mx, s, bad);
         } else {
             for (uint32_t k = 0; k < 4 && i0 + k < n; ++k) {
                 x[at + k] = xo[k];
                 w[at + k] = wo[k];
-                if (mirror) {
-                    mirror[i0 + k] = wo[k];
-                    mirror[n + i0 + k] = wo[k];
-                }
                 fold(wo[k], mx, s, bad);
             }
         }
-        if (mirror && i0 < kMirrorPad) {
-            // the padding after the two copies: M[2n + k] = w_{k mod n}
+        if (seam && (i0 < kSeam || i0 + 3u + kSeam >= n)) {
+            // seam[c] = w_{(n - kSeam + c) mod n}: the places of w_i are the
+            // c < 2 kSeam that are i + kSeam modulo n
             for (uint32_t k = 0; k < 4 && i0 + k < n; ++k)
-                for (uint32_t c = i0 + k; c < kMirrorPad; c += n) mirror[2ull * n + c] = wo[k];
+                for (uint32_t c = (i0 + k + kSeam) % n; c < 2u * kSeam; c += n) seam[c] = wo[k];
         }
     }
     block_reduce(mx, s, bad);
@@ -384,7 +371,7 @@ int enqueue_resample(mgp_sir_filter* f, uint32_t t, hipStream_t s)
         J.key1 = f->key1 + t;
         return enqueue_prefix(J, f->R, f->prefix_method, s);
     }
-    // stage 1 wrote the partials and the mirror: finalize and accept loop only
+    // stage 1 wrote the partials and the seam: finalize and accept loop only
     return enqueue_batch(f->cfg.variant, f->shape, f->d_fd, f->R, nullptr, 0u, f->d_parts, f->d_stats, f->d_lt,
                          f->grid, f->d_qoff, f->d_qcount, (uint32_t)f->nxcd, 1u, s);
 }
@@ -524,10 +511,10 @@ int mgp_sir_create(const mgp_sir_config* cfg, void* stream, mgp_sir_filter** out
     const size_t o_stats = take((size_t)f->R * sizeof(mgp_stats));
     const size_t o_q = take(sizeof(uint32_t) * 2 * (kMaxXcd + 1));
     const size_t o_lt = take(table.size() * sizeof(LTile));
-    const size_t mirror_row = align256(sizeof(float) * (2 * (size_t)f->n + kMirrorPad));
+    const size_t seam_row = align256(sizeof(float) * window_floats(true, f->n));
     const size_t offs_row = align256(sizeof(uint32_t) * (size_t)offs_cap);
     const size_t o_offs = mego ? take((size_t)f->R * offs_row) : 0;
-    const size_t o_mirror = mego ? take((size_t)f->R * mirror_row) : 0;
+    const size_t o_seam = mego ? take((size_t)f->R * seam_row) : 0;
     const size_t prefix_row = prefix ? align256(prefix_region(f->n, &f->job)) : 0;
     const size_t o_prefix = prefix ? take((size_t)f->R * prefix_row) : 0;
     f->dmem_bytes = off;
@@ -578,10 +565,10 @@ int mgp_sir_create(const mgp_sir_config* cfg, void* stream, mgp_sir_filter** out
         F.states = f->x + (size_t)r * f->ld;
         F.out = f->xbar + (size_t)r * f->ld;
         F.stats_user = nullptr;
-        F.mirror = mego ? reinterpret_cast<float*>(f->dmem + o_mirror + (size_t)r * mirror_row) : nullptr;
         F.offsets = mego ? reinterpret_cast<uint32_t*>(f->dmem + o_offs + (size_t)r * offs_row) : nullptr;
         F.eps = cfg->epsilon;
         F.n = f->n;
+        if (mego) F.set_windows(true, reinterpret_cast<float*>(f->dmem + o_seam + (size_t)r * seam_row));  // rows are 256-byte aligned
         F.B_user = B_fixed;
         F.b_max = f->cfg.b_max;
         F.key0 = f->key0;
@@ -592,7 +579,7 @@ int mgp_sir_create(const mgp_sir_config* cfg, void* stream, mgp_sir_filter** out
         F.chunk = 4u * kSirThreads;
         F.n_w = n_w;
         F.n_part = (uint32_t)(((uint64_t)f->n + n_w - 1u) / n_w);
-        F.vec = (!mego || f->n % 4u == 0) ? 1u : 0u;  // rows are 256-byte aligned
+        F.vec = 1u;  // rows are 256-byte aligned
         F.rows4 = 0;
     }
     if (hipMemcpyAsync(f->d_fd, fd.data(), fd.size() * sizeof(FilterDev), hipMemcpyHostToDevice, s) != hipSuccess ||
