@@ -21,13 +21,15 @@ constexpr uint32_t kDefaultBMax = 65536;
 constexpr uint32_t kBMaxLimit = 1u << 24;
 
 // Workspace layout of a single-filter call (byte offsets, 256-aligned):
-//   [stats: mgp_stats][layout: u32][partials: kMaxPartials x Partial]
+//   [stats: mgp_stats][layout: u32, log(eps): f64]
+//   [partials: kMaxPartials x Partial]
 //   [offsets: b_max x u32]
 //   [windows: (2n + 2048) x f32 reserved, Megopolis with n <= kWindowMaxN
 //    only: the seam (2 kSeam weights) or the copy (n + kSeam), as `layout`
 //    (kLayoutInPlace or kLayoutCopy) says]
 constexpr size_t kWsStatsOffset = 0;
 constexpr size_t kWsLayoutOffset = 128;
+constexpr size_t kWsLogEpsOffset = 136;
 constexpr size_t kWsPartialsOffset = 256;
 constexpr uint32_t kWindowReserve = 2048;  // of the reserved 2n + 2048: >= 2 kSeam, and >= kSeam - n
 static_assert(kWindowReserve >= 2 * kSeam, "the seam must fit the reserved region");
@@ -44,6 +46,7 @@ constexpr size_t kWsOffsetsOffset = kWsPartialsOffset + (size_t)kMaxPartials * s
 
 struct FinalizeArgs {
     double eps;
+    const double* log_eps = nullptr;  // log(eps) if an earlier launch of the call computed it, else null
     uint32_t n;
     uint32_t B_user;
     uint32_t b_max;
@@ -105,9 +108,9 @@ int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, char
 int enqueue_gather(const float* states, uint32_t n_states, uint32_t d, const int32_t* anc, uint32_t n_out,
                    float* out, hipStream_t stream);
 // mgp_resample's work: one launch up to 8192 (Megopolis) or 4096 particles,
-// two up to 32768 (Megopolis: the finalize step inside the accept loop),
-// leaving nothing in the workspace for a prepared loop; else the reduction +
-// finalize and the accept loop.
+// leaving nothing in the workspace for a prepared loop; two (the reduction,
+// then the accept loop with the finalize step in every block) while that is
+// faster; else the reduction + finalize and the accept loop.
 int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_stats* st_user, int32_t* anc,
                      hipStream_t stream, const RowCopy& rc = RowCopy{});
 

@@ -46,20 +46,45 @@ int check_launch(const char* what)
 //    The block decomposition depends on n only, so the fp64 sum (and B) is
 //    the same on every call.
 // ---------------------------------------------------------------------------
+// What the reduction launch does beside the reduction, in blocks of their own
+// after its nparts blocks, so that they run beside those:
+//   - ends != 0: the ends of a Megopolis loop's windows (block nparts), with the
+//     layout that the loop finds there;
+//   - early_offsets > 0: offsets o_0 .. o_{early_offsets - 1} and log(eps), for
+//     a loop that does the finalize step itself. The offsets do not depend on
+//     the weights, B only says how many are used.
+struct ReduceExtra {
+    float* copy;
+    float* seam;
+    uint32_t* layout;
+    uint32_t ends;
+    uint32_t early_offsets;
+    uint32_t* offsets;
+    double* log_eps;
+    FinalizeArgs a;
+};
+
+constexpr uint32_t kOffsetsPerBlock = 4096;  // early offsets: four calls per thread
+
 // Block b < nparts reduces w[b*chunk, min(n, (b+1)*chunk)); chunk is a
 // multiple of 4 and, with Vec, w is 16-byte aligned so float4 loads stay
-// aligned. For a Megopolis loop (layout != null) one more block writes the
-// ends of the loop's windows, beside the others rather than after one of them,
-// and the layout that the loop finds there.
+// aligned.
 template <bool Vec>
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restrict__ w, uint32_t n,
                                                            uint32_t chunk, uint32_t nparts, Partial* __restrict__ part,
-                                                           float* __restrict__ copy, float* __restrict__ seam,
-                                                           uint32_t* __restrict__ layout)
+                                                           ReduceExtra x)
 {
-    if (blockIdx.x == nparts) {
-        write_window_ends(w, n, copy, seam);
-        if (threadIdx.x == 0) *layout = seam ? kLayoutInPlace : kLayoutCopy;
+    if (blockIdx.x >= nparts) {
+        const uint32_t e = blockIdx.x - nparts;
+        if (x.ends && e == 0) {
+            write_window_ends(w, n, x.copy, x.seam);
+            if (threadIdx.x == 0) *x.layout = x.seam ? kLayoutInPlace : kLayoutCopy;
+        } else {
+            const uint32_t first = (e - x.ends) * kOffsetsPerBlock;
+            const uint32_t end = first + kOffsetsPerBlock < x.early_offsets ? first + kOffsetsPerBlock : x.early_offsets;
+            if (first < end) draw_offsets(x.a, first, end, threadIdx.x, kReduceThreads, x.offsets);
+            if (e == x.ends && threadIdx.x == 0) *x.log_eps = log(x.a.eps);
+        }
         return;
     }
     // trailing blocks may start at or past n when chunk was rounded up: their
@@ -70,7 +95,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restri
     float mx = 0.0f;
     double s = 0.0;
     uint32_t bad = 0;
-    reduce_range<Vec>(w, start, end, copy, mx, s, bad);
+    reduce_range<Vec>(w, start, end, x.copy, mx, s, bad);
     block_reduce(mx, s, bad);
     if (threadIdx.x == 0) part[blockIdx.x] = Partial{s, mx, bad};
 }
@@ -87,23 +112,57 @@ __global__ __launch_bounds__(kReduceThreads) void k_finalize(const Partial* __re
 }
 
 // ---------------------------------------------------------------------------
-// 3. The accept loop, one particle per thread.
+// 3. The accept loop. B and the validity of the weights come from the stats
+//    that k_finalize wrote, or (Fin) every block does the finalize step over
+//    the reduction's partials: the same sums in the same order, so the same B
+//    and stats, which block 0 returns. That saves a launch of 3-5 us and its
+//    gap for about 2 us at the start of each block.
 // ---------------------------------------------------------------------------
-template <int V, bool Narrow>
+struct LoopStart {
+    const mgp_stats* st;   // !Fin: k_finalize's record
+    uint32_t tag, b_cap;   // !Fin: what that record must say
+    const Partial* parts;  // Fin
+    uint32_t nparts;
+    FinalizeArgs a;
+    mgp_stats* st_ws;      // Fin: the workspace's record
+    uint32_t prepares;     // Fin: that record may serve a prepared loop (as k_finalize leaves it), else it is refused
+    mgp_stats* st_user;    // Fin: the caller's stats or null
+};
+
+// B, or 0 when every ancestor is -1: invalid weights, or (!Fin) a record that
+// is not this very call's (n, variant, seed, stream) or a B beyond the
+// workspace's offsets.
+template <bool Fin>
+__device__ __forceinline__ uint32_t loop_start(const LoopStart& l, uint32_t n)
+{
+    if constexpr (Fin) {
+        __shared__ mgp_stats st_local;
+        const uint32_t B = finalize_one(l.parts, l.nparts, l.a, &st_local, blockIdx.x == 0 ? l.st_user : nullptr,
+                                        nullptr);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            mgp_stats r = st_local;
+            if (!l.prepares) r.n = r.tag = 0u;
+            *l.st_ws = r;
+        }
+        return B;
+    } else {
+        const uint32_t B = l.st->B;
+        return l.st->status == MGP_OK && l.st->tag == l.tag && l.st->n == n && B <= l.b_cap ? B : 0u;
+    }
+}
+
+// One particle per thread, any variant.
+template <int V, bool Narrow, bool Fin>
 __global__ __launch_bounds__(kLoopThreads) void k_resample(const float* __restrict__ w, uint32_t n, uint32_t m,
-                                                           const mgp_stats* __restrict__ st,
-                                                           const uint32_t* __restrict__ offsets, uint32_t key0,
-                                                           uint32_t key1, uint32_t stream_id, uint32_t n_w,
-                                                           uint32_t n_part, uint32_t tag, uint32_t b_cap,
-                                                           uint32_t seg_mask, int32_t* __restrict__ anc, RowCopy rc)
+                                                           LoopStart ls, const uint32_t* __restrict__ offsets,
+                                                           uint32_t key0, uint32_t key1, uint32_t stream_id,
+                                                           uint32_t n_w, uint32_t n_part, uint32_t seg_mask,
+                                                           int32_t* __restrict__ anc, RowCopy rc)
 {
     const uint32_t i = blockIdx.x * kLoopThreads + threadIdx.x;
-    const uint32_t B = st->B;
-    // the stats must come from the reduction of this very call (same n,
-    // variant, seed and stream), and B must fit the workspace
-    const bool ok = st->status == MGP_OK && st->tag == tag && st->n == n && B <= b_cap;
+    const uint32_t B = loop_start<Fin>(ls, n);
     int32_t k = -1;
-    if (ok) {
+    if (B > 0) {
         // every lane runs a chain, also past m (C2 shares each group's
         // partition draws across its half-wave): output i starts at input
         // i mod n, i itself when i < n
@@ -132,17 +191,14 @@ __device__ __forceinline__ Windows load_windows(const WindowArgs& a, uint32_t n)
 // Megopolis by windows, P particles per thread, rounds of D steps. Rows
 // selects the particle copy of the epilogue: 0 none, D4 > 0 rows of D4
 // float4s, -1 any row shape (copy_row).
-template <int P, int D, int Rows>
-__global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint32_t n, uint32_t m,
-                                                            const mgp_stats* __restrict__ st,
+template <int P, int D, int Rows, bool Fin>
+__global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint32_t n, uint32_t m, LoopStart ls,
                                                             const uint32_t* __restrict__ offsets, uint32_t key0,
-                                                            uint32_t key1, uint32_t stream_id, uint32_t tag,
-                                                            uint32_t b_cap, uint32_t seg_mask,
+                                                            uint32_t key1, uint32_t stream_id, uint32_t seg_mask,
                                                             int32_t* __restrict__ anc, RowCopy rc)
 {
     const uint32_t start = blockIdx.x * (kLoopThreads * P);
-    const uint32_t B = st->B;
-    const bool ok = st->status == MGP_OK && st->tag == tag && st->n == n && B <= b_cap;
+    const uint32_t B = loop_start<Fin>(ls, n);
     uint32_t idx[P];
     int32_t k[P];
     bool live[P];
@@ -152,7 +208,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint3
         live[p] = idx[p] < m;
         k[p] = -1;
     }
-    if (ok) {
+    if (B > 0) {
         // every lane runs, also past m (start < m <= n here): the window
         // keeps those loads in bounds, and only real outputs store
         uint32_t kc[P];
@@ -175,11 +231,17 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint3
     }
 }
 
-// For few outputs one particle per thread and rounds of kDeepSteps steps: up
-// to kDeepMaxM the four-particle kernel leaves too few waves in flight to hide
-// its round trips to memory.
-constexpr int kDeepSteps = 20;
-constexpr uint32_t kDeepMaxM = 1u << 18;
+// Few outputs are few waves, which hide fewer round trips to memory: fewer
+// particles per thread and longer rounds then. Whole calls, us, at B = 4 / 16 /
+// 354 by particles per thread and steps per round:
+//            1, 20              2, 10              4, 5
+//   2^17     8.1 /  9.9 / 45.6  7.8 /  9.5 / 51.0  -
+//   2^18     9.2 / 12.1 / 73.4  8.4 / 10.7 / 64.3  8.4 / 10.9 / 76.4 (4, 10)
+//   2^19    12.3 / 17.3 /  128  9.6 / 13.6 /  101  9.2 / 13.1 /  104
+//   2^20    18.2 / 27.8 /  235 12.4 / 20.1 /  174 11.2 / 18.0 /  165
+// Up to 2^16 k_megopolis_split is the fastest (below).
+constexpr uint32_t kOneMaxM = 1u << 17;  // one particle per thread
+constexpr uint32_t kTwoMaxM = 1u << 18;  // two
 
 // mgp_resample of a small filter in one launch (Megopolis up to kSmallMaxN
 // particles, the other variants up to kSmallMaxNOther): every block copies
@@ -274,55 +336,43 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
     return B;
 }
 
-// The split loop's modes: the B, stats and offsets of a preceding k_finalize
-// (kSplitPrepared); the finalize step inside every block over the partials
-// of a preceding k_reduce (kSplitFinalize); or, for n <= kSmallMaxN, the whole
-// of mgp_resample in one launch with the weights in LDS
+// The split loop's modes: B from k_finalize's record (kSplitPrepared), by the
+// finalize step inside every block (kSplitFinalize), or, for n <= kSmallMaxN,
+// the whole of mgp_resample in one launch with the weights in LDS
 // (kSplitSmall, with small_prologue).
 constexpr int kSplitPrepared = 0, kSplitFinalize = 1, kSplitSmall = 2;
 
-// What the split loop needs beyond the prepared workspace.
-struct SplitArgs {
-    const Partial* parts;  // kSplitFinalize: the reduction's partials
-    uint32_t nparts;       // kSplitFinalize, kSplitSmall
-    FinalizeArgs a;        // kSplitFinalize, kSplitSmall
-    mgp_stats* st_ws;      // kSplitFinalize, kSplitSmall: the workspace record, marked unusable
-    mgp_stats* st_user;    // kSplitFinalize, kSplitSmall: the caller's stats or null
-    const float* w;        // kSplitSmall: the weights
-    uint32_t chunk;        // kSplitSmall: weights per reduction chunk
-    uint32_t copy_vec;     // kSplitSmall: float4 copies into LDS
-    uint32_t fold_vec;     // kSplitSmall: float4 folds in the reduction
+// What kSplitSmall needs beside its LoopStart.
+struct SmallArgs {
+    const float* w;
+    uint32_t chunk;     // weights per reduction chunk
+    uint32_t copy_vec;  // float4 copies into LDS
+    uint32_t fold_vec;  // float4 folds in the reduction
 };
 
 constexpr uint32_t kSplitMaxM = 1u << 16;  // beyond, four waves per 64 particles cost more than they hide
-// mgp_resample up to this size does the finalize step inside the split loop
-// (beyond, its extra registers cost more than the launch it saves)
-constexpr uint32_t kSplitFusedMaxN = 1u << 15;
-
 // Megopolis by windows for n up to kSplitMaxM, with each particle's draws
 // spread over four lanes. A block serves 64 particles: in each pass of
 // kSplitPass steps its four waves compute the particles' u draws (one Philox
-// call per five steps), their candidates' positions and weights, all independent of the chain, into LDS; then wave 0 runs the
-// chains, whose serial part is only the product, the compare and two selects
-// per step. Every load of a pass is issued before the first LDS store, and
+// call per five steps), their candidates' positions and weights, all
+// independent of the chain, into LDS; then wave 0 runs the chains, whose
+// serial part is only the product, the compare and two selects per step. Every load of a pass is issued before the first LDS store, and
 // steps past the pass write a spare row, so nothing branches around a load.
 // The arithmetic and the draws are those of megopolis_chain: the ancestors are
 // identical.
-// In modes kSplitFinalize (mgp_resample, n <= kSplitFusedMaxN) and
-// kSplitSmall every block finds B itself and draws each pass's offsets into
-// LDS (waves 1-3 draw the next pass's while wave 0 runs the chains), so the
-// finalize launch goes; kSplitSmall also reads the candidates from LDS.
+// kSplitSmall reads the candidates from LDS and draws each pass's offsets into
+// LDS too (waves 1-3 draw the next pass's while wave 0 runs the chains).
 constexpr uint32_t kSplitPass = 20;  // steps per pass: a multiple of 20 (chain rounds) and of 5 (u blocks)
 constexpr uint32_t kSplitGroups = kLoopThreads / 64u;
 constexpr uint32_t kSplitBlocksPerWave = kSplitPass / (5u * kSplitGroups);
 static_assert(kSplitPass % (5u * kSplitGroups) == 0 && kSplitPass % 20u == 0, "whole u blocks per wave and rounds");
 
 template <int Mode>
-__global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa, uint32_t n, uint32_t m, const mgp_stats* __restrict__ st,
+__global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa, uint32_t n, uint32_t m, LoopStart ls,
                                                                   const uint32_t* __restrict__ offsets,
                                                                   uint32_t key0, uint32_t key1, uint32_t stream_id,
-                                                                  uint32_t tag, uint32_t b_cap, uint32_t seg_mask,
-                                                                  int32_t* __restrict__ anc, SplitArgs f, RowCopy rc)
+                                                                  uint32_t seg_mask, int32_t* __restrict__ anc,
+                                                                  SmallArgs f, RowCopy rc)
 {
     __shared__ float su[kSplitPass + 1][64];   // row kSplitPass: the spare row
     __shared__ float swj[kSplitPass + 1][64];
@@ -332,37 +382,20 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
     // are scalar loads
     const uint32_t q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t i = blockIdx.x * 64u + lane;
-    constexpr bool kOwnOffsets = Mode != kSplitPrepared;
+    constexpr bool kOwnOffsets = Mode == kSplitSmall;
     __shared__ uint32_t soffs[2][kOwnOffsets ? kSplitPass : 1];  // this pass's offsets and the next pass's
     __shared__ __align__(16) float Ms[Mode == kSplitSmall ? kSmallMaxN + kSmallPad : 1];
     uint32_t B;
-    bool ok;
     if constexpr (Mode == kSplitSmall) {
         // the weights into LDS, the reduction and B (small_prologue)
         __shared__ Partial parts[kSmallMaxParts];
         __shared__ mgp_stats st_local;
-        B = small_prologue(f.w, n, f.nparts, f.chunk, f.copy_vec, f.fold_vec, f.a, f.st_ws, f.st_user, Ms, parts,
+        B = small_prologue(f.w, n, ls.nparts, f.chunk, f.copy_vec, f.fold_vec, ls.a, ls.st_ws, ls.st_user, Ms, parts,
                            &st_local);
-        ok = B > 0;
-    } else if constexpr (Mode == kSplitFinalize) {
-        // the finalize step in every block, over the partials k_reduce wrote:
-        // B and the stats exactly as k_finalize computes them (block 0
-        // returns the stats; the workspace record is marked unusable for a
-        // prepared loop, which would find no offsets there)
-        __shared__ mgp_stats st_local;
-        B = finalize_one(f.parts, f.nparts, f.a, &st_local, blockIdx.x == 0 ? f.st_user : nullptr, nullptr);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            mgp_stats r = st_local;
-            r.n = 0;
-            r.tag = 0;
-            *f.st_ws = r;
-        }
-        ok = B > 0;
     } else {
-        B = st->B;
-        ok = st->status == MGP_OK && st->tag == tag && st->n == n && B <= b_cap;
+        B = loop_start<Mode == kSplitFinalize>(ls, n);
     }
-    if (!ok) {
+    if (B == 0) {
         if (q == 0 && i < m) {
             if (anc) anc[i] = -1;
             if (rc.states) copy_row(rc, i, -1);
@@ -384,9 +417,9 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
     };
     uint32_t kk = i * 4u;
     float wk = candidate(start, lane * 4u);
-    // the offsets of the pass starting at step c0, drawn as k_finalize draws
+    // the offsets of the pass starting at step c0, drawn as draw_offsets draws
     // them, by the threads t0, t0 + stride, ... of the block
-    auto draw_offsets = [&](uint32_t c0, uint32_t* dst, uint32_t t0, uint32_t stride) {
+    auto draw_pass = [&](uint32_t c0, uint32_t* dst, uint32_t t0, uint32_t stride) {
         const uint32_t cnt = B - c0 < kSplitPass ? B - c0 : kSplitPass;
         for (uint32_t c = t0; c < (cnt + 3u) / 4u; c += stride) {
             const Words x = philox(c0 / 4u + c, kTagOffset, stream_id, 0u, key0, key1);
@@ -397,7 +430,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
         }
     };
     if constexpr (kOwnOffsets) {
-        draw_offsets(0u, soffs[0], threadIdx.x, kLoopThreads);
+        draw_pass(0u, soffs[0], threadIdx.x, kLoopThreads);
         __syncthreads();
     }
     for (uint32_t b0 = 0, buf = 0; b0 < B; b0 += kSplitPass, buf ^= 1u) {
@@ -467,7 +500,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
         } else if constexpr (kOwnOffsets) {
             // while wave 0 runs the chains, the other waves draw the next
             // pass's offsets into the other buffer
-            if (b0 + kSplitPass < B) draw_offsets(b0 + kSplitPass, soffs[buf ^ 1u], threadIdx.x - 64u, kLoopThreads - 64u);
+            if (b0 + kSplitPass < B) draw_pass(b0 + kSplitPass, soffs[buf ^ 1u], threadIdx.x - 64u, kLoopThreads - 64u);
         }
         __syncthreads();  // the next pass overwrites the buffers
     }
@@ -636,42 +669,12 @@ static uint32_t loop_layout(const float* w, uint32_t n, uint32_t m, const int32_
     return in_place(w, n, outs, 3) ? kLayoutInPlace : kLayoutCopy;
 }
 
-// The reduction launch of the three-launch path: partials (and, for
-// Megopolis with make_offsets, the ends of the windows or the copy) in the
-// workspace. Returns the number of partials through *nparts.
-static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
-                          uint32_t* nparts, hipStream_t stream)
-{
-    Partial* part = reinterpret_cast<Partial*>(ws + kWsPartialsOffset);
-    const bool windows = make_offsets && uses_windows(n, p.variant);
-    float* aux = windows ? reinterpret_cast<float*>(ws + windows_offset(p.b_max)) : nullptr;
-    float* copy = layout == kLayoutCopy ? aux : nullptr;
-    float* seam = layout == kLayoutInPlace ? aux : nullptr;
-    uint32_t* layout_dev = reinterpret_cast<uint32_t*>(ws + kWsLayoutOffset);
-    const uint32_t g = reduce_blocks(n);
-    const uint32_t chunk = reduce_chunk(n, g);
-    const dim3 grid(g + (windows ? 1u : 0u));
-    if (((uintptr_t)w & 15u) == 0)
-        hipLaunchKernelGGL(k_reduce<true>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, copy, seam,
-                           layout_dev);
-    else
-        hipLaunchKernelGGL(k_reduce<false>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, copy, seam,
-                           layout_dev);
-    *nparts = g;
-    return check_launch("reduce kernel");
-}
-
-static WindowArgs window_args(const float* w, const Params& p, char* ws)
-{
-    return WindowArgs{w, reinterpret_cast<const float*>(ws + windows_offset(p.b_max)),
-                      reinterpret_cast<const uint32_t*>(ws + kWsLayoutOffset)};
-}
-
 static FinalizeArgs finalize_args(uint32_t n, const Params& p, bool make_offsets)
 {
     FinalizeArgs a;
     a.n = n;
     a.eps = p.eps;
+    a.log_eps = nullptr;
     a.B_user = p.B;
     a.b_max = p.b_max;
     a.make_offsets = make_offsets ? 1u : 0u;
@@ -682,6 +685,48 @@ static FinalizeArgs finalize_args(uint32_t n, const Params& p, bool make_offsets
     return a;
 }
 
+// The reduction launch: partials and, for Megopolis with make_offsets, the
+// ends of the windows or the copy; with early > 0 also that many offsets, and
+// log(eps). Returns the number of partials through *nparts.
+static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout,
+                          bool early, char* ws, uint32_t* nparts, hipStream_t stream)
+{
+    Partial* part = reinterpret_cast<Partial*>(ws + kWsPartialsOffset);
+    const uint32_t g = reduce_blocks(n);
+    const uint32_t chunk = reduce_chunk(n, g);
+    ReduceExtra x{};
+    uint32_t extra = 0;
+    if (make_offsets && uses_windows(n, p.variant)) {
+        float* aux = reinterpret_cast<float*>(ws + windows_offset(p.b_max));
+        x.copy = layout == kLayoutCopy ? aux : nullptr;
+        x.seam = layout == kLayoutInPlace ? aux : nullptr;
+        x.layout = reinterpret_cast<uint32_t*>(ws + kWsLayoutOffset);
+        x.ends = 1u;
+        extra = 1u;
+    }
+    if (early) {
+        x.early_offsets = make_offsets ? (p.B ? p.B : p.b_max) : 0u;
+        x.offsets = reinterpret_cast<uint32_t*>(ws + kWsOffsetsOffset);
+        x.log_eps = reinterpret_cast<double*>(ws + kWsLogEpsOffset);
+        x.a = finalize_args(n, p, false);
+        const uint32_t blocks = (x.early_offsets + kOffsetsPerBlock - 1u) / kOffsetsPerBlock;
+        extra += blocks ? blocks : 1u;
+    }
+    const dim3 grid(g + extra);
+    if (((uintptr_t)w & 15u) == 0)
+        hipLaunchKernelGGL(k_reduce<true>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, x);
+    else
+        hipLaunchKernelGGL(k_reduce<false>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, x);
+    *nparts = g;
+    return check_launch("reduce kernel");
+}
+
+static WindowArgs window_args(const float* w, const Params& p, char* ws)
+{
+    return WindowArgs{w, reinterpret_cast<const float*>(ws + windows_offset(p.b_max)),
+                      reinterpret_cast<const uint32_t*>(ws + kWsLayoutOffset)};
+}
+
 int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
                             mgp_stats* st_user, hipStream_t stream)
 {
@@ -689,52 +734,93 @@ int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool ma
     mgp_stats* st = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
     uint32_t* offs = reinterpret_cast<uint32_t*>(ws + kWsOffsetsOffset);
     uint32_t g = 0;
-    int rc = enqueue_reduce(w, n, p, make_offsets, layout, ws, &g, stream);
+    int rc = enqueue_reduce(w, n, p, make_offsets, layout, false, ws, &g, stream);
     if (rc) return rc;
     const FinalizeArgs a = finalize_args(n, p, make_offsets);
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kReduceThreads), 0, stream, part, g, a, st, st_user, offs);
     return check_launch("finalize kernel");
 }
 
-template <int V>
-static void launch_loop(bool narrow, dim3 grid, hipStream_t s, const float* w, uint32_t n, uint32_t m,
-                        const mgp_stats* st, const uint32_t* offs, uint32_t k0, uint32_t k1, uint32_t sid,
-                        uint32_t n_w, uint32_t n_part, uint32_t tag, uint32_t b_cap, uint32_t seg_mask,
-                        int32_t* anc, const RowCopy& rc)
-{
-    if (narrow)
-        hipLaunchKernelGGL((k_resample<V, true>), grid, dim3(kLoopThreads), 0, s, w, n, m, st, offs, k0, k1, sid,
-                           n_w, n_part, tag, b_cap, seg_mask, anc, rc);
-    else
-        hipLaunchKernelGGL((k_resample<V, false>), grid, dim3(kLoopThreads), 0, s, w, n, m, st, offs, k0, k1, sid,
-                           n_w, n_part, tag, b_cap, seg_mask, anc, rc);
-}
+// The accept loop's launch for m outputs from n inputs, with the finalize
+// step done before it (Fin false) or by its blocks.
+template <bool Fin>
+struct LoopLaunch {
+    const float* w;
+    uint32_t n, m;
+    const Params& p;
+    char* ws;
+    LoopStart ls;
+    int32_t* anc;
+    const RowCopy& rc;
+    hipStream_t stream;
+    const uint32_t* offs = reinterpret_cast<const uint32_t*>(ws + kWsOffsetsOffset);
+    uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
+    uint32_t seg_mask = p.segment - 1u;
 
-// A Megopolis loop with the epilogue that fits the row copy.
-template <int P, int D>
-static void launch_megopolis(hipStream_t s, const WindowArgs& wa, uint32_t n, uint32_t m, const mgp_stats* st,
-                             const uint32_t* offs, uint32_t k0, uint32_t k1, uint32_t sid, uint32_t tag, uint32_t cap,
-                             uint32_t seg_mask, int32_t* anc, const RowCopy& rc)
-{
-    const dim3 g((m + kLoopThreads * P - 1u) / (kLoopThreads * P));
-    const dim3 bt(kLoopThreads);
-    const uint32_t d4 = rc.vec4 ? rc.d / 4u : 0u;
-    if (!rc.states)
-        hipLaunchKernelGGL((k_megopolis<P, D, 0>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
-                           anc, rc);
-    else if (d4 == 1u)
-        hipLaunchKernelGGL((k_megopolis<P, D, 1>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
-                           anc, rc);
-    else if (d4 == 2u)
-        hipLaunchKernelGGL((k_megopolis<P, D, 2>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
-                           anc, rc);
-    else if (d4 == 4u)
-        hipLaunchKernelGGL((k_megopolis<P, D, 4>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
-                           anc, rc);
-    else
-        hipLaunchKernelGGL((k_megopolis<P, D, -1>), g, bt, 0, s, wa, n, m, st, offs, k0, k1, sid, tag, cap, seg_mask,
-                           anc, rc);
-}
+    template <int V>
+    void variant() const
+    {
+        const uint32_t n_w = p.partition_bytes / 4u;
+        const uint32_t n_part = (uint32_t)(((uint64_t)n + n_w - 1u) / n_w);
+        const dim3 grid((m + kLoopThreads - 1u) / kLoopThreads);
+        if (Fin || n <= (1u << 30))  // Fin: n <= kFinMaxN
+            hipLaunchKernelGGL((k_resample<V, true, Fin>), grid, dim3(kLoopThreads), 0, stream, w, n, m, ls, offs, k0,
+                               k1, p.stream_id, n_w, n_part, seg_mask, anc, rc);
+        else
+            hipLaunchKernelGGL((k_resample<V, false, false>), grid, dim3(kLoopThreads), 0, stream, w, n, m, ls, offs,
+                               k0, k1, p.stream_id, n_w, n_part, seg_mask, anc, rc);
+    }
+
+    template <int P, int D, int Rows>
+    void windows_rows() const
+    {
+        const dim3 grid((m + kLoopThreads * P - 1u) / (kLoopThreads * P));
+        hipLaunchKernelGGL((k_megopolis<P, D, Rows, Fin>), grid, dim3(kLoopThreads), 0, stream, window_args(w, p, ws),
+                           n, m, ls, offs, k0, k1, p.stream_id, seg_mask, anc, rc);
+    }
+
+    // by windows, with the epilogue that fits the row copy
+    template <int P, int D>
+    void windows() const
+    {
+        const uint32_t d4 = rc.vec4 ? rc.d / 4u : 0u;
+        if (!rc.states)
+            windows_rows<P, D, 0>();
+        else if (d4 == 1u)
+            windows_rows<P, D, 1>();
+        else if (d4 == 2u)
+            windows_rows<P, D, 2>();
+        else if (d4 == 4u)
+            windows_rows<P, D, 4>();
+        else
+            windows_rows<P, D, -1>();
+    }
+
+    int run() const
+    {
+        if (uses_windows(n, p.variant) && m <= n) {
+            if (m <= kSplitMaxM)
+                hipLaunchKernelGGL(k_megopolis_split<(Fin ? kSplitFinalize : kSplitPrepared)>, dim3((m + 63u) / 64u),
+                                   dim3(kLoopThreads), 0, stream, window_args(w, p, ws), n, m, ls, offs, k0, k1,
+                                   p.stream_id, seg_mask, anc, SmallArgs{}, rc);
+            else if (m <= kOneMaxM)
+                windows<1, 20>();
+            else if (m <= kTwoMaxM)
+                windows<2, 10>();
+            else
+                windows<kMegopolisPPT, 5>();
+        } else if (p.variant == kMetropolis) {
+            variant<kMetropolis>();
+        } else if (p.variant == kC1) {
+            variant<kC1>();
+        } else if (p.variant == kC2) {
+            variant<kC2>();
+        } else if constexpr (!Fin) {
+            variant<kMegopolis>();  // m > n, or n beyond the windows
+        }
+        return check_launch("resample kernel");
+    }
+};
 
 int enqueue_loop(const float* w, uint32_t n, const Params& p, char* ws, int32_t* anc, hipStream_t stream,
                  const RowCopy& rc)
@@ -745,51 +831,11 @@ int enqueue_loop(const float* w, uint32_t n, const Params& p, char* ws, int32_t*
 int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, char* ws, int32_t* anc,
                    hipStream_t stream, const RowCopy& rc)
 {
-    const mgp_stats* st = reinterpret_cast<const mgp_stats*>(ws + kWsStatsOffset);
-    const uint32_t* offs = reinterpret_cast<const uint32_t*>(ws + kWsOffsetsOffset);
-    const uint32_t n_w = p.partition_bytes / 4u;
-    const uint32_t n_part = (uint32_t)(((uint64_t)n + n_w - 1u) / n_w);
-    const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
-    const dim3 grid((m + kLoopThreads - 1u) / kLoopThreads);
-    const bool narrow = n <= (1u << 30);
-    const uint32_t tag = call_tag(n, p.variant, p.seed, p.stream_id);
-    const uint32_t cap = p.b_max;
-    const uint32_t seg_mask = p.segment - 1u;
-    if (uses_windows(n, p.variant) && m <= n) {
-        // few outputs are few waves: up to 2^16 the draws spread over four
-        // lanes, up to 2^18 twenty steps' loads per round trip, and four
-        // particles per thread above
-        const WindowArgs wa = window_args(w, p, ws);
-        if (m <= kSplitMaxM)
-            hipLaunchKernelGGL(k_megopolis_split<kSplitPrepared>, dim3((m + 63u) / 64u), dim3(kLoopThreads), 0, stream,
-                               wa, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc, SplitArgs{}, rc);
-        else if (m <= kDeepMaxM)
-            launch_megopolis<1, kDeepSteps>(stream, wa, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask, anc,
-                                            rc);
-        else
-            launch_megopolis<kMegopolisPPT, 5>(stream, wa, n, m, st, offs, k0, k1, p.stream_id, tag, cap, seg_mask,
-                                               anc, rc);
-        return check_launch("megopolis kernel");
-    }
-    switch (p.variant) {
-    case kMetropolis:
-        launch_loop<kMetropolis>(narrow, grid, stream, w, n, m, st, offs, k0, k1, p.stream_id, n_w, n_part, tag, cap, seg_mask, anc,
-                         rc);
-        break;
-    case kC1:
-        launch_loop<kC1>(narrow, grid, stream, w, n, m, st, offs, k0, k1, p.stream_id, n_w, n_part, tag, cap, seg_mask, anc,
-                         rc);
-        break;
-    case kC2:
-        launch_loop<kC2>(narrow, grid, stream, w, n, m, st, offs, k0, k1, p.stream_id, n_w, n_part, tag, cap, seg_mask, anc,
-                         rc);
-        break;
-    default:
-        launch_loop<kMegopolis>(narrow, grid, stream, w, n, m, st, offs, k0, k1, p.stream_id, n_w, n_part, tag, cap, seg_mask, anc,
-                         rc);
-        break;
-    }
-    return check_launch("resample kernel");
+    LoopStart ls{};
+    ls.st = reinterpret_cast<const mgp_stats*>(ws + kWsStatsOffset);
+    ls.tag = call_tag(n, p.variant, p.seed, p.stream_id);
+    ls.b_cap = p.b_max;
+    return LoopLaunch<false>{w, n, m, p, ws, ls, anc, rc, stream}.run();
 }
 
 // mgp_resample with n <= kSmallMaxN (Megopolis) or kSmallMaxNOther: one
@@ -812,18 +858,14 @@ int enqueue_small(const float* w, uint32_t n, const Params& p, char* ws, mgp_sta
     const uint32_t n_part = (uint32_t)(((uint64_t)n + n_w - 1u) / n_w);
     switch (p.variant) {
     case kMegopolis: {
-            SplitArgs f{};
-            f.nparts = g;
-            f.a = a;
-            f.st_ws = st_ws;
-            f.st_user = st_user;
-            f.w = w;
-            f.chunk = chunk;
-            f.copy_vec = copy_vec;
-            f.fold_vec = fold_vec;
+            LoopStart ls{};
+            ls.nparts = g;
+            ls.a = a;
+            ls.st_ws = st_ws;
+            ls.st_user = st_user;
             hipLaunchKernelGGL(k_megopolis_split<kSplitSmall>, dim3((n + 63u) / 64u), dim3(kLoopThreads), 0, stream,
-                               WindowArgs{}, n, n, nullptr, nullptr, a.key0, a.key1, p.stream_id, a.tag, p.b_max,
-                               p.segment - 1u, anc, f, rc);
+                               WindowArgs{}, n, n, ls, nullptr, a.key0, a.key1, p.stream_id, p.segment - 1u, anc,
+                               SmallArgs{w, chunk, copy_vec, fold_vec}, rc);
             break;
         }
     case kMetropolis:
@@ -842,30 +884,41 @@ int enqueue_small(const float* w, uint32_t n, const Params& p, char* ws, mgp_sta
     return check_launch("resample kernel (one launch)");
 }
 
+// mgp_resample does the finalize step inside the loop (two launches instead of
+// three) up to these sizes; beyond, the step repeated in every block costs more
+// than the launch. Whole calls, us, three launches / two, at B = 16:
+//   Megopolis   2^15 10.6 / 9.0, 2^17 11.8 / 9.9, 2^20 19.9 / 18.0, 2^21 28.3 / 29.3
+//   Metropolis  2^14 10.2 / 8.7, 2^18 26.2 / 24.9, 2^19 42.8 / 42.8, 2^20 80.6 / 84.0
+//   C1, C2      2^14 9.9 / 8.4 and 10.3 / 8.9, 2^18 12.8 / 11.8 and 13.6 / 12.6,
+//               2^19 16.5 / 17.1 and 17.9 / 18.9
+constexpr uint32_t kFinMaxN = 1u << 20;
+constexpr uint32_t kFinMaxNOther = 1u << 18;
+constexpr uint32_t kEarlyOffsetsMax = 65536;    // offsets worth drawing before B is known: 16 blocks
+constexpr uint32_t kNoPrepareMaxN = 1u << 15;
+
 int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_stats* st_user, int32_t* anc,
                      hipStream_t stream, const RowCopy& rc)
 {
     if (n <= (p.variant == kMegopolis ? kSmallMaxN : kSmallMaxNOther))
         return enqueue_small(w, n, p, ws, st_user, anc, stream, rc);
+    const bool mego = p.variant == kMegopolis;
     const uint32_t layout = loop_layout(w, n, n, anc, st_user, rc);
-    if (p.variant == kMegopolis && n <= kSplitFusedMaxN) {
-        // two launches: the reduction (partials and windows), then the split
-        // accept loop with the finalize step done in every block
+    if (n <= (mego ? kFinMaxN : kFinMaxNOther) && (!mego || p.B || p.b_max <= kEarlyOffsetsMax)) {
         uint32_t g = 0;
-        const int err = enqueue_reduce(w, n, p, true, layout, ws, &g, stream);
+        const int err = enqueue_reduce(w, n, p, mego, layout, true, ws, &g, stream);
         if (err) return err;
-        SplitArgs f{};
-        f.parts = reinterpret_cast<const Partial*>(ws + kWsPartialsOffset);
-        f.nparts = g;
-        f.a = finalize_args(n, p, false);
-        f.st_ws = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
-        f.st_user = st_user;
-        hipLaunchKernelGGL(k_megopolis_split<kSplitFinalize>, dim3((n + 63u) / 64u), dim3(kLoopThreads), 0, stream,
-                           window_args(w, p, ws), n, n, nullptr, nullptr, f.a.key0, f.a.key1, p.stream_id, f.a.tag, p.b_max,
-                           p.segment - 1u, anc, f, rc);
-        return check_launch("megopolis kernel (finalize and split loop)");
+        LoopStart ls{};
+        ls.parts = reinterpret_cast<const Partial*>(ws + kWsPartialsOffset);
+        ls.nparts = g;
+        ls.a = finalize_args(n, p, false);
+        ls.a.log_eps = reinterpret_cast<const double*>(ws + kWsLogEpsOffset);
+        ls.st_ws = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
+        ls.st_user = st_user;
+        // up to 2^15 particles Megopolis has never left a workspace that a prepared loop takes
+        ls.prepares = !mego || n > kNoPrepareMaxN ? 1u : 0u;
+        return LoopLaunch<true>{w, n, n, p, ws, ls, anc, rc, stream}.run();
     }
-    int err = enqueue_reduce_finalize(w, n, p, p.variant == kMegopolis, layout, ws, st_user, stream);
+    int err = enqueue_reduce_finalize(w, n, p, mego, layout, ws, st_user, stream);
     if (err) return err;
     return enqueue_loop(w, n, p, ws, anc, stream, rc);
 }

@@ -97,6 +97,22 @@ __device__ __forceinline__ void write_window_ends(const float* __restrict__ w, u
 //    offsets are drawn before the particle loop; here in parallel, four per
 //    Philox call).
 // ---------------------------------------------------------------------------
+// Offsets b of [first, end) (first a multiple of 4), four per call, by the
+// threads t, t + stride, ...
+__device__ __forceinline__ void draw_offsets(const FinalizeArgs& a, uint32_t first, uint32_t end, uint32_t t,
+                                             uint32_t stride, uint32_t* __restrict__ offsets)
+{
+    for (uint32_t c = first / 4u + t; c < (end + 3u) / 4u; c += stride) {
+        const Words x = philox(c, kTagOffset, a.stream_id, 0u, a.key0, a.key1);
+        const uint32_t o[4] = {x.x0, x.x1, x.x2, x.x3};
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t b = 4u * c + r;
+            if (b < end) offsets[b] = uniform_index(o[r], a.n);
+        }
+    }
+}
+
 // Returns B (0 for invalid weights) in every thread.
 __device__ __forceinline__ uint32_t finalize_one(const Partial* __restrict__ part, uint32_t nparts, const FinalizeArgs& a,
                              mgp_stats* __restrict__ st, mgp_stats* __restrict__ st_user,
@@ -133,7 +149,7 @@ __device__ __forceinline__ uint32_t finalize_one(const Partial* __restrict__ par
             if (a.B_user > 0) {
                 r.B = a.B_user;
             } else {
-                const double raw = ratio >= 1.0 ? 1.0 : log(a.eps) / log1p(-ratio);
+                const double raw = ratio >= 1.0 ? 1.0 : (a.log_eps ? *a.log_eps : log(a.eps)) / log1p(-ratio);
                 r.b_raw = raw;
                 double c = ceil(raw);
                 if (c < 1.0) c = 1.0;
@@ -150,18 +166,8 @@ __device__ __forceinline__ uint32_t finalize_one(const Partial* __restrict__ par
     }
     __syncthreads();
     const uint32_t B = sB;
-    if (a.make_offsets && B > 0) {
-        const uint32_t calls = (B + 3u) / 4u;
-        for (uint32_t c = threadIdx.x; c < calls; c += blockDim.x) {
-            const Words x = philox(c, kTagOffset, a.stream_id, 0u, a.key0, a.key1);
-            const uint32_t o[4] = {x.x0, x.x1, x.x2, x.x3};
-#pragma unroll
-            for (uint32_t r = 0; r < 4; ++r) {
-                const uint32_t b = 4u * c + r;
-                if (b < B) offsets[b] = uniform_index(o[r], a.n);
-            }
-        }
-    }
+    if (a.make_offsets && B > 0)
+        draw_offsets(a, 0u, B, threadIdx.x, blockDim.x, offsets);
     return B;
 }
 
