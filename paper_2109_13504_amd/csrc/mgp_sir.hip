@@ -45,6 +45,7 @@
 #include "mgp_batch_internal.h"
 #include "mgp_device.h"
 #include "mgp_internal.h"
+#include "mgp_math.h"
 #include "mgp_prefix.h"
 #include "mgp_reduce.h"
 
@@ -53,7 +54,6 @@ namespace mgp {
 constexpr uint32_t kTagSirNoise = 5u;
 constexpr uint32_t kSirThreads = 256;
 constexpr uint32_t kRowAlign = 64;     // floats: every run's row starts 256-byte aligned
-constexpr double kPi = 3.14159265358979323846;
 
 // Box-Muller in its two-output form for one pair of 32-bit words (a, b):
 // u1 = (a + 1) 2^-32 in (0, 1], u2 = b 2^-32 in [0, 1), radius
@@ -61,11 +61,9 @@ constexpr double kPi = 3.14159265358979323846;
 // the sine output to the odd one.
 __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& even, double& odd)
 {
-    const double u1 = ((double)a + 1.0) * 0x1p-32;
-    const double u2 = (double)b * 0x1p-32;
-    const double radius = sqrt(-2.0 * log(u1));
+    const double radius = sqrt_positive(2.0 * neg_log_fraction(a));
     double sn, cs;
-    sincos(2.0 * kPi * u2, &sn, &cs);
+    sincos_turn(b, sn, cs);
     even = radius * cs;
     odd = radius * sn;
 }
@@ -134,11 +132,11 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_predict_update(float* __res
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
             const double xp = (double)xin[k];
-            const double xn = xp / 2.0 + 25.0 * xp / (1.0 + xp * xp) + drift + sigma_v * e[k];
+            const double xn = xp / 2.0 + ratio(25.0 * xp, 1.0 + xp * xp) + drift + sigma_v * e[k];
             xo[k] = (float)xn;
             const double xd = (double)xo[k];
-            const double res = zt - xd * xd / 20.0;
-            wo[k] = (float)exp(-0.5 * res * res);
+            const double res = zt - twentieth(xd * xd);
+            wo[k] = (float)exp_negative(-0.5 * res * res);
         }
         if (full) {
             *reinterpret_cast<float4*>(x + at) = make_float4(xo[0], xo[1], xo[2], xo[3]);
