@@ -49,19 +49,22 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_reduce(const FilterDev
 {
     const RTile t = tiles[blockIdx.x];
     const FilterDev& F = fd[t.f];
+    const float* w = in_hbm(F.w);
+    float* copy = F.copy ? in_hbm(F.copy) : nullptr;
+    if (t.c == kEndsTile) {
+        write_window_ends(w, F.n, copy, F.seam ? in_hbm(F.seam) : nullptr);
+        return;
+    }
     const uint64_t start = (uint64_t)t.c * F.chunk;
     const uint64_t stop = start + F.chunk < (uint64_t)F.n ? start + F.chunk : (uint64_t)F.n;
     const uint64_t end = stop > start ? stop : start;
     float mx = 0.0f;
     double s = 0.0;
     uint32_t bad = 0;
-    const float* w = in_hbm(F.w);
-    float* copy = F.copy ? in_hbm(F.copy) : nullptr;
     if (F.vec)
         reduce_range<true>(w, start, end, copy, mx, s, bad);
     else
         reduce_range<false>(w, start, end, copy, mx, s, bad);
-    if (t.c == 0) write_window_ends(w, F.n, copy, F.seam ? in_hbm(F.seam) : nullptr);
     block_reduce(mx, s, bad);
     if (threadIdx.x == 0) parts[F.part_base + t.c] = Partial{s, mx, bad};
 }
@@ -722,6 +725,8 @@ int mgp_batch_plan_create(const mgp_filter_desc* filters, int32_t count, const m
         total_parts += nparts[f];
         for (uint32_t c = 0; c < nparts[f]; ++c) rt.push_back(RTile{(uint32_t)f, c});
     }
+    if (mego)
+        for (int f = 0; f < count; ++f) rt.push_back(RTile{(uint32_t)f, kEndsTile});
     p->n_rtiles = (uint32_t)rt.size();
     const size_t o_rt = off;
     off = align256(off + sizeof(RTile) * rt.size());

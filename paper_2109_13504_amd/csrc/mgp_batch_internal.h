@@ -54,9 +54,13 @@ struct FilterDev {
 // Floats of a filter's window region.
 inline size_t window_floats(bool in_place, uint32_t n) { return in_place ? 2u * (size_t)kSeam : (size_t)n + kSeam; }
 
+// A block of the batched reduction: chunk c of filter f, or (kEndsTile) the
+// ends of a Megopolis filter's windows, which run beside its chunks then
+// instead of after one of them.
 struct RTile {
     uint32_t f, c;
 };
+constexpr uint32_t kEndsTile = 0xFFFFFFFFu;
 
 struct LTile {
     uint32_t f, start;

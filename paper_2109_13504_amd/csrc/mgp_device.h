@@ -411,8 +411,13 @@ __device__ __forceinline__ uint32_t window_start(uint32_t start, uint32_t o, uin
 // writes it).
 __device__ __forceinline__ void write_seam(const float* __restrict__ w, uint32_t n, float* __restrict__ seam)
 {
-    const uint32_t shift = n - kSeam % n;
-    for (uint32_t k = threadIdx.x; k < 2u * kSeam; k += blockDim.x) seam[k] = w[(k + shift) % n];
+    if (n >= kSeam) {  // no division in the usual case
+        for (uint32_t k = threadIdx.x; k < 2u * kSeam; k += blockDim.x)
+            seam[k] = w[k < kSeam ? n - kSeam + k : k - kSeam];
+    } else {
+        const uint32_t shift = n - kSeam % n;
+        for (uint32_t k = threadIdx.x; k < 2u * kSeam; k += blockDim.x) seam[k] = w[(k + shift) % n];
+    }
 }
 
 // What the rounds of a thread's chains share (wave-uniform but the last two).

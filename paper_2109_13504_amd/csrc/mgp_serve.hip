@@ -220,7 +220,7 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
     std::vector<uint32_t> ns(count);
     std::vector<double> cost(count);
     uint32_t need_rt = 0;
-    for (uint32_t f = 0; f < count; ++f) need_rt += reduce_blocks((uint32_t)rs[f]->in.n);
+    for (uint32_t f = 0; f < count; ++f) need_rt += reduce_blocks((uint32_t)rs[f]->in.n) + 1u;  // and its ends tile
     if (count > s->cap_f || need_rt > s->cap_rt) return fail(MGP_ERANGE, "micro-batch exceeds the slot tables");
     uint32_t nrt = 0;
     for (uint32_t f = 0; f < count; ++f) {
@@ -261,6 +261,8 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
         ns[f] = n;
         cost[f] = (double)n;  // B is found on the device during the run
     }
+    if (s->variant == kMegopolis)
+        for (uint32_t f = 0; f < count; ++f) sl.h_rt[nrt++] = RTile{f, kEndsTile};
     std::vector<LTile> table;
     build_tile_table(ns, cost, s->shape, s->nxcd, table, sl.h_qoff);
     if (table.empty()) table.push_back(LTile{kNoFilter, 0});
