@@ -508,12 +508,12 @@ typedef enum mgp_prefix_method {
 } mgp_prefix_method;
 
 /* Bytes of device workspace mgp_resample_prefix needs for n particles
- * (about 8n: the prefix sums). Host-only. */
+ * (about n/2: sums of groups of 16 inputs). Host-only. */
 int mgp_prefix_workspace_size(int32_t n, size_t* bytes);
 
 /* Ancestors by multinomial or systematic resampling, all on `stream`: the
  * reduction and validation of mgp_resample (stats_dev as there, with B = 1),
- * the fixed-point prefix sum, then one threshold and bisection per output.
+ * the fixed-point prefix sum, then one threshold and search per output.
  * w_dev: n fp32 weights (device), >= 0, finite, not all zero (else stats
  * status MGP_EWEIGHTS and every ancestor -1). ancestors_dev: n int32
  * (device), written. method: mgp_prefix_method. seed, stream_id: the Philox

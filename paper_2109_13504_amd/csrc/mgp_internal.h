@@ -97,6 +97,10 @@ bool in_place(const float* w, uint32_t n, const OutRange* outs, int count);
 // layout: kLayoutInPlace or kLayoutCopy (Megopolis with windows), else unused.
 int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
                             mgp_stats* st_user, hipStream_t stream);
+// The reduction's partials alone, and the arguments of the finalize step that
+// the next kernel does over them.
+int enqueue_partials(const float* w, uint32_t n, const Params& p, char* ws, uint32_t* nparts, FinalizeArgs* fin,
+                     hipStream_t stream);
 // The accept loop (after the reduction and finalize launches); with rc.states
 // set, the particle copy x_bar_i = x_{k_i} runs as its epilogue. anc may be
 // null when rc copies the rows.

@@ -741,6 +741,13 @@ int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool ma
     return check_launch("finalize kernel");
 }
 
+int enqueue_partials(const float* w, uint32_t n, const Params& p, char* ws, uint32_t* nparts, FinalizeArgs* fin,
+                     hipStream_t stream)
+{
+    *fin = finalize_args(n, p, false);
+    return enqueue_reduce(w, n, p, false, kLayoutInPlace, false, ws, nparts, stream);
+}
+
 // The accept loop's launch for m outputs from n inputs, with the finalize
 // step done before it (Fin false) or by its blocks.
 template <bool Fin>

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "mgp.h"
+#include "mgp_internal.h"
 
 namespace mgp {
 
@@ -18,7 +19,14 @@ constexpr int kMaxLevels = 8;  // levels of the 16-ary search tree: 16^8 = 2^32 
 struct PrefixJob {
     const float* w;           // run r's weights: w + r w_ld
     uint64_t w_ld;
-    const mgp_stats* stats;   // run r's validation and max: stats[r]
+    mgp_stats* stats;         // run r's validation and max: stats[r]
+    // Where the finalize step has not run yet (a single filter): the
+    // reduction's partials, over which every block of the first kernel does
+    // it; block 0 writes stats and st_user. parts null: stats are there.
+    const Partial* parts;
+    uint32_t nparts;
+    FinalizeArgs fin;
+    mgp_stats* st_user;
     char* region;
     uint64_t region_ld;
     int32_t* anc;             // run r's ancestors: anc + r anc_ld (null: none)
@@ -32,18 +40,19 @@ struct PrefixJob {
     uint32_t vec;             // the weights of every run 16-byte aligned
     uint32_t key0, key1;
     uint32_t stream0;         // run r draws from stream stream0 + r
-    uint64_t o_hdr, o_sum, o_excl, o_bracket, o_incl;
+    uint64_t o_hdr, o_sum;
     uint64_t o_level[kMaxLevels + 1];  // level k (1..top) of the tree
-    uint32_t count[kMaxLevels + 1];    // its real entries (the last is S), padded with S to a multiple of kFan
-    int top;                           // 0 when n <= kFan (level 0 alone)
+    uint32_t count[kMaxLevels + 1];    // its entries, padded to a multiple of the fan-out
+    uint32_t top_span;                 // count[top] rounded up to a power of two
+    int top;                           // the first level of at most kTopMax entries
 };
 
 // Fills the region layout and n, nch, log2n of J for runs of n particles;
 // returns the bytes of one run's region.
 uint64_t prefix_region(uint32_t n, PrefixJob* J);
 
-// Enqueues the scan and search of a job whose stats (validation, max) are
-// already on the device: R runs, method MGP_MULTINOMIAL or MGP_SYSTEMATIC.
+// Enqueues the scan and search of a job: R runs, method MGP_MULTINOMIAL or
+// MGP_SYSTEMATIC.
 int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s);
 
 }  // namespace mgp

@@ -10,32 +10,40 @@
 // exact in any order, so the parallel scan here and a sequential sum give the
 // same prefix and the same ancestors.
 //
-// The search runs down a 16-ary tree over the prefix sums: level 0 is the
-// inclusive sums themselves, level k holds every 16^k-th of them (the sum at
-// the end of each group of 16^k inputs), and the top level has at most 16
-// entries. A lane reads one 128-byte row of 16 sums per level and counts the
-// sums <= t, which is the child to descend into.
+// The search runs down a 16-ary tree of exclusive sums: level 1 holds the sum
+// before every group of 16 inputs, level k that before every 16^k inputs, and
+// the top is the first level of at most 2048 entries, which a block keeps in
+// LDS. The sums inside a group are not stored: the search adds up the group's
+// own 64 bytes of weights. A level of 8 bytes per input would be 16 times
+// level 1 (128 of 136 MB at 2^24), written once and read for the last line of
+// every descent; this way the scan works on 0.5 byte per input and the last
+// line comes from the weights.
 //
-// Launches: the reduction and finalize step of the other resamplers
-// (validation, max, fp64 sum), then
-//   k_prefix_chunks   per chunk of kChunk weights: the fixed-point chunk sum
-//   k_prefix_top      one block: exclusive sums over the chunks, the header
-//   k_prefix_scan     per chunk: the inclusive sums (coalesced through LDS)
-//                     and the tree's entries that fall in the chunk
-//   multinomial:      k_prefix_multinomial, a descent per output (eight
-//                     lanes share each row read)
-//   systematic:       k_prefix_brackets, a descent for every 256th output,
-//                     then k_prefix_systematic, a bisection per output between
-//                     the two brackets of its group (thresholds rise with i)
+// Launches, after the reduction of the other resamplers (validation, max,
+// fp64 sum):
+//   k_prefix_groups   per chunk of 2048 weights: the fixed-point sum of each
+//                     group, and of the chunk; for a single filter its blocks
+//                     also do the finalize step over the reduction's partials
+//   k_prefix_scan     per 2048 groups: the levels' exclusive sums, the header
+//                     (up to 32768 inputs the search's blocks do it instead)
+//   k_prefix_multinomial   a descent per output, four lanes to a row
+//   k_prefix_systematic    1024 outputs per block, whose inputs (thresholds rise
+//                     with i) are added up once, in LDS, and bisected there
+// Whole calls, us, with a level of sums per input and six or seven launches /
+// now: multinomial 10^3 19 / 11, 2^16 22 / 17, 2^20 54 / 39, 2^24 626 / 571;
+// systematic 10^3 20 / 14, 2^16 24 / 19, 10^7 107 / 77, 2^24 154 / 108.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mgp.h"
 #include "mgp_device.h"
 #include "mgp_internal.h"
 #include "mgp_prefix.h"
+#include "mgp_reduce.h"
 
 namespace mgp {
 
@@ -43,6 +51,9 @@ constexpr uint32_t kPrefixThreads = 256;
 constexpr uint32_t kPrefixPer = 8;                        // weights per thread in a chunk
 constexpr uint32_t kChunk = kPrefixThreads * kPrefixPer;  // 2048 weights per chunk
 constexpr uint32_t kFan = 16;                             // the tree's fan-out: one 128-byte row of sums
+constexpr uint32_t kTopMax = 2048;                        // entries of the top level, kept in LDS (16 KB)
+constexpr uint32_t kScanGroups = kPrefixThreads * 8;      // groups per block of the scan
+constexpr uint32_t kChunksPerScan = kScanGroups * kFan / kChunk;
 constexpr uint32_t kTagMultinomial = 6u;
 constexpr uint32_t kTagSystematic = 7u;
 
@@ -67,18 +78,21 @@ __device__ __forceinline__ int fixed_exponent(float w_max, int log2n_ceil)
     return 62 - log2n_ceil - E;
 }
 
-// q = floor(w 2^K) for a finite w >= 0, from its fields: w = m 2^(e - 150)
-// with m = 2^23 + mantissa for a normal w (biased exponent e >= 1), and
-// w = mantissa 2^-149 for a subnormal one; the shift by e - 150 + K is exact
-// (a right shift floors).
-__device__ __forceinline__ uint64_t fixed_weight(float w, int K)
+// q = floor(w 2^K) for a finite w >= 0 with q < 2^62, given scale = 2^(K - 32):
+// y = w 2^(K - 32) is exact in fp64 (24 bits; K - 32 is between -98 and 179),
+// its integer part is the high word and its fraction times 2^32, cut off, the
+// low word.
+__device__ __forceinline__ uint64_t fixed_weight(float w, double scale)
 {
-    const uint32_t bits = __float_as_uint(w) & 0x7FFFFFFFu;  // -0.0 is 0
-    const uint32_t e = bits >> 23;
-    const uint64_t m = e ? (uint64_t)((bits & 0x7FFFFFu) | 0x800000u) : (uint64_t)bits;
-    const int sh = (e ? (int)e - 150 : -149) + K;
-    if (sh >= 0) return m << sh;
-    return sh <= -64 ? 0u : m >> (-sh);
+    const double y = (double)w * scale;
+    const uint32_t hi = (uint32_t)y;
+    const uint32_t lo = (uint32_t)(__builtin_amdgcn_fract(y) * 0x1p32);
+    return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
+__device__ __forceinline__ double fixed_scale(float w_max, int log2n_ceil)
+{
+    return ldexp(1.0, fixed_exponent(w_max, log2n_ceil) - 32);
 }
 
 // Block-wide exclusive scan of one uint64 per thread; returns the thread's
@@ -107,198 +121,179 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* t
     return before + x - v;
 }
 
-// The fixed-point weights of this thread's kPrefixPer consecutive inputs of
-// chunk `chunk` of the run (0 past n).
-__device__ __forceinline__ void load_fixed(const PrefixJob& J, uint32_t chunk, int K, uint64_t (&q)[kPrefixPer])
+// The fixed-point weights of the Per consecutive inputs from `base` on (0 past
+// n; Per and base multiples of 4). Whole: base + Per <= n is known and the
+// weights are 16-byte aligned.
+template <int Per, bool Whole>
+__device__ __forceinline__ void load_fixed(const PrefixJob& J, uint64_t base, double scale, uint64_t (&q)[Per])
 {
-    const float* __restrict__ w = J.w + (uint64_t)blockIdx.y * J.w_ld;
-    const uint64_t base = (uint64_t)chunk * kChunk + (uint64_t)threadIdx.x * kPrefixPer;
-    if (J.vec && base + kPrefixPer <= J.n) {
-        const float4 a = *reinterpret_cast<const float4*>(w + base);
-        const float4 b = *reinterpret_cast<const float4*>(w + base + 4);
-        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    const GlobalPtr<const float> w = global_ptr(J.w + (uint64_t)blockIdx.y * J.w_ld);
+    float v[Per];
+    if (Whole) {
 #pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; ++e) q[e] = fixed_weight(v[e], K);
+        for (int e = 0; e < Per; e += 4) {
+            const Row4 x = *(GlobalPtr<const Row4>)(w + base + e);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[e + c] = x[c];
+        }
     } else {
 #pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; ++e) q[e] = base + e < J.n ? fixed_weight(w[base + e], K) : 0u;
+        for (int e = 0; e < Per; ++e) v[e] = base + e < J.n ? w[base + e] : 0.0f;
     }
+#pragma unroll
+    for (int e = 0; e < Per; ++e) q[e] = fixed_weight(v[e], scale);
 }
 
-__global__ __launch_bounds__(kPrefixThreads) void k_prefix_chunks(PrefixJob J)
+// The same for a block whose threads read Per inputs each from `first` on, one
+// after the other: all of them inside n, or each checked.
+template <int Per>
+__device__ __forceinline__ void load_fixed_tile(const PrefixJob& J, uint64_t first, double scale, uint64_t (&q)[Per])
 {
-    const mgp_stats& st = J.stats[blockIdx.y];
-    uint64_t* chunk_sum = at<uint64_t>(J, J.o_sum);
-    if (st.status != MGP_OK) {
-        if (threadIdx.x == 0) chunk_sum[blockIdx.x] = 0;
-        return;
+    const uint64_t base = first + (uint64_t)threadIdx.x * Per;
+    if (J.vec && first + (uint64_t)Per * kPrefixThreads <= J.n)
+        load_fixed<Per, true>(J, base, scale, q);
+    else
+        load_fixed<Per, false>(J, base, scale, q);
+}
+
+// The sums of the chunk's groups (in level 1's place) and of the chunk. Fin:
+// the finalize step of the call comes first, in every block.
+template <bool Fin>
+__global__ __launch_bounds__(kPrefixThreads) void k_prefix_groups(PrefixJob J)
+{
+    mgp_stats st;
+    if constexpr (Fin) {
+        __shared__ mgp_stats st_local;
+        finalize_one(J.parts, J.nparts, J.fin, &st_local, blockIdx.x == 0 ? J.st_user : nullptr, nullptr);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *J.stats = st_local;
+        st = st_local;
+    } else {
+        st = J.stats[blockIdx.y];
     }
+    if (st.status != MGP_OK) return;
     uint64_t q[kPrefixPer];
-    load_fixed(J, blockIdx.x, fixed_exponent(st.w_max, J.log2n), q);
+    load_fixed_tile(J, (uint64_t)blockIdx.x * kChunk, fixed_scale(st.w_max, J.log2n), q);
     uint64_t s = 0;
 #pragma unroll
     for (uint32_t e = 0; e < kPrefixPer; ++e) s += q[e];
+    // two threads hold a group
+    const uint64_t both = s + (uint64_t)__shfl_xor((unsigned long long)s, 1, 64);
+    const uint32_t g = blockIdx.x * (kChunk / kFan) + threadIdx.x / 2u;
+    if (threadIdx.x % 2u == 0 && g < J.count[1]) at<uint64_t>(J, J.o_level[1])[g] = both;
     uint64_t total = 0;
     block_exclusive_scan(s, &total);
-    if (threadIdx.x == 0) chunk_sum[blockIdx.x] = total;
+    if (threadIdx.x == 0) at<uint64_t>(J, J.o_sum)[blockIdx.x] = total;
 }
 
-// One block per run: chunk_excl[c] = sum of chunk_sum[0..c), and the header.
-// The chunk sums go through LDS a tile of kChunk at a time, so that the
-// loads and stores are coalesced; each thread scans kPrefixPer consecutive
-// sums of the tile, and the tile's total carries into the next.
-__global__ __launch_bounds__(kPrefixThreads) void k_prefix_top(PrefixJob J)
-{
-    __shared__ uint64_t tile[kChunk];
-    const uint64_t* chunk_sum = at<uint64_t>(J, J.o_sum);
-    uint64_t* chunk_excl = at<uint64_t>(J, J.o_excl);
-    uint64_t carry = 0;
-    for (uint32_t base = 0; base < J.nch; base += kChunk) {
-#pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; ++e) {
-            const uint32_t c = base + e * kPrefixThreads + threadIdx.x;
-            tile[e * kPrefixThreads + threadIdx.x] = c < J.nch ? chunk_sum[c] : 0u;
-        }
-        __syncthreads();
-        uint64_t v[kPrefixPer];
-        uint64_t s = 0;
-#pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; ++e) {
-            v[e] = tile[threadIdx.x * kPrefixPer + e];
-            s += v[e];
-        }
-        uint64_t total = 0;
-        uint64_t run = carry + block_exclusive_scan(s, &total);
-#pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; ++e) {
-            tile[threadIdx.x * kPrefixPer + e] = run;
-            run += v[e];
-        }
-        __syncthreads();
-#pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; ++e) {
-            const uint32_t c = base + e * kPrefixThreads + threadIdx.x;
-            if (c < J.nch) chunk_excl[c] = tile[e * kPrefixThreads + threadIdx.x];
-        }
-        carry += total;
-        __syncthreads();  // the tile is overwritten next
-    }
-    if (threadIdx.x == 0) {
-        const mgp_stats& st = J.stats[blockIdx.y];
-        const bool ok = st.status == MGP_OK;
-        PrefixHeader h;
-        h.total = ok ? carry : 0u;
-        h.K = ok ? fixed_exponent(st.w_max, J.log2n) : 0;
-        h.valid = ok ? 1 : 0;
-        *at<PrefixHeader>(J, J.o_hdr) = h;
-    }
-}
-
-// The inclusive sums of one chunk: computed per thread over its kPrefixPer
-// inputs, passed through LDS so that each store instruction writes 512
-// contiguous bytes. Positions past n hold S (level 0 is padded to whole
-// chunks). The tree's entries that fall in the chunk are written here too:
-// level k entry m is the sum at position (m + 1) 16^k - 1, and the thread
-// holding position n - 1 writes the last real entry (S) and the padding of
-// every level.
+// The exclusive sums of kScanGroups groups, from the chunk sums before them
+// and the groups' own sums, which they replace; the entries of the higher
+// levels among them; and, by the block with the last group, every level's
+// padding (the largest integer, above any threshold) and the header.
 __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
 {
-    __shared__ uint64_t stage[kChunk];
-    const PrefixHeader h = *at<PrefixHeader>(J, J.o_hdr);
-    if (!h.valid) return;
-    uint64_t q[kPrefixPer];
-    load_fixed(J, blockIdx.x, h.K, q);
+    const mgp_stats& st = J.stats[blockIdx.y];
+    const bool last = blockIdx.x == gridDim.x - 1u;
+    if (st.status != MGP_OK) {
+        if (last && threadIdx.x == 0) *at<PrefixHeader>(J, J.o_hdr) = PrefixHeader{0u, 0, 0};
+        return;
+    }
+    uint64_t* x1 = at<uint64_t>(J, J.o_level[1]);
+    const uint32_t g0 = blockIdx.x * kScanGroups + threadIdx.x * 8u;
+    uint64_t v[8];
+#pragma unroll
+    for (uint32_t e = 0; e < 8u; ++e) v[e] = g0 + e < J.count[1] ? x1[g0 + e] : 0u;
+    const uint64_t* chunk_sum = at<uint64_t>(J, J.o_sum);
+    uint64_t before = 0;
+#pragma unroll 8
+    for (uint32_t c = threadIdx.x; c < blockIdx.x * kChunksPerScan; c += kPrefixThreads) before += chunk_sum[c];
+    uint64_t base = 0, total = 0;
+    block_exclusive_scan(before, &base);
     uint64_t s = 0;
 #pragma unroll
-    for (uint32_t e = 0; e < kPrefixPer; ++e) s += q[e];
-    uint64_t total = 0;
-    uint64_t run = at<uint64_t>(J, J.o_excl)[blockIdx.x] + block_exclusive_scan(s, &total);
-    const uint64_t base = (uint64_t)blockIdx.x * kChunk;
-    const uint64_t mine = base + (uint64_t)threadIdx.x * kPrefixPer;
+    for (uint32_t e = 0; e < 8u; ++e) s += v[e];
+    uint64_t run = base + block_exclusive_scan(s, &total);
 #pragma unroll
-    for (uint32_t e = 0; e < kPrefixPer; ++e) {
-        run += q[e];
-        stage[threadIdx.x * kPrefixPer + e] = run;
-        const uint64_t p = mine + e;
-        if (p < J.n && (p + 1u) % kFan == 0u) {
-            // level k entry (p + 1) / 16^k - 1 for every k with 16^k | p + 1
-            uint64_t g = (p + 1u) / kFan;
+    for (uint32_t e = 0; e < 8u; ++e) {
+        if (g0 + e < J.count[1]) {
+            // level k entry m is the sum before input m 16^k
+            uint32_t g = g0 + e;
             for (int k = 1; k <= J.top; ++k) {
-                at<uint64_t>(J, J.o_level[k])[g - 1u] = run;
+                at<uint64_t>(J, J.o_level[k])[g] = run;
                 if (g % kFan != 0u) break;
                 g /= kFan;
             }
         }
-        if (p == (uint64_t)J.n - 1u) {
-            for (int k = 1; k <= J.top; ++k) {
-                uint64_t* lv = at<uint64_t>(J, J.o_level[k]);
-                const uint32_t end = (J.count[k] + kFan - 1u) / kFan * kFan;
-                for (uint32_t m = J.count[k] - 1u; m < end; ++m) lv[m] = run;
-            }
-        }
+        run += v[e];
     }
-    __syncthreads();
-    uint64_t* incl = at<uint64_t>(J, J.o_incl);
-#pragma unroll
-    for (uint32_t e = 0; e < kPrefixPer; ++e)
-        incl[base + e * kPrefixThreads + threadIdx.x] = stage[e * kPrefixThreads + threadIdx.x];
+    if (last) {
+        for (int k = 1; k <= J.top; ++k) {
+            const uint32_t end = (J.count[k] + kFan - 1u) / kFan * kFan;
+            const uint32_t m = J.count[k] + threadIdx.x;
+            if (m < end) at<uint64_t>(J, J.o_level[k])[m] = ~(uint64_t)0;
+        }
+        if (threadIdx.x == 0)
+            *at<PrefixHeader>(J, J.o_hdr) = PrefixHeader{base + total, fixed_exponent(st.w_max, J.log2n), 1};
+    }
 }
 
-// The first j with incl[j] > t (t < S): down the tree, one row of kFan sums
-// per level.
-__device__ __forceinline__ uint32_t descend(const PrefixJob& J, uint64_t t)
+// The input whose interval holds t (t < S), by one lane on its own: down the
+// tree, then through the group's weights.
+__device__ __forceinline__ uint32_t descend(const PrefixJob& J, double scale, uint64_t t)
 {
-    uint64_t g = 0;
-    for (int k = J.top; k >= 0; --k) {
-        const uint64_t* row = at<uint64_t>(J, k ? J.o_level[k] : J.o_incl) + g * kFan;
-        uint64_t v[kFan];
-#pragma unroll
-        for (uint32_t m = 0; m < kFan; m += 2) {
-            const ulonglong2 x = *reinterpret_cast<const ulonglong2*>(row + m);
-            v[m] = x.x;
-            v[m + 1] = x.y;
-        }
+    const uint64_t* top = at<uint64_t>(J, J.o_level[J.top]);
+    uint32_t g = 0;
+    for (uint32_t step = J.top_span / 2u; step > 0; step >>= 1)
+        if (g + step < J.count[J.top] && top[g + step] <= t) g += step;
+    uint64_t before = top[g];
+    for (int k = J.top - 1; k >= 1; --k) {
+        const uint64_t* row = at<uint64_t>(J, J.o_level[k]) + (uint64_t)g * kFan;
         uint32_t c = 0;
-#pragma unroll
-        for (uint32_t m = 0; m < kFan; ++m) c += v[m] <= t ? 1u : 0u;
+        for (uint32_t m = 1; m < kFan; ++m)
+            if (row[m] <= t) c = m;
+        before = row[c];
         g = g * kFan + c;
     }
-    return (uint32_t)g;
-}
-
-// The first j in [lo, lo + len) with a[j] > t, given a[lo + len - 1] > t.
-__device__ __forceinline__ uint32_t first_above(const uint64_t* __restrict__ a, uint32_t lo, uint32_t len, uint64_t t)
-{
-    while (len > 1u) {
-        const uint32_t half = len / 2u;
-        lo = a[lo + half - 1u] <= t ? lo + half : lo;  // [lo, lo + half) all <= t: skip them
-        len -= half;
+    uint64_t q[kFan];
+    load_fixed<(int)kFan, false>(J, (uint64_t)g * kFan, scale, q);
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < kFan; ++e) {
+        before += q[e];
+        c += before <= t ? 1u : 0u;
     }
-    return lo;
+    return g * kFan + c;
 }
 
-// The threshold of output i of run r in [0, S).
-template <int Method>
-__device__ __forceinline__ uint64_t prefix_threshold(const PrefixJob& J, uint64_t S, uint32_t i)
+// Algorithm 7: the threshold of output i of run r, u ~ U[0, S), one 64-bit draw
+// per output.
+__device__ __forceinline__ uint64_t multinomial_threshold(const PrefixJob& J, uint64_t S, uint32_t i)
 {
-    const uint32_t sid = J.stream0 + blockIdx.y;
-    if constexpr (Method == MGP_MULTINOMIAL) {
-        // Algorithm 7: u ~ U[0, S), one 64-bit draw per output
-        const Words x = philox(0u, kTagMultinomial, sid, i, J.key0, J.key1);
+    const Words x = philox(0u, kTagMultinomial, J.stream0 + blockIdx.y, i, J.key0, J.key1);
+    const uint64_t r = (uint64_t)x.x0 | ((uint64_t)x.x1 << 32);
+    return __umul64hi(r, S);
+}
+
+// Algorithm 8: u = (i + u_t) / N after one draw u_t ~ U[0, 1) per run, in fp64
+// with each operation rounded once.
+struct SystematicDraw {
+    double ut, c;  // u_t, S / N
+    uint64_t S;
+
+    __device__ __forceinline__ SystematicDraw(const PrefixJob& J, uint64_t total) : S(total)
+    {
+        const Words x = philox(0u, kTagSystematic, J.stream0 + blockIdx.y, 0u, J.key0, J.key1);
         const uint64_t r = (uint64_t)x.x0 | ((uint64_t)x.x1 << 32);
-        return __umul64hi(r, S);
-    } else {
-        // Algorithm 8: u = (i + u_t) / N after one draw u_t ~ U[0, 1), in fp64
-        // with each operation rounded once
-        const Words x = philox(0u, kTagSystematic, sid, 0u, J.key0, J.key1);
-        const uint64_t r = (uint64_t)x.x0 | ((uint64_t)x.x1 << 32);
-        const double ut = (double)(r >> 11) * 0x1p-53;
-        const double c = __ddiv_rn((double)S, (double)J.n);
-        const double v = __dmul_rn(__dadd_rn((double)i, ut), c);
-        const uint64_t t = (uint64_t)floor(v);
+        ut = (double)(r >> 11) * 0x1p-53;
+        c = __ddiv_rn((double)S, (double)J.n);
+    }
+
+    // rises with i
+    __device__ __forceinline__ uint64_t threshold(uint32_t i) const
+    {
+        const uint64_t t = (uint64_t)floor(__dmul_rn(__dadd_rn((double)i, ut), c));
         return t < S ? t : S - 1u;
     }
-}
+};
 
 // Output i of run r: the ancestor and, when the job copies rows, the row
 // (a NaN row for invalid weights, a = -1).
@@ -312,116 +307,309 @@ __device__ __forceinline__ void emit(const PrefixJob& J, uint32_t i, int32_t a)
     }
 }
 
-// Multinomial: the descents of a wave's 64 outputs, eight lanes to a row.
-// A lane that read a whole 128-byte row by itself would make each load
-// instruction of the wave touch 64 lines, and the address path, not the
-// memory, would bound the kernel. Here the lanes of an octet (8 lanes) read
-// the 16-byte quarters of one row together, so an instruction touches 8
-// lines: lane l serves outputs r*8 + l/8 (r = 0..7) of the wave, reading
-// their rows' quarter l mod 8, and the octet adds up its counts. Lane l draws
-// the threshold of output l, and gets back the ancestor of output l, by
-// cross-lane permutes. Every lane of the wave runs to the end (outputs past n
-// search too, and are not stored).
-__global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob J)
+using U64x2 = uint64_t __attribute__((ext_vector_type(2)));
+
+// For up to kTopMax groups (32768 inputs), whose level 1 is the top: the scan
+// of the groups' sums in LDS by the block that searches them, so that
+// k_prefix_scan's launch goes. top[g] is the sum before group g, the largest
+// integer from the last group to kTopMax.
+__device__ __forceinline__ PrefixHeader scan_in_lds(const PrefixJob& J, uint64_t* top)
 {
-    constexpr uint32_t kOct = 8;  // lanes per row; also the outputs per lane
+    const mgp_stats& st = J.stats[blockIdx.y];
+    if (st.status != MGP_OK) return PrefixHeader{0u, 0, 0};
+    const uint64_t* x1 = at<uint64_t>(J, J.o_level[1]);
+    const uint32_t g0 = threadIdx.x * 8u;
+    uint64_t v[8], s = 0, total = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < 8u; ++e) v[e] = g0 + e < J.count[1] ? x1[g0 + e] : 0u;
+#pragma unroll
+    for (uint32_t e = 0; e < 8u; ++e) s += v[e];
+    uint64_t run = block_exclusive_scan(s, &total);
+#pragma unroll
+    for (uint32_t e = 0; e < 8u; ++e) {
+        top[g0 + e] = g0 + e < J.count[1] ? run : ~(uint64_t)0;
+        run += v[e];
+    }
+    __syncthreads();
+    return PrefixHeader{total, fixed_exponent(st.w_max, J.log2n), 1};
+}
+static_assert(kTopMax == kPrefixThreads * 8u, "eight groups per thread");
+
+// x of the lane whose number differs in the bits of Mask (1 or 2): a quad
+// permutation on the vector unit.
+template <int Mask>
+__device__ __forceinline__ uint32_t quad_swap(uint32_t x)
+{
+    constexpr int kPerm = Mask == 1 ? 0xB1 : 0x4E;  // lanes 1,0,3,2 or 2,3,0,1 of each four
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kPerm, 0xF, 0xF, true);
+}
+
+template <int Mask>
+__device__ __forceinline__ uint64_t quad_swap(uint64_t x)
+{
+    return (uint64_t)quad_swap<Mask>((uint32_t)x) | ((uint64_t)quad_swap<Mask>((uint32_t)(x >> 32)) << 32);
+}
+
+__device__ __forceinline__ uint64_t shuffle64(uint64_t x, int src)
+{
+    return (uint64_t)(uint32_t)__shfl((int)(uint32_t)x, src, 64) |
+           ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(x >> 32), src, 64) << 32);
+}
+
+// Multinomial: 64 outputs per wave and pass. Each lane bisects the top level in
+// LDS for its own output; the rows below are read by quads, so that one load
+// instruction touches 16 lines and not 64 (a row per lane would be bound by
+// the address path): lane l serves the outputs r*16 + l/4, r < 4, reading their
+// rows' parts l mod 4, and the quad adds up its counts. Requests to L2: one
+// line per level below the top and one of weights, two in all up to 2^19
+// inputs and three up to 2^23 (five and six with a level of sums per input and
+// no level in LDS). What bounds it is VALU issue, about half of it the 64-bit
+// sums of the groups' weights. Every lane of the wave runs to the end (outputs
+// past n search too, and are not stored). Narrow: n <= 2^30, the byte offsets
+// of weights and sums fit 32 bits.
+template <bool Narrow, bool OwnScan>
+__global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob J, uint32_t passes)
+{
+    using Off = std::conditional_t<Narrow, uint32_t, uint64_t>;
+    __shared__ uint64_t top[kTopMax];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t i = blockIdx.x * kPrefixThreads + threadIdx.x;
-    const PrefixHeader h = *at<PrefixHeader>(J, J.o_hdr);
+    const uint32_t first = blockIdx.x * kPrefixThreads * passes + threadIdx.x;
+    PrefixHeader h;
+    if constexpr (OwnScan)
+        h = scan_in_lds(J, top);
+    else
+        h = *at<PrefixHeader>(J, J.o_hdr);
     if (!h.valid) {
-        if (i < J.n) emit(J, i, -1);
+        for (uint32_t p = 0; p < passes; ++p)
+            if (first + p * kPrefixThreads < J.n) emit(J, first + p * kPrefixThreads, -1);
         return;
     }
-    const uint64_t t_mine = prefix_threshold<MGP_MULTINOMIAL>(J, h.total, i < J.n ? i : J.n - 1u);
-    const uint32_t oct = lane / kOct, quarter = lane % kOct;
-    uint64_t t[kOct];
-    uint32_t g[kOct];
-#pragma unroll
-    for (uint32_t r = 0; r < kOct; ++r) {
-        const int src = (int)(r * kOct + oct);
-        const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)t_mine, src, 64);
-        const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(t_mine >> 32), src, 64);
-        t[r] = (uint64_t)lo | ((uint64_t)hi << 32);
-        g[r] = 0u;
-    }
-    for (int k = J.top; k >= 0; --k) {
-        const uint64_t* lv = at<uint64_t>(J, k ? J.o_level[k] : J.o_incl) + quarter * 2u;
-        ulonglong2 v[kOct];
-#pragma unroll
-        for (uint32_t r = 0; r < kOct; ++r) v[r] = *reinterpret_cast<const ulonglong2*>(lv + (uint64_t)g[r] * kFan);
-        // counts of up to 16 per row, one byte each: outputs 0-3 in c0, 4-7 in c1
-        uint32_t c0 = 0, c1 = 0;
-#pragma unroll
-        for (uint32_t r = 0; r < kOct; ++r) {
-            const uint32_t c = (v[r].x <= t[r] ? 1u : 0u) + (v[r].y <= t[r] ? 1u : 0u);
-            if (r < 4) c0 |= c << (8u * r);
-            else c1 |= c << (8u * (r - 4u));
-        }
-#pragma unroll
-        for (int off = 1; off < (int)kOct; off <<= 1) {
-            c0 += (uint32_t)__shfl_xor((int)c0, off, 64);
-            c1 += (uint32_t)__shfl_xor((int)c1, off, 64);
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < kOct; ++r)
-            g[r] = g[r] * kFan + (((r < 4 ? c0 : c1) >> (8u * (r % 4u))) & 0xFFu);
-    }
-    // output l's ancestor is g[l / 8] of the octet l mod 8
-    uint32_t a = 0;
-#pragma unroll
-    for (uint32_t r = 0; r < kOct; ++r) {
-        const uint32_t x = (uint32_t)__shfl((int)g[r], (int)((lane % kOct) * kOct), 64);
-        if (lane / kOct == r) a = x;
-    }
-    if (i < J.n) emit(J, i, (int32_t)a);
-}
-
-// Systematic, first pass: the ancestors of outputs 0, G, 2G, ... (G =
-// kPrefixThreads) and n - 1, which bracket those of every output between.
-__global__ __launch_bounds__(kPrefixThreads) void k_prefix_brackets(PrefixJob J, uint32_t nb)
-{
-    const uint32_t b = blockIdx.x * kPrefixThreads + threadIdx.x;
-    const PrefixHeader h = *at<PrefixHeader>(J, J.o_hdr);
-    if (b > nb || !h.valid) return;
-    const uint32_t i = b < nb ? b * kPrefixThreads : J.n - 1u;
-    at<uint32_t>(J, J.o_bracket)[b] = descend(J, prefix_threshold<MGP_SYSTEMATIC>(J, h.total, i));
-}
-
-// Systematic, second pass: output i's ancestor lies between the brackets of
-// its group of G outputs (the thresholds, and so the ancestors, rise with
-// i). When the bracketed sums fit kStageMax entries the block reads them into
-// LDS once (coalesced) and bisects there; otherwise each lane bisects in
-// memory.
-constexpr uint32_t kStageMax = 2048;
-
-__global__ __launch_bounds__(kPrefixThreads) void k_prefix_systematic(PrefixJob J)
-{
-    __shared__ uint64_t stage[kStageMax];
-    const uint32_t i = blockIdx.x * kPrefixThreads + threadIdx.x;
-    const PrefixHeader h = *at<PrefixHeader>(J, J.o_hdr);
-    if (!h.valid) {
-        if (i < J.n) emit(J, i, -1);
-        return;
-    }
-    const uint32_t* bracket = at<uint32_t>(J, J.o_bracket);
-    const uint64_t* incl = at<uint64_t>(J, J.o_incl);
-    const uint32_t lo = bracket[blockIdx.x], hi = bracket[blockIdx.x + 1u];
-    const uint32_t len = hi - lo + 1u;
-    const uint64_t t = prefix_threshold<MGP_SYSTEMATIC>(J, h.total, i < J.n ? i : J.n - 1u);
-    if (len <= kStageMax) {  // the same for every lane of the block
-        for (uint32_t k = threadIdx.x; k < len; k += kPrefixThreads) stage[k] = incl[lo + k];
+    if constexpr (!OwnScan) {
+        const uint64_t* lv_top = at<uint64_t>(J, J.o_level[J.top]);
+        for (uint32_t k = threadIdx.x; k < J.top_span; k += kPrefixThreads)
+            top[k] = k < J.count[J.top] ? lv_top[k] : ~(uint64_t)0;
         __syncthreads();
-        if (i < J.n) emit(J, i, (int32_t)(lo + first_above(stage, 0u, len, t)));
-    } else if (i < J.n) {
-        emit(J, i, (int32_t)first_above(incl, lo, len, t));
+    }
+    const double scale = ldexp(1.0, h.K - 32);
+    const uint32_t quad = lane / 4u, part = lane % 4u;
+    const GlobalPtr<const char> w = global_ptr(reinterpret_cast<const char*>(J.w + (uint64_t)blockIdx.y * J.w_ld));
+    const uint32_t whole = J.vec ? J.n / kFan : 0u;  // groups below it can be read by vectors
+    for (uint32_t p = 0; p < passes; ++p) {
+        const uint32_t i = first + p * kPrefixThreads;
+        const uint64_t t_own = multinomial_threshold(J, h.total, i < J.n ? i : J.n - 1u);
+        // the last entry <= t; entry 0 is 0
+        uint32_t g_own = 0;
+        for (uint32_t step = J.top_span / 2u; step > 0; step >>= 1)
+            if (top[g_own + step] <= t_own) g_own += step;
+        uint64_t t[4], before[4];
+        uint32_t g[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int src = (int)(r * 16 + quad);
+            before[r] = shuffle64(top[g_own], src);
+            t[r] = shuffle64(t_own, src);
+            g[r] = (uint32_t)__shfl((int)g_own, src, 64);
+        }
+        for (int k = J.top - 1; k >= 1; --k) {
+            const GlobalPtr<const char> lv = global_ptr(at<const char>(J, J.o_level[k]));
+            U64x2 a[4], b[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const Off row = (Off)g[r] * (8u * kFan) + part * 16u;
+                a[r] = *(GlobalPtr<const U64x2>)(lv + row);
+                b[r] = *(GlobalPtr<const U64x2>)(lv + row + 64u);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                uint32_t c = (a[r].x <= t[r] ? 1u : 0u) + (a[r].y <= t[r] ? 1u : 0u) + (b[r].x <= t[r] ? 1u : 0u) +
+                             (b[r].y <= t[r] ? 1u : 0u);
+                c += quad_swap<1>(c);
+                c += quad_swap<2>(c);
+                g[r] = g[r] * kFan + c - 1u;  // entry 0 of a row is <= t
+                if (k == 1) {
+                    // the largest entry <= t of the row, the sum before the
+                    // group (reading it again would cost another request)
+                    uint64_t m = a[r].x <= t[r] ? a[r].x : 0u;
+                    m = a[r].y <= t[r] ? a[r].y : m;
+                    m = b[r].x <= t[r] ? b[r].x : m;
+                    m = b[r].y <= t[r] ? b[r].y : m;
+                    uint64_t o = quad_swap<1>(m);
+                    m = o > m ? o : m;
+                    o = quad_swap<2>(m);
+                    before[r] = o > m ? o : m;
+                }
+            }
+        }
+        // the groups' weights, four to a lane
+        Row4 v[4];
+        bool inside = true;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) inside = inside && g[r] < whole;
+        if (__all(inside)) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                v[r] = *(GlobalPtr<const Row4>)(w + ((Off)g[r] * (4u * kFan) + part * 16u));
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) {
+                    const uint64_t j = (uint64_t)g[r] * kFan + part * 4u + e;
+                    v[r][e] = j < J.n ? *(GlobalPtr<const float>)(w + 4u * j) : 0.0f;
+                }
+        }
+        uint32_t anc = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint64_t p0 = fixed_weight(v[r][0], scale), p1 = p0 + fixed_weight(v[r][1], scale),
+                           p2 = p1 + fixed_weight(v[r][2], scale), p3 = p2 + fixed_weight(v[r][3], scale);
+            // the sum before the lane's four
+            const uint64_t one = quad_swap<1>(p3);
+            const uint64_t two = quad_swap<2>(p3 + one);
+            const uint64_t base = before[r] + ((part & 1u) ? one : 0u) + ((part & 2u) ? two : 0u);
+            uint32_t c = (base + p0 <= t[r] ? 1u : 0u) + (base + p1 <= t[r] ? 1u : 0u) +
+                         (base + p2 <= t[r] ? 1u : 0u) + (base + p3 <= t[r] ? 1u : 0u);
+            c += quad_swap<1>(c);
+            c += quad_swap<2>(c);
+            // output l's ancestor is that of r = l / 16 from the quad l mod 16
+            const uint32_t x = (uint32_t)__shfl((int)(g[r] * kFan + c), (int)((lane % 16u) * 4u), 64);
+            if (lane / 16u == (uint32_t)r) anc = x;
+        }
+        if (i < J.n) emit(J, i, (int32_t)anc);
+    }
+}
+
+// Systematic: kSysOut outputs per block. Their thresholds rise with i, so their
+// ancestors lie between those of the first and the last of them, whose groups
+// the block finds together (one count over the top level, one 16-entry row per
+// level below). It then adds up the weights from the one to the other in tiles
+// of 2048 through LDS and bisects there: N outputs come from N inputs, so 1792
+// outputs take one tile unless their weights are very uneven, and every weight
+// is read about once. When the weights between them are more than kSysTiles
+// tiles (long runs of very small weights), each lane descends by itself
+// (OwnScan: never more than 16 tiles, which it adds up).
+constexpr uint32_t kSysPer = 7;
+constexpr uint32_t kSysOut = kSysPer * kPrefixThreads;
+constexpr uint32_t kSysTiles = 8;
+
+// Left to itself the compiler interleaves the seven bisections into 132
+// registers (3 waves per SIMD); asked for 6 waves it takes 80: a whole call at
+// 10^7 inputs 78 instead of 94 us.
+template <bool OwnScan>
+__global__ __launch_bounds__(kPrefixThreads) __attribute__((amdgpu_waves_per_eu(6)))
+void k_prefix_systematic(PrefixJob J)
+{
+    __shared__ __align__(16) uint64_t stage[kChunk];
+    __shared__ uint32_t s_cnt[kPrefixThreads / 64];
+    __shared__ uint32_t s_g[2];
+    const uint32_t first = blockIdx.x * kSysOut;
+    PrefixHeader h;
+    if constexpr (OwnScan)
+        h = scan_in_lds(J, stage);
+    else
+        h = *at<PrefixHeader>(J, J.o_hdr);
+    if (!h.valid) {
+        for (uint32_t e = 0; e < kSysPer; ++e) {
+            const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
+            if (i < J.n) emit(J, i, -1);
+        }
+        return;
+    }
+    const SystematicDraw draw(J, h.total);
+    const uint32_t last = J.n - first > kSysOut ? first + kSysOut - 1u : J.n - 1u;
+    const uint64_t t_end[2] = {draw.threshold(first), draw.threshold(last)};
+    // the top level: how many entries are <= either threshold
+    const uint64_t* lv = at<uint64_t>(J, J.o_level[J.top]);
+    uint32_t c0 = 0, c1 = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < kTopMax / kPrefixThreads; ++e) {
+        const uint32_t k = e * kPrefixThreads + threadIdx.x;
+        const uint64_t v = k < J.count[J.top] ? (OwnScan ? stage[k] : lv[k]) : ~(uint64_t)0;
+        c0 += v <= t_end[0] ? 1u : 0u;
+        c1 += v <= t_end[1] ? 1u : 0u;
+    }
+    c0 |= c1 << 16;  // at most 2048 each
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c0 += (uint32_t)__shfl_xor((int)c0, off, 64);
+    if ((threadIdx.x & 63u) == 0) s_cnt[threadIdx.x >> 6] = c0;
+    __syncthreads();
+    if (threadIdx.x < 64u) {
+        // lanes 0-15 follow the first threshold, 16-31 the last
+        const uint32_t which = (threadIdx.x >> 4) & 1u, m = threadIdx.x & 15u;
+        uint32_t both = 0;
+        for (uint32_t k = 0; k < kPrefixThreads / 64u; ++k) both += s_cnt[k];
+        uint32_t g = (which ? both >> 16 : both & 0xFFFFu) - 1u;
+        for (int k = J.top - 1; k >= 1; --k) {
+            const uint64_t v = at<uint64_t>(J, J.o_level[k])[(uint64_t)g * kFan + m];
+            const uint64_t mask = __ballot(v <= (which ? t_end[1] : t_end[0]));
+            g = g * kFan + (uint32_t)__popcll((mask >> (which * 16u)) & 0xFFFFu) - 1u;
+        }
+        if (m == 0 && threadIdx.x < 32u) s_g[which] = g;
+    }
+    __syncthreads();
+    const uint32_t g_lo = s_g[0], g_hi = s_g[1];
+    uint64_t base = OwnScan ? stage[g_lo] : at<uint64_t>(J, J.o_level[1])[g_lo];
+    const uint64_t lo = (uint64_t)g_lo * kFan, end = ((uint64_t)g_hi + 1u) * kFan;
+    const double scale = ldexp(1.0, h.K - 32);
+    if (!OwnScan && end - lo > (uint64_t)kSysTiles * kChunk) {  // the same for every lane of the block
+#pragma unroll 1
+        for (uint32_t e = 0; e < kSysPer; ++e) {
+            const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
+            if (i < J.n) emit(J, i, (int32_t)descend(J, scale, draw.threshold(i)));
+        }
+        return;
+    }
+    uint64_t t[kSysPer];
+    int32_t a[kSysPer];
+#pragma unroll
+    for (uint32_t e = 0; e < kSysPer; ++e) {
+        const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
+        t[e] = draw.threshold(i < J.n ? i : J.n - 1u);
+        a[e] = -1;
+    }
+    if (OwnScan) __syncthreads();  // base is read before the stage is overwritten
+    for (uint64_t tile = lo; tile < end; tile += kChunk) {
+        uint64_t q[kPrefixPer];
+        load_fixed_tile(J, tile, scale, q);
+#pragma unroll
+        for (uint32_t e = 1; e < kPrefixPer; ++e) q[e] += q[e - 1u];
+        uint64_t total = 0;
+        const uint64_t run = base + block_exclusive_scan(q[kPrefixPer - 1u], &total);
+#pragma unroll
+        for (uint32_t e = 0; e < kPrefixPer; e += 2u)
+            *reinterpret_cast<U64x2*>(stage + threadIdx.x * kPrefixPer + e) = U64x2{run + q[e], run + q[e + 1u]};
+        __syncthreads();
+        // the thresholds of this tile are those below its last sum that no
+        // earlier tile took; all are bisected together, the others for nothing
+        uint32_t at_[kSysPer];
+#pragma unroll
+        for (uint32_t e = 0; e < kSysPer; ++e) at_[e] = 0u;
+        for (uint32_t step = kChunk / 2u; step > 0; step >>= 1) {
+#pragma unroll
+            for (uint32_t e = 0; e < kSysPer; ++e) at_[e] += stage[at_[e] + step - 1u] <= t[e] ? step : 0u;
+        }
+#pragma unroll
+        for (uint32_t e = 0; e < kSysPer; ++e)
+            if (a[e] < 0 && t[e] < base + total) a[e] = (int32_t)(tile + at_[e]);
+        base += total;
+        __syncthreads();  // the stage is overwritten next
+    }
+    // through LDS, so that the copy of a row is in the code once and not for
+    // each output in registers of its own
+    int32_t* out = reinterpret_cast<int32_t*>(stage);
+#pragma unroll
+    for (uint32_t e = 0; e < kSysPer; ++e) out[e * kPrefixThreads + threadIdx.x] = a[e];
+#pragma unroll 1
+    for (uint32_t e = 0; e < kSysPer; ++e) {
+        const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
+        if (i < J.n) emit(J, i, out[e * kPrefixThreads + threadIdx.x]);
     }
 }
 
 static uint64_t align256(uint64_t b) { return (b + 255u) & ~(uint64_t)255u; }
 
-// The layout of one run's scan region: [header][chunk sums][chunk exclusive
-// sums][brackets][tree levels 1..top][level 0: the inclusive sums, whole
-// chunks]. Returns the region's size.
+// The layout of one run's scan region: [header][chunk sums][tree levels
+// 1..top]. Returns the region's size.
 uint64_t prefix_region(uint32_t n, PrefixJob* J)
 {
     const uint64_t nch = ((uint64_t)n + kChunk - 1u) / kChunk;
@@ -430,22 +618,18 @@ uint64_t prefix_region(uint32_t n, PrefixJob* J)
     o += 256u;
     J->o_sum = o;
     o += align256(nch * 8u);
-    J->o_excl = o;
-    o += align256(nch * 8u);
-    J->o_bracket = o;
-    o += align256(((uint64_t)n / kPrefixThreads + 2u) * 4u);
-    // level k has ceil(n / 16^k) real entries; the top is the first with <= 16
+    // level k has ceil(n / 16^k) entries; the top is the first with <= kTopMax
     uint64_t cnt = n;
     J->top = 0;
-    while (cnt > kFan) {
+    do {
         cnt = (cnt + kFan - 1u) / kFan;
         ++J->top;
         J->count[J->top] = (uint32_t)cnt;
         J->o_level[J->top] = o;
         o += align256((cnt + kFan - 1u) / kFan * kFan * 8u);
-    }
-    J->o_incl = o;
-    o += align256(nch * kChunk * 8u);
+    } while (cnt > kTopMax);
+    J->top_span = 1u;
+    while (J->top_span < cnt) J->top_span *= 2u;
     J->n = n;
     J->nch = (uint32_t)nch;
     int L = 0;
@@ -454,22 +638,35 @@ uint64_t prefix_region(uint32_t n, PrefixJob* J)
     return o;
 }
 
-// Enqueues the scan and search of a job whose stats (validation, max) are
-// already on the device: R runs, method MGP_MULTINOMIAL or MGP_SYSTEMATIC.
 int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s)
 {
-    const dim3 chunks(J.nch, R);
-    hipLaunchKernelGGL(k_prefix_chunks, chunks, dim3(kPrefixThreads), 0, s, J);
-    hipLaunchKernelGGL(k_prefix_top, dim3(1, R), dim3(kPrefixThreads), 0, s, J);
-    hipLaunchKernelGGL(k_prefix_scan, chunks, dim3(kPrefixThreads), 0, s, J);
+    const dim3 bt(kPrefixThreads);
+    if (J.parts)
+        hipLaunchKernelGGL(k_prefix_groups<true>, dim3(J.nch, R), bt, 0, s, J);
+    else
+        hipLaunchKernelGGL(k_prefix_groups<false>, dim3(J.nch, R), bt, 0, s, J);
+    const bool own_scan = J.top == 1;
+    if (!own_scan)
+        hipLaunchKernelGGL(k_prefix_scan, dim3((J.count[1] + kScanGroups - 1u) / kScanGroups, R), bt, 0, s, J);
     int err = check_launch("prefix-sum kernels");
     if (err) return err;
-    const uint32_t nb = (J.n + kPrefixThreads - 1u) / kPrefixThreads;  // groups of outputs
     if (method == MGP_MULTINOMIAL) {
-        hipLaunchKernelGGL(k_prefix_multinomial, dim3(nb, R), dim3(kPrefixThreads), 0, s, J);
+        // four passes per block read the top level once for 1024 outputs, where that leaves enough blocks
+        const uint32_t passes = (uint64_t)J.n * R >= (1u << 19) ? 4u : 1u;
+        const uint32_t per = kPrefixThreads * passes;
+        const dim3 grid((J.n + per - 1u) / per, R);
+        if (own_scan)
+            hipLaunchKernelGGL((k_prefix_multinomial<true, true>), grid, bt, 0, s, J, passes);
+        else if (J.n <= (1u << 30))
+            hipLaunchKernelGGL((k_prefix_multinomial<true, false>), grid, bt, 0, s, J, passes);
+        else
+            hipLaunchKernelGGL((k_prefix_multinomial<false, false>), grid, bt, 0, s, J, passes);
     } else {
-        hipLaunchKernelGGL(k_prefix_brackets, dim3(nb / kPrefixThreads + 1u, R), dim3(kPrefixThreads), 0, s, J, nb);
-        hipLaunchKernelGGL(k_prefix_systematic, dim3(nb, R), dim3(kPrefixThreads), 0, s, J);
+        const dim3 grid((J.n + kSysOut - 1u) / kSysOut, R);
+        if (own_scan)
+            hipLaunchKernelGGL(k_prefix_systematic<true>, grid, bt, 0, s, J);
+        else
+            hipLaunchKernelGGL(k_prefix_systematic<false>, grid, bt, 0, s, J);
     }
     return check_launch("prefix-sum search kernel");
 }
@@ -477,6 +674,10 @@ int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s)
 }  // namespace mgp
 
 using namespace mgp;
+
+// Up to this size the finalize step runs in every block of k_prefix_groups;
+// beyond, its 1024 to 4096 partials per block cost more than its own launch.
+constexpr uint32_t kPrefixFinMaxN = 1u << 21;
 
 extern "C" {
 
@@ -517,10 +718,17 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     p.stream_id = stream_id;
     p.partition_bytes = 128;
     p.b_max = 1;
-    const int err = enqueue_reduce_finalize(w_dev, un, p, false, kLayoutInPlace, ws, stats_dev, s);
-    if (err) return err;
+    J.stats = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
+    if (un <= kPrefixFinMaxN) {
+        J.parts = reinterpret_cast<const Partial*>(ws + kWsPartialsOffset);
+        J.st_user = stats_dev;
+        const int err = enqueue_partials(w_dev, un, p, ws, &J.nparts, &J.fin, s);
+        if (err) return err;
+    } else {
+        const int err = enqueue_reduce_finalize(w_dev, un, p, false, kLayoutInPlace, ws, stats_dev, s);
+        if (err) return err;
+    }
     J.w = w_dev;
-    J.stats = reinterpret_cast<const mgp_stats*>(ws + kWsStatsOffset);
     J.region = ws + workspace_bytes(1u);
     J.anc = ancestors_dev;
     J.vec = ((uintptr_t)w_dev & 15u) == 0 ? 1u : 0u;
