@@ -90,6 +90,13 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_finalize(const FilterD
     if (blockIdx.x == 0 && threadIdx.x < nq) queues[threadIdx.x] = 0;
 }
 
+// Megopolis steps per round of loads: one and two particles per thread are the
+// shapes of batches too small to fill the chip, where round trips count
+// (105 filters of 2300 to 5000 particles: 37.3 us with rounds of 5, 36.6 with
+// 10, 36.3 with 20 at one particle; 44.3 against 44.2 at two).
+template <int P>
+constexpr int kBatchRound = P == 1 ? 20 : P == 2 ? 10 : 5;
+
 // One tile: the chains of the block's BT * P particles from `start` on, then
 // the ancestors and the particle copy x_bar_i = x_{k_i}.
 template <int V, int BT, int P>
@@ -111,7 +118,7 @@ __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats
     if (st->status == MGP_OK) {
         if constexpr (V == kMegopolis) {
             uint32_t kc[P];
-            megopolis_chain<P, BT, 5>(F.windows, offset_ptr(F.offsets), n, B, F.key0, F.key1, F.stream_id, start, kc);
+            megopolis_chain<P, BT, kBatchRound<P>>(F.windows, offset_ptr(F.offsets), n, B, F.key0, F.key1, F.stream_id, start, kc);
 #pragma unroll
             for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
         } else {
