@@ -227,37 +227,37 @@ def mgp_last_error() -> str:
 
 def mgp_workspace_size(n: int, params: mgp_params) -> int:
     out = ctypes.c_size_t()
-    _check(lib().mgp_workspace_size(n, ctypes.byref(params), ctypes.byref(out)), "mgp_workspace_size")
+    _check(lib().mgp_workspace_size(n, params, ctypes.byref(out)), "mgp_workspace_size")
     return out.value
 
 
 def mgp_resample(w_dev: int, n: int, params: mgp_params, ancestors_dev: int, stats_dev: int, workspace_dev: int,
                  workspace_bytes: int, stream: int) -> None:
-    _check(lib().mgp_resample(w_dev, n, ctypes.byref(params), ancestors_dev, stats_dev or None, workspace_dev,
+    _check(lib().mgp_resample(w_dev, n, params, ancestors_dev, stats_dev or None, workspace_dev,
                               workspace_bytes, stream or None), "mgp_resample")
 
 
 def mgp_resample_noalloc(w_dev: int, n: int, params: mgp_params, ancestors_dev: int, stats_dev: int,
                          stream: int) -> None:
-    _check(lib().mgp_resample_noalloc(w_dev, n, ctypes.byref(params), ancestors_dev, stats_dev or None,
+    _check(lib().mgp_resample_noalloc(w_dev, n, params, ancestors_dev, stats_dev or None,
                                       stream or None), "mgp_resample_noalloc")
 
 
 def mgp_resample_m(w_dev: int, n: int, m: int, params: mgp_params, ancestors_dev: int, stats_dev: int,
                    workspace_dev: int, workspace_bytes: int, stream: int) -> None:
-    _check(lib().mgp_resample_m(w_dev, n, m, ctypes.byref(params), ancestors_dev, stats_dev or None, workspace_dev,
+    _check(lib().mgp_resample_m(w_dev, n, m, params, ancestors_dev, stats_dev or None, workspace_dev,
                                 workspace_bytes, stream or None), "mgp_resample_m")
 
 
 def mgp_compute_B(w_dev: int, n: int, params: mgp_params, stats_dev: int, workspace_dev: int,
                   workspace_bytes: int, stream: int) -> None:
-    _check(lib().mgp_compute_B(w_dev, n, ctypes.byref(params), stats_dev or None, workspace_dev, workspace_bytes,
+    _check(lib().mgp_compute_B(w_dev, n, params, stats_dev or None, workspace_dev, workspace_bytes,
                                stream or None), "mgp_compute_B")
 
 
 def mgp_resample_prepared(w_dev: int, n: int, params: mgp_params, ancestors_dev: int, workspace_dev: int,
                           workspace_bytes: int, stream: int) -> None:
-    _check(lib().mgp_resample_prepared(w_dev, n, ctypes.byref(params), ancestors_dev, workspace_dev,
+    _check(lib().mgp_resample_prepared(w_dev, n, params, ancestors_dev, workspace_dev,
                                        workspace_bytes, stream or None), "mgp_resample_prepared")
 
 
@@ -268,7 +268,7 @@ def mgp_gather(states_dev: int, n_states: int, d: int, ancestors_dev: int, n_out
 
 def mgp_resample_gather(w_dev: int, n: int, params: mgp_params, states_dev: int, d: int, ancestors_dev: int,
                         out_dev: int, stats_dev: int, workspace_dev: int, workspace_bytes: int, stream: int) -> None:
-    _check(lib().mgp_resample_gather(w_dev, n, ctypes.byref(params), states_dev, d, ancestors_dev or None, out_dev,
+    _check(lib().mgp_resample_gather(w_dev, n, params, states_dev, d, ancestors_dev or None, out_dev,
                                      stats_dev or None, workspace_dev, workspace_bytes, stream or None),
            "mgp_resample_gather")
 
@@ -276,7 +276,7 @@ def mgp_resample_gather(w_dev: int, n: int, params: mgp_params, states_dev: int,
 def mgp_resample_gather_prepared(w_dev: int, n: int, params: mgp_params, states_dev: int, d: int,
                                  ancestors_dev: int, out_dev: int, workspace_dev: int, workspace_bytes: int,
                                  stream: int) -> None:
-    _check(lib().mgp_resample_gather_prepared(w_dev, n, ctypes.byref(params), states_dev, d, ancestors_dev or None,
+    _check(lib().mgp_resample_gather_prepared(w_dev, n, params, states_dev, d, ancestors_dev or None,
                                               out_dev, workspace_dev, workspace_bytes, stream or None),
            "mgp_resample_gather_prepared")
 
@@ -447,13 +447,23 @@ def mgp_probe_pattern_read(mirror_dev: int, mirror_bytes: int, n: int, offsets_d
 # torch helpers
 # ---------------------------------------------------------------------------
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def current_stream() -> int:
-    return _torch().cuda.current_stream().cuda_stream
+    """The current stream of the current device as a raw handle. The handle
+    itself is asked for: building torch's Stream object takes 1.5 us more, a
+    tenth of what a whole call of a small filter takes."""
+    torch = _torch()
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def decode_stats(stats_tensor) -> dict:
@@ -497,7 +507,8 @@ class Resampler:
         n = w.numel()
         if out is None:
             out = torch.empty(n, dtype=torch.int32, device=w.device)
-        _require_buffer(out, n, torch.int32, "out (ancestors)", w.device)
+        else:
+            _require_buffer(out, n, torch.int32, "out (ancestors)", w.device)
         p = make_params(variant, B, epsilon, seed, stream_id, partition_bytes, self.b_max, segment)
         mgp_resample(w.data_ptr(), n, p, out.data_ptr(), self.stats.data_ptr(), self.workspace.data_ptr(),
                      self.ws_bytes, current_stream() if stream is None else stream)
@@ -511,7 +522,8 @@ class Resampler:
         torch = _torch()
         if out is None:
             out = torch.empty(int(m), dtype=torch.int32, device=w.device)
-        _require_buffer(out, int(m), torch.int32, "out (ancestors)", w.device)
+        else:
+            _require_buffer(out, int(m), torch.int32, "out (ancestors)", w.device)
         p = make_params(variant, B, epsilon, seed, stream_id, partition_bytes, self.b_max, segment)
         mgp_resample_m(w.data_ptr(), w.numel(), int(m), p, out.data_ptr(), self.stats.data_ptr(),
                        self.workspace.data_ptr(), self.ws_bytes, current_stream() if stream is None else stream)
@@ -535,7 +547,8 @@ class Resampler:
         n = w.numel()
         if out is None:
             out = torch.empty(n, dtype=torch.int32, device=w.device)
-        _require_buffer(out, n, torch.int32, "out (ancestors)", w.device)
+        else:
+            _require_buffer(out, n, torch.int32, "out (ancestors)", w.device)
         p = make_params(variant, B, epsilon, seed, stream_id, partition_bytes, self.b_max, segment)
         mgp_resample_prepared(w.data_ptr(), n, p, out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
                               current_stream() if stream is None else stream)
@@ -547,16 +560,18 @@ class Resampler:
         n = w.numel()
         if states.dtype != torch.float32 or not states.is_cuda or not states.is_contiguous() or states.dim() < 1:
             raise ValueError("states must be a contiguous fp32 device tensor [n, d]")
-        st2 = states.view(states.shape[0], -1)
+        st2 = states if states.dim() == 2 else states.view(states.shape[0], -1)
         if st2.shape[0] != n or st2.device != w.device:
             raise ValueError(f"states must hold {n} rows on {w.device}")
         d = st2.shape[1]
         if out is None:
             out = torch.empty((n, d), dtype=torch.float32, device=w.device)
-        _require_buffer(out, n * d, torch.float32, "out (x_bar)", w.device)
-        if anc is None and with_anc:
-            anc = torch.empty(n, dtype=torch.int32, device=w.device)
-        if anc is not None:
+        else:
+            _require_buffer(out, n * d, torch.float32, "out (x_bar)", w.device)
+        if anc is None:
+            if with_anc:
+                anc = torch.empty(n, dtype=torch.int32, device=w.device)
+        else:
             _require_buffer(anc, n, torch.int32, "anc (ancestors)", w.device)
         return st2, d, out, anc
 
@@ -614,7 +629,8 @@ class PrefixResampler:
         n = w.numel()
         if out is None:
             out = torch.empty(n, dtype=torch.int32, device=w.device)
-        _require_buffer(out, n, torch.int32, "out (ancestors)", w.device)
+        else:
+            _require_buffer(out, n, torch.int32, "out (ancestors)", w.device)
         m = PREFIX_METHODS[method] if isinstance(method, str) else int(method)
         mgp_resample_prefix(w.data_ptr(), n, m, seed, stream_id, out.data_ptr(), self.stats.data_ptr(),
                             self.workspace.data_ptr(), self.ws_bytes, current_stream() if stream is None else stream)
@@ -639,14 +655,15 @@ def gather(states, anc, out=None, stream: int | None = None):
         raise ValueError("states must be a contiguous fp32 device tensor [n_states, d]")
     if anc.dtype != torch.int32 or not anc.is_cuda or not anc.is_contiguous():
         raise ValueError("ancestors must be a contiguous int32 device tensor")
-    st2 = states.view(states.shape[0], -1)
+    st2 = states if states.dim() == 2 else states.view(states.shape[0], -1)
     n_states, d = st2.shape
     n_out = anc.numel()
     if anc.device != states.device:
         raise ValueError("ancestors and states must be on the same device")
     if out is None:
         out = torch.empty((n_out, d), dtype=torch.float32, device=states.device)
-    _require_buffer(out, n_out * d, torch.float32, "out (gathered states)", states.device)
+    else:
+        _require_buffer(out, n_out * d, torch.float32, "out (gathered states)", states.device)
     mgp_gather(st2.data_ptr(), n_states, d, anc.data_ptr(), n_out, out.data_ptr(),
                current_stream() if stream is None else stream)
     return out
