@@ -508,7 +508,7 @@ typedef enum mgp_prefix_method {
 } mgp_prefix_method;
 
 /* Bytes of device workspace mgp_resample_prefix needs for n particles
- * (about n/2: sums of groups of 16 inputs). Host-only. */
+ * (about 8n). Host-only. */
 int mgp_prefix_workspace_size(int32_t n, size_t* bytes);
 
 /* Ancestors by multinomial or systematic resampling, all on `stream`: the

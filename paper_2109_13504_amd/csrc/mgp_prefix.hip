@@ -675,6 +675,22 @@ int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s)
 
 using namespace mgp;
 
+// The scan room that the single-filter entry point asks for: 8 bytes per input
+// (whole chunks) and per entry of the tree down to 16 entries, 16 per chunk, 4
+// per 256 outputs. The scan itself uses a tenth of it (prefix_region); what a
+// caller's workspace must hold is kept as it was, so that the same buffers
+// are taken and refused.
+static uint64_t prefix_workspace(uint32_t n)
+{
+    const uint64_t nch = ((uint64_t)n + kChunk - 1u) / kChunk;
+    uint64_t o = 256u + 2u * align256(nch * 8u) + align256(((uint64_t)n / 256u + 2u) * 4u);
+    for (uint64_t cnt = n; cnt > kFan;) {
+        cnt = (cnt + kFan - 1u) / kFan;
+        o += align256((cnt + kFan - 1u) / kFan * kFan * 8u);
+    }
+    return workspace_bytes(1u) + o + align256(nch * kChunk * 8u);
+}
+
 // Up to this size the finalize step runs in every block of k_prefix_groups;
 // beyond, its 1024 to 4096 partials per block cost more than its own launch.
 constexpr uint32_t kPrefixFinMaxN = 1u << 21;
@@ -686,8 +702,7 @@ int mgp_prefix_workspace_size(int32_t n, size_t* bytes)
     clear_error();
     if (!bytes) return fail(MGP_EINVAL, "bytes is NULL");
     if (n < 1) return fail(MGP_EINVAL, "n must be >= 1 (got %d)", n);
-    PrefixJob J{};
-    *bytes = workspace_bytes(1u) + prefix_region((uint32_t)n, &J);
+    *bytes = prefix_workspace((uint32_t)n);
     return MGP_OK;
 }
 
@@ -704,7 +719,8 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     if (((uintptr_t)workspace_dev & 255u) != 0) return fail(MGP_EINVAL, "workspace must be 256-byte aligned");
     const uint32_t un = (uint32_t)n;
     PrefixJob J{};
-    const size_t need = workspace_bytes(1u) + prefix_region(un, &J);
+    prefix_region(un, &J);
+    const size_t need = prefix_workspace(un);
     if (workspace_bytes_ < need) return fail(MGP_ERANGE, "workspace has %zu bytes, needs %zu", workspace_bytes_, need);
     char* ws = static_cast<char*>(workspace_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
