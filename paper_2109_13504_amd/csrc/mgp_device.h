@@ -130,15 +130,6 @@ __device__ __forceinline__ uint32_t megopolis_index(uint32_t i_aligned, uint32_t
     return jm < j ? jm : j;
 }
 
-// C1/C2 candidate inside partition p of n_w weights (the last one cut at n).
-__device__ __forceinline__ uint32_t partition_index(uint32_t p, uint32_t jword, uint32_t n, uint32_t n_w)
-{
-    const uint32_t start = p * n_w;
-    const uint32_t rest = n - start;
-    const uint32_t width = rest < n_w ? rest : n_w;
-    return start + uniform_index(jword, width);
-}
-
 // Pointers read from a record in memory (a batch's filters) carry no address
 // space, and the compiler then uses FLAT accesses, 64-bit vector addresses
 // and, for the wave-uniform offsets, one vector load per lane. These types
@@ -165,23 +156,31 @@ __device__ __forceinline__ T* in_hbm(T* p)
 
 __device__ __forceinline__ OffsetPtr offset_ptr(const uint32_t* p) { return (OffsetPtr)(uintptr_t)p; }
 
-// Loads w[j]. With `Narrow` the byte offset fits 32 bits (n <= 2^30), which
-// lets the compiler use the scalar-base + 32-bit vector-offset form.
+// A position in the weights: its byte offset where that fits 32 bits (Narrow,
+// n <= 2^30: the scalar-base + 32-bit vector-offset form of a load, with no
+// shift left to do), else its index.
 template <bool Narrow>
-__device__ __forceinline__ float load_weight(GlobalPtr<const float> w, uint32_t j)
+__device__ __forceinline__ uint32_t position(uint32_t j)
+{
+    return Narrow ? j << 2 : j;
+}
+
+template <bool Narrow>
+__device__ __forceinline__ float load_weight(GlobalPtr<const float> w, uint32_t at)
 {
     if constexpr (Narrow) {
-        return *(GlobalPtr<const float>)((GlobalPtr<const char>)w + (j << 2));
+        return *(GlobalPtr<const float>)((GlobalPtr<const char>)w + at);
     } else {
-        return w[(size_t)j];
+        return w[(size_t)at];
     }
 }
 
 // The same from weights kept in LDS.
 template <bool Narrow>
-__device__ __forceinline__ float load_weight(const float* w, uint32_t j)
+__device__ __forceinline__ float load_weight(const float* w, uint32_t at)
 {
-    return w[j];
+    static_assert(Narrow, "weights in LDS are few");
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(w) + at);
 }
 
 // Per-call parameters of the accept loop (all wave-uniform). Weights is
@@ -217,7 +216,7 @@ struct Unroll {
 
 // What a chain carries from block to block, and what is fixed for it.
 struct ChainState {
-    uint32_t k;  // current ancestor
+    uint32_t k;  // current ancestor's position
     float wk;    // its weight
 };
 
@@ -226,7 +225,7 @@ struct ChainFixed {
     uint32_t group;      // i / 32
     uint32_t i_aligned;  // Megopolis: segment base of the start position
     uint32_t i_low;      // Megopolis: place of the start position in its segment
-    uint32_t c1_part;    // C1: the group's partition
+    uint32_t c1_first;   // C1: the first weight of the group's partition
 };
 
 // The particle index as an opaque value: an empty volatile asm statement
@@ -246,28 +245,34 @@ __device__ __forceinline__ uint32_t pinned(uint32_t x)
 // block's loads are in flight together; then the serial accept steps.
 // Partial skips the steps past cnt (cnt is wave-uniform), including their
 // generator calls and loads.
-template <int V, bool Narrow, bool Shared, bool Partial, typename W>
+// Even (C1, C2): n is a multiple of the partition size, so that every
+// partition has the same width.
+template <int V, bool Narrow, bool Shared, bool Even, bool Partial, typename W>
 __device__ __forceinline__ void chain_block(const LoopParams<W>& P, const ChainFixed& F, uint32_t q, uint32_t cnt,
                                             ChainState& c)
 {
     constexpr uint32_t U = Unroll<V>::value;
     constexpr bool kShare = Shared && V == kC2;
     UBlock ub;
-    Words jb{}, pb{}, pmine{};
+    Words jb{}, pb{};
+    uint32_t mine[4];  // kShare: the first weights of the partitions this lane drew
     uint32_t jj[U];
     float wj[U];
     if constexpr (kShare) {
-        // lane k (< U / 4) of the half-wave: the call of block q U / 4 + k
+        // lane k (< U / 4) of the half-wave: the call of block q U / 4 + k,
+        // and the partitions of its four words, once for all 32 particles
         const uint32_t k = __lane_id() & 31u;
-        pmine = philox(q * (U / 4) + (k < U / 4 ? k : 0u), kTagC2Part, P.stream_id, F.group, P.key0, P.key1);
+        const Words x = philox(q * (U / 4) + (k < U / 4 ? k : 0u), kTagC2Part, P.stream_id, F.group, P.key0, P.key1);
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) mine[r] = uniform_index(word(x, r), P.n_part) * P.n_w;
     }
 #pragma unroll
     for (uint32_t s = 0; s < U; ++s) {
         if (Partial && s >= cnt) continue;
         const uint32_t b = q * U + s;
-        uint32_t j;
+        uint32_t at;
         if constexpr (V == kMegopolis) {
-            j = megopolis_index(F.i_aligned, F.i_low, offset_at(P, b), P.n, P.seg_mask);
+            at = position<Narrow>(megopolis_index(F.i_aligned, F.i_low, offset_at(P, b), P.n, P.seg_mask));
         } else {
             if (s % 4 == 0) {
                 const uint32_t blk = q * (U / 4) + s / 4;
@@ -280,20 +285,22 @@ __device__ __forceinline__ void chain_block(const LoopParams<W>& P, const ChainF
             }
             const uint32_t jw = word(jb, s % 4);
             if constexpr (V == kMetropolis) {
-                j = uniform_index(jw, P.n);
-            } else if constexpr (V == kC1) {
-                j = partition_index(F.c1_part, jw, P.n, P.n_w);
+                at = position<Narrow>(uniform_index(jw, P.n));
             } else {
-                uint32_t pw;
-                if constexpr (kShare)
-                    pw = (uint32_t)__shfl((int)word(pmine, s % 4), (int)((__lane_id() & 32u) + s / 4), 64);
+                uint32_t first;
+                if constexpr (V == kC1)
+                    first = F.c1_first;
+                else if constexpr (kShare)
+                    first = (uint32_t)__shfl((int)mine[s % 4], (int)((__lane_id() & 32u) + s / 4), 64);
                 else
-                    pw = word(pb, s % 4);
-                j = partition_index(uniform_index(pw, P.n_part), jw, P.n, P.n_w);
+                    first = uniform_index(word(pb, s % 4), P.n_part) * P.n_w;
+                const uint32_t rest = P.n - first;  // the last partition is cut at n
+                const uint32_t width = Even || rest >= P.n_w ? P.n_w : rest;
+                at = position<Narrow>(first + uniform_index(jw, width));
             }
         }
-        jj[s] = j;
-        wj[s] = load_weight<Narrow>(P.w, j);
+        jj[s] = at;
+        wj[s] = load_weight<Narrow>(P.w, at);
     }
 #pragma unroll
     for (uint32_t s = 0; s < U; ++s) {
@@ -321,6 +328,16 @@ __device__ __forceinline__ void chain_block(const LoopParams<W>& P, const ChainF
 // once per four steps, lane k of the half-wave makes the call of the k-th
 // four-step block of the block's twenty steps and the others read its words
 // with a cross-lane permute: one call per lane per twenty steps.
+template <int V, bool Narrow, bool Shared, bool Even, typename W>
+__device__ __forceinline__ void run_blocks(const LoopParams<W>& P, const ChainFixed& F, ChainState& c)
+{
+    constexpr uint32_t U = Unroll<V>::value;
+    const uint32_t nblk = P.B / U;
+    for (uint32_t q = 0; q < nblk; ++q) chain_block<V, Narrow, Shared, Even, false>(P, F, q, U, c);
+    const uint32_t rest = P.B - nblk * U;
+    if (rest) chain_block<V, Narrow, Shared, Even, true>(P, F, nblk, rest, c);
+}
+
 template <int V, bool Narrow, bool Shared = false, typename W>
 __device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i, uint32_t pos)
 {
@@ -329,18 +346,21 @@ __device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i
     F.group = i / kSegment;
     F.i_aligned = pos & ~P.seg_mask;
     F.i_low = pos & P.seg_mask;
-    F.c1_part = 0;
+    F.c1_first = 0;
     if constexpr (V == kC1) {
         const Words px = philox(0u, kTagC1Part, P.stream_id, F.group, P.key0, P.key1);
-        F.c1_part = uniform_index(px.x0, P.n_part);
+        F.c1_first = uniform_index(px.x0, P.n_part) * P.n_w;
     }
-    ChainState c{pos, load_weight<Narrow>(P.w, pos)};
-    constexpr uint32_t U = Unroll<V>::value;
-    const uint32_t nblk = P.B / U;
-    for (uint32_t q = 0; q < nblk; ++q) chain_block<V, Narrow, Shared, false>(P, F, q, U, c);
-    const uint32_t rest = P.B - nblk * U;
-    if (rest) chain_block<V, Narrow, Shared, true>(P, F, nblk, rest, c);
-    return c.k;
+    ChainState c{position<Narrow>(pos), load_weight<Narrow>(P.w, position<Narrow>(pos))};
+    if constexpr (V == kC1 || V == kC2) {
+        if (P.n_part * P.n_w == P.n)
+            run_blocks<V, Narrow, Shared, true>(P, F, c);
+        else
+            run_blocks<V, Narrow, Shared, false>(P, F, c);
+    } else {
+        run_blocks<V, Narrow, Shared, true>(P, F, c);
+    }
+    return Narrow ? c.k >> 2 : c.k;
 }
 
 template <int V, bool Narrow, bool Shared = false, typename W>
