@@ -108,7 +108,10 @@ __device__ __forceinline__ UBlock u_block(const Words& x)
     r.u[1] = u_from_bits(x.x1 >> 8);
     r.u[2] = u_from_bits(x.x2 >> 8);
     r.u[3] = u_from_bits(x.x3 >> 8);
-    r.u[4] = u_from_bits((x.x0 & 0xFFu) | ((x.x1 & 0xFFu) << 8) | ((x.x2 & 0xFFu) << 16));
+    // the low bytes of x0, x1, x2 (in that order from the bottom) as two byte
+    // permutations; shifts and masks take four instructions
+    const uint32_t low2 = __builtin_amdgcn_perm(x.x1, x.x0, 0x0C0C0400u);
+    r.u[4] = u_from_bits(__builtin_amdgcn_perm(x.x2, low2, 0x0C040100u));
     return r;
 }
 
