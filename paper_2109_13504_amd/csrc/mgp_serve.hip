@@ -130,6 +130,96 @@ struct Slot {
     uint32_t* h_qoff = nullptr;
 };
 
+// One launch copies a finished request's ancestors and states to the caller.
+// Bound by what a launch costs the host, as requests are mostly a few hundred
+// KB: two copies through the runtime took FIGA per request of a burst, this
+// kernel takes FIGB (24 requests of 2^12 to 2^20 particles, 8 floats each).
+// A block moves kCopyChunk bytes of one array, 16 bytes per lane where both
+// sides allow it and 4 otherwise; all its loads are in flight before the first
+// store. Up to kCopyMaxBlocks, which leaves the grid's thread count far below
+// its limit of 2^32, and where the runtime's copy is not worse any more.
+constexpr uint32_t kCopyThreads = 256;
+constexpr uint32_t kCopyChunk = kCopyThreads * 32u;  // bytes
+constexpr uint32_t kCopyMaxBlocks = 1u << 17;        // 1 GiB
+
+struct OutputCopy {
+    const char* src;  // 256-byte aligned (a pool block)
+    void* dst;        // 4-byte aligned
+    uint64_t bytes;   // a multiple of 4
+    uint32_t blocks;
+};
+
+__global__ __launch_bounds__(kCopyThreads) void k_copy_outputs(OutputCopy a, OutputCopy b)
+{
+    const bool first = blockIdx.x < a.blocks;
+    const OutputCopy c = first ? a : b;
+    const uint64_t at = (uint64_t)(first ? blockIdx.x : blockIdx.x - a.blocks) * kCopyChunk;
+    const uint64_t left = c.bytes - at;
+    const uint32_t words = (left < kCopyChunk ? (uint32_t)left : kCopyChunk) / 4u;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(c.src + at);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(static_cast<char*>(c.dst) + at);
+    const bool whole = words * 4u == kCopyChunk;
+    if (whole && ((uintptr_t)c.dst & 15u) == 0) {
+        const uint4* s4 = reinterpret_cast<const uint4*>(src);
+        uint4* d4 = reinterpret_cast<uint4*>(dst);
+        const uint4 x = s4[threadIdx.x], y = s4[threadIdx.x + kCopyThreads];
+        d4[threadIdx.x] = x;
+        d4[threadIdx.x + kCopyThreads] = y;
+        return;
+    }
+    constexpr uint32_t kIt = kCopyChunk / (4u * kCopyThreads);
+    uint32_t v[kIt];
+#pragma unroll
+    for (uint32_t k = 0; k < kIt; ++k) {
+        const uint32_t i = threadIdx.x + k * kCopyThreads;
+        v[k] = src[i < words ? i : 0u];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kIt; ++k) {
+        const uint32_t i = threadIdx.x + k * kCopyThreads;
+        if (i < words) dst[i] = v[k];
+    }
+}
+
+uint32_t copy_blocks(uint64_t bytes) { return (uint32_t)((bytes + kCopyChunk - 1u) / kCopyChunk); }
+
+// Whether `bytes` from p on are words of one ordinary allocation on `device`.
+bool device_words(const void* p, uint64_t bytes, int device)
+{
+    if ((uintptr_t)p & 3u) return false;
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+        (at.type == hipMemoryTypeDevice && hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess)) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (at.type != hipMemoryTypeDevice || at.device != device) return false;
+    const uint64_t off = (uint64_t)((const char*)p - (const char*)base);
+    return off <= size && bytes <= size - off;
+}
+
+// The kernel copies where the runtime would copy within the server's device:
+// both destinations there, inside their allocations, and the stream and the
+// thread on it too. Any other destination (host or managed memory, a peer, a
+// range that the runtime refuses) takes the runtime's copy, as does one beyond
+// kCopyMaxBlocks.
+bool copies_by_kernel(int device, hipStream_t st, const void* anc, uint64_t anc_bytes, const void* out,
+                      uint64_t out_bytes)
+{
+    if (anc_bytes / kCopyChunk >= kCopyMaxBlocks || out_bytes / kCopyChunk >= kCopyMaxBlocks) return false;
+    int current = -1;
+    if (hipGetDevice(&current) != hipSuccess || current != device) return false;
+    hipDevice_t on = device;
+    if (st && hipStreamGetDevice(st, &on) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return on == device && device_words(anc, anc_bytes, device) &&
+           (!out_bytes || device_words(out, out_bytes, device));
+}
+
 }  // namespace
 }  // namespace mgp
 
@@ -672,6 +762,14 @@ int mgp_server_copy_outputs(mgp_server* s, uint64_t ticket, int32_t* anc, float*
     // the outputs stay allocated until release, which the caller orders
     // after this copy
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (!out || !src_out) out_bytes = 0;
+    if (copies_by_kernel(s->device, st, anc, anc_bytes, out, out_bytes)) {
+        const OutputCopy a{src_anc, anc, anc_bytes, copy_blocks(anc_bytes)};
+        const OutputCopy o{src_out, out, out_bytes, copy_blocks(out_bytes)};
+        hipLaunchKernelGGL(k_copy_outputs, dim3(a.blocks + o.blocks), dim3(kCopyThreads), 0, st, a, o);
+        if (hipGetLastError() != hipSuccess) return fail(MGP_EHIP, "copying the outputs failed");
+        return MGP_OK;
+    }
     if (hipMemcpyAsync(anc, src_anc, anc_bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)
         return fail(MGP_EHIP, "copying ancestors failed");
     if (out && src_out && hipMemcpyAsync(out, src_out, out_bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)
