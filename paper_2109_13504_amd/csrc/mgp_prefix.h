@@ -45,6 +45,8 @@ struct PrefixJob {
     uint32_t count[kMaxLevels + 1];    // its entries, padded to a multiple of the fan-out
     uint32_t top_span;                 // count[top] rounded up to a power of two
     int top;                           // the first level of at most kTopMax entries
+    uint32_t nsys;                     // blocks of the systematic search
+    uint64_t o_start;                  // the group each of them starts in, and the last one's end
 };
 
 // Fills the region layout and n, nch, log2n of J for runs of n particles;

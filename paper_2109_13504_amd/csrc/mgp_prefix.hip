@@ -185,10 +185,66 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_groups(PrefixJob J)
     if (threadIdx.x == 0) at<uint64_t>(J, J.o_sum)[blockIdx.x] = total;
 }
 
+// Algorithm 8: u = (i + u_t) / N after one draw u_t ~ U[0, 1) per run, in fp64
+// with each operation rounded once.
+struct SystematicDraw {
+    double ut, c;  // u_t, S / N
+    double c32;    // c / 2^32
+    double inv;    // N / S
+    uint64_t S;
+
+    __device__ __forceinline__ SystematicDraw(const PrefixJob& J, uint64_t total) : S(total)
+    {
+        const Words x = philox(0u, kTagSystematic, J.stream0 + blockIdx.y, 0u, J.key0, J.key1);
+        const uint64_t r = (uint64_t)x.x0 | ((uint64_t)x.x1 << 32);
+        ut = (double)(r >> 11) * 0x1p-53;
+        c = __ddiv_rn((double)S, (double)J.n);
+        c32 = c * 0x1p-32;
+        inv = __ddiv_rn((double)J.n, (double)S);
+    }
+
+    // rises with i
+    __device__ __forceinline__ uint64_t threshold(uint32_t i) const
+    {
+        const uint64_t t = (uint64_t)floor(__dmul_rn(__dadd_rn((double)i, ut), c));
+        return t < S ? t : S - 1u;
+    }
+
+    // The number of outputs whose threshold is below P (0 <= P <= S), so the
+    // first output of the input that starts at P; more than N when P = S.
+    // P N / S - u_t is that crossing to within 2^-18 (each operation, here and in
+    // threshold(), is off by 2^-53 of at most 2^31), so only the output nearest
+    // to it has to be asked: those before are below P, those after are not. Its
+    // threshold is compared as integers, high and low word (c32 scales by a
+    // power of two, which rounds nothing), and those that threshold() holds at
+    // S - 1 are not below P unless P = S.
+    __device__ __forceinline__ uint32_t outputs_below(uint64_t P) const
+    {
+        const double f = fmax(rint(fma((double)P, inv, -ut)), 0.0);
+        const double x = __dmul_rn(__dadd_rn(f, ut), c32);
+        const uint32_t hi = (uint32_t)x;
+        const uint32_t lo = (uint32_t)(__builtin_amdgcn_fract(x) * 0x1p32);
+        const uint64_t t = (uint64_t)lo | ((uint64_t)hi << 32);
+        return (uint32_t)f + (t >= P && P < S ? 0u : 1u);
+    }
+};
+
+// The systematic search: kSysOut outputs per block, of up to kSysTiles tiles of inputs.
+constexpr uint32_t kSysPer = 7;
+constexpr uint32_t kSysOut = kSysPer * kPrefixThreads;
+constexpr uint32_t kSysTiles = 8;
+
 // The exclusive sums of kScanGroups groups, from the chunk sums before them
 // and the groups' own sums, which they replace; the entries of the higher
 // levels among them; and, by the block with the last group, every level's
 // padding (the largest integer, above any threshold) and the header.
+//
+// Sys: also where the blocks of the systematic search start. The thread with
+// the sum before a group has the first output there (outputs_below), so
+// start[b], the group of output b kSysOut, is written by the thread whose group
+// has it: about one in 100 of them, against a search from the top of the tree
+// at the start of every block.
+template <bool Sys>
 __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
 {
     const mgp_stats& st = J.stats[blockIdx.y];
@@ -203,11 +259,20 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
 #pragma unroll
     for (uint32_t e = 0; e < 8u; ++e) v[e] = g0 + e < J.count[1] ? x1[g0 + e] : 0u;
     const uint64_t* chunk_sum = at<uint64_t>(J, J.o_sum);
-    uint64_t before = 0;
+    const uint32_t own = blockIdx.x * kChunksPerScan;  // the first chunk of this block
+    uint64_t before = 0, after = 0;
 #pragma unroll 8
-    for (uint32_t c = threadIdx.x; c < blockIdx.x * kChunksPerScan; c += kPrefixThreads) before += chunk_sum[c];
-    uint64_t base = 0, total = 0;
+    for (uint32_t c = threadIdx.x; c < (Sys ? J.nch : own); c += kPrefixThreads) {
+        const uint64_t x = chunk_sum[c];
+        before += c < own ? x : 0u;
+        after += c < own ? 0u : x;
+    }
+    uint64_t base = 0, total = 0, S = 0;
     block_exclusive_scan(before, &base);
+    if constexpr (Sys) {
+        block_exclusive_scan(after, &S);
+        S += base;
+    }
     uint64_t s = 0;
 #pragma unroll
     for (uint32_t e = 0; e < 8u; ++e) s += v[e];
@@ -224,6 +289,32 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
             }
         }
         run += v[e];
+    }
+    if constexpr (Sys) {
+        const SystematicDraw draw(J, S);
+        uint32_t* start = at<uint32_t>(J, J.o_start);
+        const uint32_t lane = threadIdx.x & 63u;
+        run -= s;
+        uint32_t from = (draw.outputs_below(run) + kSysOut - 1u) / kSysOut;
+#pragma unroll
+        for (uint32_t e = 0; e < 8u; ++e) {
+            // blocks [from, to) start in group g0 + e; the last group with a
+            // weight also ends the last block's range
+            run += v[e];
+            const uint32_t below = draw.outputs_below(run);
+            const bool ends = run == S && v[e] > 0u;
+            const uint32_t to = ends ? J.nsys + 1u : ((below < J.n ? below : J.n) + kSysOut - 1u) / kSysOut;
+            uint64_t mask = __ballot(to > from);
+            while (mask) {
+                const int l = __ffsll((unsigned long long)mask) - 1;
+                mask &= mask - 1u;
+                const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)from, l);
+                const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)to, l);
+                const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)(g0 + e), l);
+                for (uint32_t b = a + lane; b < z; b += 64u) start[b] = g;
+            }
+            from = to;
+        }
     }
     if (last) {
         for (int k = 1; k <= J.top; ++k) {
@@ -272,28 +363,6 @@ __device__ __forceinline__ uint64_t multinomial_threshold(const PrefixJob& J, ui
     const uint64_t r = (uint64_t)x.x0 | ((uint64_t)x.x1 << 32);
     return __umul64hi(r, S);
 }
-
-// Algorithm 8: u = (i + u_t) / N after one draw u_t ~ U[0, 1) per run, in fp64
-// with each operation rounded once.
-struct SystematicDraw {
-    double ut, c;  // u_t, S / N
-    uint64_t S;
-
-    __device__ __forceinline__ SystematicDraw(const PrefixJob& J, uint64_t total) : S(total)
-    {
-        const Words x = philox(0u, kTagSystematic, J.stream0 + blockIdx.y, 0u, J.key0, J.key1);
-        const uint64_t r = (uint64_t)x.x0 | ((uint64_t)x.x1 << 32);
-        ut = (double)(r >> 11) * 0x1p-53;
-        c = __ddiv_rn((double)S, (double)J.n);
-    }
-
-    // rises with i
-    __device__ __forceinline__ uint64_t threshold(uint32_t i) const
-    {
-        const uint64_t t = (uint64_t)floor(__dmul_rn(__dadd_rn((double)i, ut), c));
-        return t < S ? t : S - 1u;
-    }
-};
 
 // Output i of run r: the ancestor and, when the job copies rows, the row
 // (a NaN row for invalid weights, a = -1).
@@ -480,28 +549,21 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob
 }
 
 // Systematic: kSysOut outputs per block. Their thresholds rise with i, so their
-// ancestors lie between those of the first and the last of them, whose groups
-// the block finds together (one count over the top level, one 16-entry row per
-// level below). It then adds up the weights from the one to the other in tiles
-// of 2048 through LDS and bisects there: N outputs come from N inputs, so 1792
-// outputs take one tile unless their weights are very uneven, and every weight
-// is read about once. When the weights between them are more than kSysTiles
-// tiles (long runs of very small weights), each lane descends by itself
-// (OwnScan: never more than 16 tiles, which it adds up).
-constexpr uint32_t kSysPer = 7;
-constexpr uint32_t kSysOut = kSysPer * kPrefixThreads;
-constexpr uint32_t kSysTiles = 8;
-
-// Left to itself the compiler interleaves the seven bisections into 132
-// registers (3 waves per SIMD); asked for 6 waves it takes 80: a whole call at
-// 10^7 inputs 78 instead of 94 us.
+// ancestors lie between the groups of the block's first output and of the next
+// block's, which the scan has left (OwnScan: the block counts them itself over
+// its sums in LDS). The block goes through the weights from the one to the
+// other in tiles of 2048: N outputs come from N inputs, so 1792 outputs take
+// one tile unless their weights are very uneven, and every weight is read about
+// once. Each input marks the first of its outputs, if it has any
+// (outputs_below of the sums before and after it), and the running maximum of
+// the marks is the ancestors. When the weights are more than kSysTiles tiles
+// (long runs of very small weights), each lane descends by itself (OwnScan:
+// never more than 16 tiles, which it adds up).
 template <bool OwnScan>
-__global__ __launch_bounds__(kPrefixThreads) __attribute__((amdgpu_waves_per_eu(6)))
-void k_prefix_systematic(PrefixJob J)
+__global__ __launch_bounds__(kPrefixThreads) void k_prefix_systematic(PrefixJob J)
 {
-    __shared__ __align__(16) uint64_t stage[kChunk];
+    __shared__ __align__(16) uint64_t stage[OwnScan ? kTopMax : kSysOut / 2u];
     __shared__ uint32_t s_cnt[kPrefixThreads / 64];
-    __shared__ uint32_t s_g[2];
     const uint32_t first = blockIdx.x * kSysOut;
     PrefixHeader h;
     if constexpr (OwnScan)
@@ -516,39 +578,33 @@ void k_prefix_systematic(PrefixJob J)
         return;
     }
     const SystematicDraw draw(J, h.total);
-    const uint32_t last = J.n - first > kSysOut ? first + kSysOut - 1u : J.n - 1u;
-    const uint64_t t_end[2] = {draw.threshold(first), draw.threshold(last)};
-    // the top level: how many entries are <= either threshold
-    const uint64_t* lv = at<uint64_t>(J, J.o_level[J.top]);
-    uint32_t c0 = 0, c1 = 0;
+    const uint32_t outs = J.n - first < kSysOut ? J.n - first : kSysOut;
+    uint32_t g_lo, g_hi;
+    uint64_t base;
+    if constexpr (OwnScan) {
+        const uint64_t t_lo = draw.threshold(first), t_hi = draw.threshold(first + outs - 1u);
+        uint32_t c = 0;  // how many groups start at or below either threshold, at most 2048 each
 #pragma unroll
-    for (uint32_t e = 0; e < kTopMax / kPrefixThreads; ++e) {
-        const uint32_t k = e * kPrefixThreads + threadIdx.x;
-        const uint64_t v = k < J.count[J.top] ? (OwnScan ? stage[k] : lv[k]) : ~(uint64_t)0;
-        c0 += v <= t_end[0] ? 1u : 0u;
-        c1 += v <= t_end[1] ? 1u : 0u;
-    }
-    c0 |= c1 << 16;  // at most 2048 each
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) c0 += (uint32_t)__shfl_xor((int)c0, off, 64);
-    if ((threadIdx.x & 63u) == 0) s_cnt[threadIdx.x >> 6] = c0;
-    __syncthreads();
-    if (threadIdx.x < 64u) {
-        // lanes 0-15 follow the first threshold, 16-31 the last
-        const uint32_t which = (threadIdx.x >> 4) & 1u, m = threadIdx.x & 15u;
-        uint32_t both = 0;
-        for (uint32_t k = 0; k < kPrefixThreads / 64u; ++k) both += s_cnt[k];
-        uint32_t g = (which ? both >> 16 : both & 0xFFFFu) - 1u;
-        for (int k = J.top - 1; k >= 1; --k) {
-            const uint64_t v = at<uint64_t>(J, J.o_level[k])[(uint64_t)g * kFan + m];
-            const uint64_t mask = __ballot(v <= (which ? t_end[1] : t_end[0]));
-            g = g * kFan + (uint32_t)__popcll((mask >> (which * 16u)) & 0xFFFFu) - 1u;
+        for (uint32_t e = 0; e < kTopMax / kPrefixThreads; ++e) {
+            const uint64_t v = stage[e * kPrefixThreads + threadIdx.x];
+            c += (v <= t_lo ? 1u : 0u) + (v <= t_hi ? 0x10000u : 0u);
         }
-        if (m == 0 && threadIdx.x < 32u) s_g[which] = g;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) c += (uint32_t)__shfl_xor((int)c, off, 64);
+        if ((threadIdx.x & 63u) == 0) s_cnt[threadIdx.x >> 6] = c;
+        __syncthreads();
+        c = 0;
+        for (uint32_t k = 0; k < kPrefixThreads / 64u; ++k) c += s_cnt[k];
+        g_lo = (c & 0xFFFFu) - 1u;
+        g_hi = (c >> 16) - 1u;
+        base = stage[g_lo];
+        __syncthreads();  // the stage and s_cnt are overwritten next
+    } else {
+        const uint32_t* start = at<uint32_t>(J, J.o_start) + blockIdx.x;
+        g_lo = start[0];
+        g_hi = start[1];
+        base = at<uint64_t>(J, J.o_level[1])[g_lo];
     }
-    __syncthreads();
-    const uint32_t g_lo = s_g[0], g_hi = s_g[1];
-    uint64_t base = OwnScan ? stage[g_lo] : at<uint64_t>(J, J.o_level[1])[g_lo];
     const uint64_t lo = (uint64_t)g_lo * kFan, end = ((uint64_t)g_hi + 1u) * kFan;
     const double scale = ldexp(1.0, h.K - 32);
     if (!OwnScan && end - lo > (uint64_t)kSysTiles * kChunk) {  // the same for every lane of the block
@@ -559,15 +615,11 @@ void k_prefix_systematic(PrefixJob J)
         }
         return;
     }
-    uint64_t t[kSysPer];
-    int32_t a[kSysPer];
+    // mark[r]: 1 + the input (from lo on) whose outputs start at first + r, 0: none
+    uint32_t* mark = reinterpret_cast<uint32_t*>(stage);
 #pragma unroll
-    for (uint32_t e = 0; e < kSysPer; ++e) {
-        const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
-        t[e] = draw.threshold(i < J.n ? i : J.n - 1u);
-        a[e] = -1;
-    }
-    if (OwnScan) __syncthreads();  // base is read before the stage is overwritten
+    for (uint32_t e = 0; e < kSysPer; ++e) mark[e * kPrefixThreads + threadIdx.x] = 0u;
+    __syncthreads();
     for (uint64_t tile = lo; tile < end; tile += kChunk) {
         uint64_t q[kPrefixPer];
         load_fixed_tile(J, tile, scale, q);
@@ -575,41 +627,56 @@ void k_prefix_systematic(PrefixJob J)
         for (uint32_t e = 1; e < kPrefixPer; ++e) q[e] += q[e - 1u];
         uint64_t total = 0;
         const uint64_t run = base + block_exclusive_scan(q[kPrefixPer - 1u], &total);
+        const uint32_t j = (uint32_t)(tile - lo) + threadIdx.x * kPrefixPer + 1u;
+        // places of the block's outputs, 0 to outs
+        auto place = [&](uint64_t P) {
+            const uint32_t i = draw.outputs_below(P);
+            return i < first ? 0u : i - first < outs ? i - first : outs;
+        };
+        uint32_t from = place(run);
 #pragma unroll
-        for (uint32_t e = 0; e < kPrefixPer; e += 2u)
-            *reinterpret_cast<U64x2*>(stage + threadIdx.x * kPrefixPer + e) = U64x2{run + q[e], run + q[e + 1u]};
-        __syncthreads();
-        // the thresholds of this tile are those below its last sum that no
-        // earlier tile took; all are bisected together, the others for nothing
-        uint32_t at_[kSysPer];
-#pragma unroll
-        for (uint32_t e = 0; e < kSysPer; ++e) at_[e] = 0u;
-        for (uint32_t step = kChunk / 2u; step > 0; step >>= 1) {
-#pragma unroll
-            for (uint32_t e = 0; e < kSysPer; ++e) at_[e] += stage[at_[e] + step - 1u] <= t[e] ? step : 0u;
+        for (uint32_t e = 0; e < kPrefixPer; ++e) {
+            const uint32_t to = place(run + q[e]);
+            if (from < to) mark[from] = j + e;
+            from = to;
         }
-#pragma unroll
-        for (uint32_t e = 0; e < kSysPer; ++e)
-            if (a[e] < 0 && t[e] < base + total) a[e] = (int32_t)(tile + at_[e]);
         base += total;
-        __syncthreads();  // the stage is overwritten next
     }
-    // through LDS, so that the copy of a row is in the code once and not for
-    // each output in registers of its own
-    int32_t* out = reinterpret_cast<int32_t*>(stage);
+    __syncthreads();
+    // the running maximum, seven consecutive places per thread
+    uint32_t a[kSysPer], m = 0;
 #pragma unroll
-    for (uint32_t e = 0; e < kSysPer; ++e) out[e * kPrefixThreads + threadIdx.x] = a[e];
+    for (uint32_t e = 0; e < kSysPer; ++e) {
+        const uint32_t x = mark[threadIdx.x * kSysPer + e];
+        m = x > m ? x : m;
+        a[e] = m;
+    }
+    const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)m, off, 64);
+        if ((int)lane >= off && y > m) m = y;
+    }
+    if (lane == 63u) s_cnt[wv] = m;
+    __syncthreads();
+    uint32_t prev = (uint32_t)__shfl_up((int)m, 1, 64);
+    if (lane == 0) prev = 0u;
+    for (uint32_t k = 0; k < wv; ++k) prev = s_cnt[k] > prev ? s_cnt[k] : prev;
+#pragma unroll
+    for (uint32_t e = 0; e < kSysPer; ++e)
+        mark[threadIdx.x * kSysPer + e] = (uint32_t)lo - 1u + (a[e] > prev ? a[e] : prev);
+    __syncthreads();
 #pragma unroll 1
     for (uint32_t e = 0; e < kSysPer; ++e) {
-        const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
-        if (i < J.n) emit(J, i, out[e * kPrefixThreads + threadIdx.x]);
+        const uint32_t r = e * kPrefixThreads + threadIdx.x;
+        if (r < outs) emit(J, first + r, (int32_t)mark[r]);
     }
 }
 
 static uint64_t align256(uint64_t b) { return (b + 255u) & ~(uint64_t)255u; }
 
 // The layout of one run's scan region: [header][chunk sums][tree levels
-// 1..top]. Returns the region's size.
+// 1..top][starts of the systematic search's blocks]. Returns the region's size.
 uint64_t prefix_region(uint32_t n, PrefixJob* J)
 {
     const uint64_t nch = ((uint64_t)n + kChunk - 1u) / kChunk;
@@ -628,6 +695,9 @@ uint64_t prefix_region(uint32_t n, PrefixJob* J)
         J->o_level[J->top] = o;
         o += align256((cnt + kFan - 1u) / kFan * kFan * 8u);
     } while (cnt > kTopMax);
+    J->nsys = (uint32_t)(((uint64_t)n + kSysOut - 1u) / kSysOut);
+    J->o_start = o;
+    o += align256(((uint64_t)J->nsys + 1u) * 4u);
     J->top_span = 1u;
     while (J->top_span < cnt) J->top_span *= 2u;
     J->n = n;
@@ -646,8 +716,11 @@ int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s)
     else
         hipLaunchKernelGGL(k_prefix_groups<false>, dim3(J.nch, R), bt, 0, s, J);
     const bool own_scan = J.top == 1;
-    if (!own_scan)
-        hipLaunchKernelGGL(k_prefix_scan, dim3((J.count[1] + kScanGroups - 1u) / kScanGroups, R), bt, 0, s, J);
+    const dim3 scan_grid((J.count[1] + kScanGroups - 1u) / kScanGroups, R);
+    if (!own_scan && method == MGP_SYSTEMATIC)
+        hipLaunchKernelGGL(k_prefix_scan<true>, scan_grid, bt, 0, s, J);
+    else if (!own_scan)
+        hipLaunchKernelGGL(k_prefix_scan<false>, scan_grid, bt, 0, s, J);
     int err = check_launch("prefix-sum kernels");
     if (err) return err;
     if (method == MGP_MULTINOMIAL) {
@@ -662,7 +735,7 @@ int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s)
         else
             hipLaunchKernelGGL((k_prefix_multinomial<false, false>), grid, bt, 0, s, J, passes);
     } else {
-        const dim3 grid((J.n + kSysOut - 1u) / kSysOut, R);
+        const dim3 grid(J.nsys, R);
         if (own_scan)
             hipLaunchKernelGGL(k_prefix_systematic<true>, grid, bt, 0, s, J);
         else
