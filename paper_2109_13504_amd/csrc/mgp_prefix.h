@@ -35,7 +35,8 @@ struct PrefixJob {
     float* out;               // d floats at states / out + r rows_ld (states null: none)
     uint64_t rows_ld;
     uint32_t d, vec4;
-    uint32_t n, nch;
+    uint32_t n;
+    uint32_t per, nsum;       // chunks per block of the first kernel, its blocks
     int log2n;                // ceil(log2 n)
     uint32_t vec;             // the weights of every run 16-byte aligned
     uint32_t key0, key1;

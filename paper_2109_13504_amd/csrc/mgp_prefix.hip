@@ -21,17 +21,20 @@
 //
 // Launches, after the reduction of the other resamplers (validation, max,
 // fp64 sum):
-//   k_prefix_groups   per chunk of 2048 weights: the fixed-point sum of each
-//                     group, and of the chunk; for a single filter its blocks
-//                     also do the finalize step over the reduction's partials
+//   k_prefix_groups   per 1, 4 or 16 chunks of 2048 weights: the fixed-point sum
+//                     of each group, and of them all; for a single filter its
+//                     blocks also do the finalize step over the reduction's
+//                     partials
 //   k_prefix_scan     per 2048 groups: the levels' exclusive sums, the header
 //                     (up to 32768 inputs the search's blocks do it instead)
 //   k_prefix_multinomial   a descent per output, four lanes to a row
-//   k_prefix_systematic    1024 outputs per block, whose inputs (thresholds rise
-//                     with i) are added up once, in LDS, and bisected there
+//   k_prefix_systematic    1792 outputs per block, whose inputs (thresholds rise
+//                     with i) mark in LDS the first output that each of them has
 // Whole calls, us, with a level of sums per input and six or seven launches /
 // now: multinomial 10^3 19 / 11, 2^16 22 / 17, 2^20 54 / 39, 2^24 626 / 571;
-// systematic 10^3 20 / 14, 2^16 24 / 19, 10^7 107 / 77, 2^24 154 / 108.
+// systematic 10^3 20 / 14, 2^16 24 / 19, 10^7 107 / 62, 2^24 154 / 83, 2^28
+// 2551 / 1250. Systematic's search by bisection in LDS, eleven reads and
+// 64-bit compares per output, took 44 us of 10^7's 75; the marks take 28.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -54,6 +57,11 @@ constexpr uint32_t kFan = 16;                             // the tree's fan-out:
 constexpr uint32_t kTopMax = 2048;                        // entries of the top level, kept in LDS (16 KB)
 constexpr uint32_t kScanGroups = kPrefixThreads * 8;      // groups per block of the scan
 constexpr uint32_t kChunksPerScan = kScanGroups * kFan / kChunk;
+// Chunks per block of the first kernel: every block of the scan adds up the
+// sums that it leaves, so there are to be few of them, and still enough blocks.
+// Systematic, us, 1 chunk / 4 / 16: 2^22 41 / 39 / -, 10^7 66 / 64 / -, 2^28
+// 1629 / - / 1253, 2^29 4145 / - / 2516.
+constexpr uint32_t chunks_per_block(uint32_t n) {  return n < (1u << 22) ? 1u : n < (1u << 25) ? 4u : 16u; }
 constexpr uint32_t kTagMultinomial = 6u;
 constexpr uint32_t kTagSystematic = 7u;
 
@@ -156,8 +164,9 @@ __device__ __forceinline__ void load_fixed_tile(const PrefixJob& J, uint64_t fir
         load_fixed<Per, false>(J, base, scale, q);
 }
 
-// The sums of the chunk's groups (in level 1's place) and of the chunk. Fin:
-// the finalize step of the call comes first, in every block.
+// The sums of the groups of J.per chunks (in level 1's place) and of all of
+// them together. Fin: the finalize step of the call comes first, in every
+// block.
 template <bool Fin>
 __global__ __launch_bounds__(kPrefixThreads) void k_prefix_groups(PrefixJob J)
 {
@@ -171,17 +180,23 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_groups(PrefixJob J)
         st = J.stats[blockIdx.y];
     }
     if (st.status != MGP_OK) return;
-    uint64_t q[kPrefixPer];
-    load_fixed_tile(J, (uint64_t)blockIdx.x * kChunk, fixed_scale(st.w_max, J.log2n), q);
-    uint64_t s = 0;
+    const double scale = fixed_scale(st.w_max, J.log2n);
+    uint64_t all = 0;
+    for (uint32_t p = 0; p < J.per; ++p) {
+        const uint32_t chunk = blockIdx.x * J.per + p;
+        uint64_t q[kPrefixPer];
+        load_fixed_tile(J, (uint64_t)chunk * kChunk, scale, q);
+        uint64_t s = 0;
 #pragma unroll
-    for (uint32_t e = 0; e < kPrefixPer; ++e) s += q[e];
-    // two threads hold a group
-    const uint64_t both = s + (uint64_t)__shfl_xor((unsigned long long)s, 1, 64);
-    const uint32_t g = blockIdx.x * (kChunk / kFan) + threadIdx.x / 2u;
-    if (threadIdx.x % 2u == 0 && g < J.count[1]) at<uint64_t>(J, J.o_level[1])[g] = both;
+        for (uint32_t e = 0; e < kPrefixPer; ++e) s += q[e];
+        // two threads hold a group
+        const uint64_t both = s + (uint64_t)__shfl_xor((unsigned long long)s, 1, 64);
+        const uint64_t g = (uint64_t)chunk * (kChunk / kFan) + threadIdx.x / 2u;
+        if (threadIdx.x % 2u == 0 && g < J.count[1]) at<uint64_t>(J, J.o_level[1])[g] = both;
+        all += s;
+    }
     uint64_t total = 0;
-    block_exclusive_scan(s, &total);
+    block_exclusive_scan(all, &total);
     if (threadIdx.x == 0) at<uint64_t>(J, J.o_sum)[blockIdx.x] = total;
 }
 
@@ -234,7 +249,7 @@ constexpr uint32_t kSysPer = 7;
 constexpr uint32_t kSysOut = kSysPer * kPrefixThreads;
 constexpr uint32_t kSysTiles = 8;
 
-// The exclusive sums of kScanGroups groups, from the chunk sums before them
+// The exclusive sums of kScanGroups groups, from the chunks' sums before them
 // and the groups' own sums, which they replace; the entries of the higher
 // levels among them; and, by the block with the last group, every level's
 // padding (the largest integer, above any threshold) and the header.
@@ -258,12 +273,12 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
     uint64_t v[8];
 #pragma unroll
     for (uint32_t e = 0; e < 8u; ++e) v[e] = g0 + e < J.count[1] ? x1[g0 + e] : 0u;
-    const uint64_t* chunk_sum = at<uint64_t>(J, J.o_sum);
-    const uint32_t own = blockIdx.x * kChunksPerScan;  // the first chunk of this block
+    const uint64_t* sums = at<uint64_t>(J, J.o_sum);
+    const uint32_t own = blockIdx.x * (kChunksPerScan / J.per);  // the first sum of this block
     uint64_t before = 0, after = 0;
 #pragma unroll 8
-    for (uint32_t c = threadIdx.x; c < (Sys ? J.nch : own); c += kPrefixThreads) {
-        const uint64_t x = chunk_sum[c];
+    for (uint32_t c = threadIdx.x; c < (Sys ? J.nsum : own); c += kPrefixThreads) {
+        const uint64_t x = sums[c];
         before += c < own ? x : 0u;
         after += c < own ? 0u : x;
     }
@@ -619,7 +634,6 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_systematic(PrefixJob 
     uint32_t* mark = reinterpret_cast<uint32_t*>(stage);
 #pragma unroll
     for (uint32_t e = 0; e < kSysPer; ++e) mark[e * kPrefixThreads + threadIdx.x] = 0u;
-    __syncthreads();
     for (uint64_t tile = lo; tile < end; tile += kChunk) {
         uint64_t q[kPrefixPer];
         load_fixed_tile(J, tile, scale, q);
@@ -666,6 +680,15 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_systematic(PrefixJob 
     for (uint32_t e = 0; e < kSysPer; ++e)
         mark[threadIdx.x * kSysPer + e] = (uint32_t)lo - 1u + (a[e] > prev ? a[e] : prev);
     __syncthreads();
+    if (!J.states && J.anc) {
+        int32_t* anc = J.anc + (uint64_t)blockIdx.y * J.anc_ld + first;
+#pragma unroll
+        for (uint32_t e = 0; e < kSysPer; ++e) {
+            const uint32_t r = e * kPrefixThreads + threadIdx.x;
+            if (r < outs) anc[r] = (int32_t)mark[r];
+        }
+        return;
+    }
 #pragma unroll 1
     for (uint32_t e = 0; e < kSysPer; ++e) {
         const uint32_t r = e * kPrefixThreads + threadIdx.x;
@@ -701,7 +724,8 @@ uint64_t prefix_region(uint32_t n, PrefixJob* J)
     J->top_span = 1u;
     while (J->top_span < cnt) J->top_span *= 2u;
     J->n = n;
-    J->nch = (uint32_t)nch;
+    J->per = chunks_per_block(n);
+    J->nsum = (uint32_t)((nch + J->per - 1u) / J->per);
     int L = 0;
     while (((uint64_t)1 << L) < (uint64_t)n) ++L;
     J->log2n = L;
@@ -712,9 +736,9 @@ int enqueue_prefix(const PrefixJob& J, uint32_t R, int method, hipStream_t s)
 {
     const dim3 bt(kPrefixThreads);
     if (J.parts)
-        hipLaunchKernelGGL(k_prefix_groups<true>, dim3(J.nch, R), bt, 0, s, J);
+        hipLaunchKernelGGL(k_prefix_groups<true>, dim3(J.nsum, R), bt, 0, s, J);
     else
-        hipLaunchKernelGGL(k_prefix_groups<false>, dim3(J.nch, R), bt, 0, s, J);
+        hipLaunchKernelGGL(k_prefix_groups<false>, dim3(J.nsum, R), bt, 0, s, J);
     const bool own_scan = J.top == 1;
     const dim3 scan_grid((J.count[1] + kScanGroups - 1u) / kScanGroups, R);
     if (!own_scan && method == MGP_SYSTEMATIC)
@@ -765,8 +789,9 @@ static uint64_t prefix_workspace(uint32_t n)
 }
 
 // Up to this size the finalize step runs in every block of k_prefix_groups;
-// beyond, its 1024 to 4096 partials per block cost more than its own launch.
-constexpr uint32_t kPrefixFinMaxN = 1u << 21;
+// beyond, it has its own launch, which is nothing there. Systematic, us, in the
+// blocks / by itself: 2^22 39 / 40, 10^7 61.5 / 62.2, 2^24 83 / 84.
+constexpr uint32_t kPrefixFinMaxN = 1u << 24;
 
 extern "C" {
 
