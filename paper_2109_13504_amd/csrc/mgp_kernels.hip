@@ -351,21 +351,33 @@ struct SmallArgs {
 };
 
 constexpr uint32_t kSplitMaxM = 1u << 16;  // beyond, four waves per 64 particles cost more than they hide
-// Megopolis by windows for n up to kSplitMaxM, with each particle's draws
-// spread over four lanes. A block serves 64 particles: in each pass of
-// kSplitPass steps its four waves compute the particles' u draws (one Philox
-// call per five steps), their candidates' positions and weights, all
-// independent of the chain, into LDS; then wave 0 runs the chains, whose
-// serial part is only the product, the compare and two selects per step. Every load of a pass is issued before the first LDS store, and
-// steps past the pass write a spare row, so nothing branches around a load.
-// The arithmetic and the draws are those of megopolis_chain: the ancestors are
-// identical.
-// kSplitSmall reads the candidates from LDS and draws each pass's offsets into
-// LDS too (waves 1-3 draw the next pass's while wave 0 runs the chains).
-constexpr uint32_t kSplitPass = 20;  // steps per pass: a multiple of 20 (chain rounds) and of 5 (u blocks)
-constexpr uint32_t kSplitGroups = kLoopThreads / 64u;
-constexpr uint32_t kSplitBlocksPerWave = kSplitPass / (5u * kSplitGroups);
-static_assert(kSplitPass % (5u * kSplitGroups) == 0 && kSplitPass % 20u == 0, "whole u blocks per wave and rounds");
+// Megopolis by windows for n up to kSplitMaxM, with each particle's work
+// spread over four waves. A block serves 64 particles. Waves 1-3 compute the
+// particles' u draws (one Philox call per five steps) and their candidates'
+// weights, all independent of the chain, for a pass of kSplitPass steps into
+// one of two LDS buffers, while wave 0 runs the chains of the pass before from
+// the other; its serial part is the product, the compare and two selects per
+// step. The chain keeps the number of the last accepted step, and the position
+// comes from that step's offset at the end. The arithmetic and the draws are
+// those of megopolis_chain: the ancestors are identical.
+//
+// What bounds it is instruction issue of the producers, on the CUs that have
+// one block more than the others: at 20000 particles 160 instructions per u
+// block (200 with each window's address worked out by scalar instructions and
+// not by one lane per step); loads made a pass ahead, longer passes and more
+// producers (7 of them: 18.5 instead of 20.2, but 3% slower at small B) give
+// little. Whole calls, us, at B = 4 / 16 / 60 / 354, when the four waves took
+// turns with the chain (passes of 20 steps, two barriers each) / now:
+//   1000    6.9 / 5.9   7.8 / 6.5   9.5 / 7.8   22.2 / 12.6
+//   8192    9.8 / 8.2  10.7 / 8.5  11.8 / 10.2  26.3 / 17.3
+//   20000   7.9 / 7.8   8.7 / 8.5  11.3 / 9.9   29.6 / 20.2
+//   2^16    9.3 / 8.5  10.1 / 9.4  12.9 / 11.3  38.5 / 28.2
+// kSplitSmall reads the candidates from LDS and draws the offsets into LDS too
+// (wave 0, two passes ahead).
+constexpr uint32_t kSplitProducers = kLoopThreads / 64u - 1u;
+constexpr uint32_t kSplitBlocks = 2;  // u blocks of five steps per producer and pass
+constexpr uint32_t kSplitPass = 5u * kSplitBlocks * kSplitProducers;
+static_assert(kSplitPass <= 64u, "a lane per step of the pass");
 
 template <int Mode>
 __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa, uint32_t n, uint32_t m, LoopStart ls,
@@ -374,16 +386,14 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
                                                                   uint32_t seg_mask, int32_t* __restrict__ anc,
                                                                   SmallArgs f, RowCopy rc)
 {
-    __shared__ float su[kSplitPass + 1][64];   // row kSplitPass: the spare row
-    __shared__ float swj[kSplitPass + 1][64];
-    __shared__ uint32_t sjb[kSplitPass + 1][64];
+    __shared__ float2 step[2][kSplitPass][64];  // u and the candidate's weight
     const uint32_t lane = threadIdx.x & 63u;
-    // the wave's index, known to the compiler as wave-uniform: its offsets
-    // are scalar loads
+    // the wave's index, known to the compiler as wave-uniform: no divergence
+    // between the chains' wave and the producers
     const uint32_t q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t i = blockIdx.x * 64u + lane;
     constexpr bool kOwnOffsets = Mode == kSplitSmall;
-    __shared__ uint32_t soffs[2][kOwnOffsets ? kSplitPass : 1];  // this pass's offsets and the next pass's
+    __shared__ uint32_t soffs[2][kOwnOffsets ? kSplitPass : 1];  // the offsets of a pass and the next
     __shared__ __align__(16) float Ms[Mode == kSplitSmall ? kSmallMaxN + kSmallPad : 1];
     uint32_t B;
     if constexpr (Mode == kSplitSmall) {
@@ -415,97 +425,118 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
         else
             return *(GlobalPtr<const float>)(window_at(W, s, n, 64u) + v);
     };
-    uint32_t kk = i * 4u;
-    float wk = candidate(start, lane * 4u);
     // the offsets of the pass starting at step c0, drawn as draw_offsets draws
     // them, by the threads t0, t0 + stride, ... of the block
     auto draw_pass = [&](uint32_t c0, uint32_t* dst, uint32_t t0, uint32_t stride) {
         const uint32_t cnt = B - c0 < kSplitPass ? B - c0 : kSplitPass;
-        for (uint32_t c = t0; c < (cnt + 3u) / 4u; c += stride) {
-            const Words x = philox(c0 / 4u + c, kTagOffset, stream_id, 0u, key0, key1);
+        // whole Philox calls: c0 need not be a multiple of four
+        for (uint32_t c = c0 / 4u + t0; c < (c0 + cnt + 3u) / 4u; c += stride) {
+            const Words x = philox(c, kTagOffset, stream_id, 0u, key0, key1);
             const uint32_t o[4] = {x.x0, x.x1, x.x2, x.x3};
 #pragma unroll
-            for (uint32_t r = 0; r < 4; ++r)
-                if (4u * c + r < cnt) dst[4u * c + r] = uniform_index(o[r], n);
+            for (uint32_t r = 0; r < 4; ++r) {
+                const uint32_t d = 4u * c + r - c0;  // wraps below c0
+                if (d < cnt) dst[d] = uniform_index(o[r], n);
+            }
         }
     };
     if constexpr (kOwnOffsets) {
         draw_pass(0u, soffs[0], threadIdx.x, kLoopThreads);
+        if (B > kSplitPass) draw_pass(kSplitPass, soffs[1], threadIdx.x, kLoopThreads);
         __syncthreads();
     }
-    for (uint32_t b0 = 0, buf = 0; b0 < B; b0 += kSplitPass, buf ^= 1u) {
+    // A producer's part of the pass from step b0 on: the u blocks q - 1,
+    // q - 1 + kSplitProducers, ... of it. Lane l first works out where the window of
+    // the pass's step l lies (past B that of step B - 1, which the chain does
+    // not read); each of its steps then takes that from its lane.
+    auto produce = [&](uint32_t b0, uint32_t buf) {
         const uint32_t cnt = B - b0 < kSplitPass ? B - b0 : kSplitPass;
-        // this wave's u blocks q, q + 4, ... of the pass: draws, positions and
-        // candidate weights (steps past the pass use step cnt - 1's offset and
-        // land in the spare row)
-        UBlock ub[kSplitBlocksPerWave];
-        uint32_t jb[kSplitBlocksPerWave][5];
-        float wj[kSplitBlocksPerWave][5];
+        const uint32_t sl = lane < cnt ? lane : cnt - 1u;
+        uint32_t o = kOwnOffsets ? soffs[buf][sl] : offsets[b0 + sl];
+        o = o < n ? o : n - 1u;
+        const uint32_t at = window_start(start, o, seg_mask, n);
+        const uint32_t rot = (o & seg_mask) * 4u;
+        const uint64_t base = kOwnOffsets ? (uint64_t)at * 4u : (uint64_t)window_at(W, at, n, 64u);
+        float wj[kSplitBlocks][5];
 #pragma unroll
-        for (uint32_t t = 0; t < kSplitBlocksPerWave; ++t) {
-            const uint32_t g = q + kSplitGroups * t;
-#pragma unroll
-            for (uint32_t r = 0; r < 5u; ++r) {
-                const uint32_t s = g * 5u + r;
-                uint32_t o = kOwnOffsets ? soffs[buf][s < cnt ? s : cnt - 1u] : offsets[b0 + (s < cnt ? s : cnt - 1u)];
-                if constexpr (kOwnOffsets) o = __builtin_amdgcn_readfirstlane(o);
-                o = o < n ? o : n - 1u;
-                const uint32_t at = window_start(start, o, seg_mask, n);
-                const uint32_t voff = la4 | ((ll4 + (o & seg_mask) * 4u) & (seg_mask * 4u));
-                wj[t][r] = candidate(at, voff);
-                jb[t][r] = voff + 4u * at;
-            }
-        }
-#pragma unroll
-        for (uint32_t t = 0; t < kSplitBlocksPerWave; ++t)
-            ub[t] = u_block(philox(b0 / 5u + q + kSplitGroups * t, kTagU, stream_id, i, key0, key1));
-#pragma unroll
-        for (uint32_t t = 0; t < kSplitBlocksPerWave; ++t) {
+        for (uint32_t t = 0; t < kSplitBlocks; ++t) {
+            const uint32_t g = q - 1u + kSplitProducers * t;
+            if (g * 5u >= cnt) continue;
 #pragma unroll
             for (uint32_t r = 0; r < 5u; ++r) {
-                const uint32_t s = (q + kSplitGroups * t) * 5u + r;
-                const uint32_t row = s < cnt ? s : kSplitPass;
-                su[row][lane] = ub[t].u[r];
-                swj[row][lane] = wj[t][r];
-                sjb[row][lane] = jb[t][r];
-            }
-        }
-        __syncthreads();
-        if (q == 0) {
-            uint32_t s0 = 0;
-            for (; s0 + 20u <= cnt; s0 += 20u) {
-                float uu[20], ww[20];
-                uint32_t jj[20];
-#pragma unroll
-                for (uint32_t s = 0; s < 20u; ++s) {
-                    uu[s] = su[s0 + s][lane];
-                    ww[s] = swj[s0 + s][lane];
-                    jj[s] = sjb[s0 + s][lane];
-                }
-#pragma unroll
-                for (uint32_t s = 0; s < 20u; ++s) {
-                    const float prod = uu[s] * wk;
-                    const bool acc = prod <= ww[s];
-                    kk = acc ? jj[s] : kk;
-                    wk = acc ? ww[s] : wk;
+                const int s = (int)(g * 5u + r);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, s);
+                const uint32_t v =
+                    la4 | ((ll4 + (uint32_t)__builtin_amdgcn_readlane((int)rot, s)) & (seg_mask * 4u));
+                if constexpr (kOwnOffsets) {
+                    wj[t][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ms) + lo + v);
+                } else {
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(base >> 32), s);
+                    wj[t][r] = *(GlobalPtr<const float>)((GlobalPtr<const char>)(((uint64_t)hi << 32) | lo) + v);
                 }
             }
-            for (; s0 < cnt; ++s0) {
-                const float prod = su[s0][lane] * wk;
-                const float w = swj[s0][lane];
-                const bool acc = prod <= w;
-                kk = acc ? sjb[s0][lane] : kk;
-                wk = acc ? w : wk;
-            }
-        } else if constexpr (kOwnOffsets) {
-            // while wave 0 runs the chains, the other waves draw the next
-            // pass's offsets into the other buffer
-            if (b0 + kSplitPass < B) draw_pass(b0 + kSplitPass, soffs[buf ^ 1u], threadIdx.x - 64u, kLoopThreads - 64u);
         }
-        __syncthreads();  // the next pass overwrites the buffers
+#pragma unroll
+        for (uint32_t t = 0; t < kSplitBlocks; ++t) {
+            const uint32_t g = q - 1u + kSplitProducers * t;
+            if (g * 5u >= cnt) continue;
+            const UBlock ub = u_block(philox(b0 / 5u + g, kTagU, stream_id, i, key0, key1));
+#pragma unroll
+            for (uint32_t r = 0; r < 5u; ++r) step[buf][g * 5u + r][lane] = make_float2(ub.u[r], wj[t][r]);
+        }
+    };
+    float wk = candidate(start, lane * 4u);
+    uint32_t last = 0xFFFFFFFFu;  // the last accepted step
+    if (q > 0) produce(0u, 0u);
+    __syncthreads();
+    for (uint32_t b0 = 0, buf = 0; b0 < B; b0 += kSplitPass, buf ^= 1u) {
+        if (q > 0) {
+            if (b0 + kSplitPass < B) produce(b0 + kSplitPass, buf ^ 1u);
+        } else {
+            const uint32_t cnt = B - b0 < kSplitPass ? B - b0 : kSplitPass;
+            uint32_t at = 0xFFFFFFFFu;
+            if (cnt == kSplitPass) {
+                float2 x[kSplitPass];
+#pragma unroll
+                for (uint32_t s = 0; s < kSplitPass; ++s) x[s] = step[buf][s][lane];
+#pragma unroll
+                for (uint32_t s = 0; s < kSplitPass; ++s) {
+                    const float prod = x[s].x * wk;
+                    const bool acc = prod <= x[s].y;
+                    at = acc ? s : at;
+                    wk = acc ? x[s].y : wk;
+                }
+            } else {
+                for (uint32_t s = 0; s < cnt; ++s) {
+                    const float2 x = step[buf][s][lane];
+                    const float prod = x.x * wk;
+                    const bool acc = prod <= x.y;
+                    at = acc ? s : at;
+                    wk = acc ? x.y : wk;
+                }
+            }
+            last = at != 0xFFFFFFFFu ? b0 + at : last;
+            // the producers read the other buffer's offsets now
+            if constexpr (kOwnOffsets)
+                if (b0 + 2u * kSplitPass < B) draw_pass(b0 + 2u * kSplitPass, soffs[buf], lane, 64u);
+        }
+        __syncthreads();  // the buffers change sides
     }
     if (q == 0 && i < m) {
-        const uint32_t k = kk / 4u;
+        uint32_t k = i;
+        if (last != 0xFFFFFFFFu) {
+            uint32_t o;
+            if constexpr (kOwnOffsets) {
+                const Words x = philox(last / 4u, kTagOffset, stream_id, 0u, key0, key1);
+                const uint32_t lo = (last & 1u) ? x.x1 : x.x0, hi = (last & 1u) ? x.x3 : x.x2;
+                o = uniform_index((last & 2u) ? hi : lo, n);
+            } else {
+                o = offsets[last];
+                o = o < n ? o : n - 1u;
+            }
+            k = window_start(start, o, seg_mask, n) +
+                (la4 | ((ll4 + (o & seg_mask) * 4u) & (seg_mask * 4u))) / 4u;
+        }
         const int32_t kn = (int32_t)(k >= n ? k - n : k);
         if (anc) anc[i] = kn;
         if (rc.states) copy_row(rc, i, kn);
