@@ -616,6 +616,44 @@ __global__ __launch_bounds__(256) void k_gather_scalar(const float* __restrict__
     }
 }
 
+// The same for fewer than 2^31 elements (T: floats or float4s), Per of them to a
+// thread: the row comes from a multiplication, t / d = t mult >> shift
+// (row_divisor), where a 64-bit division of some hundred instructions per
+// element bound rows of odd lengths, and the thread's loads are in flight
+// together. us, 2^22 rows in order of a resample at y = 0, 64-bit divisions / now:
+// d = 3 34.5 / 24.6, d = 5 54.6 / 39.8, d = 33 442 / 215 (HBM rate), d = 4 and 16
+// even; 100003 rows, d = 5: 2.6 / 2.2.
+struct RowDivisor {
+    uint32_t mult, shift;
+};
+
+template <typename T, uint32_t Per>
+__global__ __launch_bounds__(256) void k_gather(const T* __restrict__ states, uint32_t n_states, uint32_t d,
+                                                RowDivisor by, const int32_t* __restrict__ anc, uint32_t total,
+                                                T* __restrict__ out)
+{
+    const uint32_t first = blockIdx.x * (256u * Per) + threadIdx.x;
+    int32_t k[Per];
+    uint32_t c[Per];
+    T v[Per];
+#pragma unroll
+    for (uint32_t e = 0; e < Per; ++e) {
+        const uint32_t t = first + 256u * e < total ? first + 256u * e : total - 1u;
+        const uint32_t row = (uint32_t)(((uint64_t)t * by.mult) >> by.shift);
+        c[e] = t - row * d;
+        k[e] = anc[row];
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < Per; ++e) {
+        const bool in = k[e] >= 0 && (uint32_t)k[e] < n_states;
+        const T x = states[(in ? (uint64_t)k[e] * d : 0u) + c[e]];
+        v[e] = in ? x : (T)NAN;
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < Per; ++e)
+        if (first + 256u * e < total) __builtin_nontemporal_store(v[e], &out[first + 256u * e]);
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -961,11 +999,35 @@ int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_
     return enqueue_loop(w, n, p, ws, anc, stream, rc);
 }
 
-// One element (or float4) per thread up to 2^20 blocks, grid-stride beyond.
+// 2^31 elements and more: 2^20 blocks, grid-stride.
 static uint32_t gather_blocks(uint64_t total)
 {
     const uint64_t b = (total + 255u) / 256u;
     return (uint32_t)(b < (1u << 20) ? (b ? b : 1) : (1u << 20));
+}
+
+// Floats from which a thread of the gather takes four and not two. us, two /
+// four: 100003 rows of 3 2.1 / 2.2, 2^20 rows of 2 4.1 / 4.0, of 5 12.6 / 9.7,
+// of 33 63 / 51. float4s: two (2^22 rows of 16 floats 92.5 either way).
+constexpr uint64_t kGatherFour = 1ull << 21;
+
+// floor(t / d) = t mult >> shift for t < 2^31: with 2^L >= d > 2^(L-1),
+// mult = (2^(31+L) + e) / d for some 0 < e <= d fits 32 bits, and the quotient
+// is too large by t e / (d 2^(31+L)) < 1 / d.
+static RowDivisor row_divisor(uint32_t d)
+{
+    uint32_t L = 0;
+    while (((uint64_t)1 << L) < d) ++L;
+    return RowDivisor{(uint32_t)(((uint64_t)1 << (31u + L)) / d + 1u), 31u + L};
+}
+
+template <typename T, uint32_t Per>
+static void launch_gather(const T* states, uint32_t n_states, uint32_t d, const int32_t* anc, uint64_t total, T* out,
+                          hipStream_t stream)
+{
+    const dim3 grid((uint32_t)((total + 256u * Per - 1u) / (256u * Per)));
+    hipLaunchKernelGGL((k_gather<T, Per>), grid, dim3(256), 0, stream, states, n_states, d, row_divisor(d), anc,
+                       (uint32_t)total, out);
 }
 
 int enqueue_gather(const float* states, uint32_t n_states, uint32_t d, const int32_t* anc, uint32_t n_out,
@@ -973,16 +1035,22 @@ int enqueue_gather(const float* states, uint32_t n_states, uint32_t d, const int
 {
     if (n_out == 0) return MGP_OK;
     const bool vec = (d % 4u == 0u) && (((uintptr_t)states & 15u) == 0) && (((uintptr_t)out & 15u) == 0);
-    if (vec) {
-        const uint32_t d4 = d / 4u;
-        const uint64_t total = (uint64_t)n_out * d4;
-        const dim3 grid(gather_blocks(total));
-        hipLaunchKernelGGL(k_gather_vec4, grid, dim3(256), 0, stream, reinterpret_cast<const float4*>(states),
-                           n_states, d4, anc, total, reinterpret_cast<float4*>(out));
+    const uint64_t total = (uint64_t)n_out * (vec ? d / 4u : d);
+    const bool wide = total >= (1ull << 31);  // 64-bit element numbers
+    if (vec && wide) {
+        hipLaunchKernelGGL(k_gather_vec4, dim3(gather_blocks(total)), dim3(256), 0, stream,
+                           reinterpret_cast<const float4*>(states), n_states, d / 4u, anc, total,
+                           reinterpret_cast<float4*>(out));
+    } else if (wide) {
+        hipLaunchKernelGGL(k_gather_scalar, dim3(gather_blocks(total)), dim3(256), 0, stream, states, n_states, d, anc,
+                           total, out);
+    } else if (vec) {
+        launch_gather<Row4, 2>(reinterpret_cast<const Row4*>(states), n_states, d / 4u, anc, total,
+                               reinterpret_cast<Row4*>(out), stream);
+    } else if (total < kGatherFour) {
+        launch_gather<float, 2>(states, n_states, d, anc, total, out, stream);
     } else {
-        const uint64_t total = (uint64_t)n_out * d;
-        const dim3 grid(gather_blocks(total));
-        hipLaunchKernelGGL(k_gather_scalar, grid, dim3(256), 0, stream, states, n_states, d, anc, total, out);
+        launch_gather<float, 4>(states, n_states, d, anc, total, out, stream);
     }
     return check_launch("gather kernel");
 }

@@ -7,7 +7,7 @@
 // division scaled against overflow. Here the angle comes as a fraction of a
 // turn in 32 bits, whose quadrant is two bits of it; the logarithm's argument
 // is a count over 2^32; the exponent is negative; the divisor is at least 1.
-// Instructions per particle of a predict/update step: 000 instead of 186.
+// Instructions per particle of a predict/update step: 138 instead of 186.
 //
 // Accuracy: worst error over 2^24 arguments of each, in units in the last
 // place against 64-bit-mantissa arithmetic, and the library function's on the
