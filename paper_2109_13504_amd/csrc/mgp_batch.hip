@@ -140,8 +140,8 @@ __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats
 }
 
 // Minimum waves per SIMD asked of the compiler for the grid-scheduled
-// accept loop. C2's shared partition draws raise its register count to 78
-// (6 waves); asked for 7 it schedules the loop into 70 registers without
+// accept loop. C2's shared partition draws raise its register count to 86
+// (5 waves); asked for 7 it schedules the loop into 69 registers without
 // spilling: 7% and 13% faster at B = 32 and 64, equal at B = 16. The others,
 // and the persistent kernel (whose queue logic adds registers), are left to
 // the compiler: asked for 7 or 8 they would spill.
