@@ -264,10 +264,6 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
 {
     const mgp_stats& st = J.stats[blockIdx.y];
     const bool last = blockIdx.x == gridDim.x - 1u;
-    if (st.status != MGP_OK) {
-        if (last && threadIdx.x == 0) *at<PrefixHeader>(J, J.o_hdr) = PrefixHeader{0u, 0, 0};
-        return;
-    }
     uint64_t* x1 = at<uint64_t>(J, J.o_level[1]);
     const uint32_t g0 = blockIdx.x * kScanGroups + threadIdx.x * 8u;
     uint64_t v[8];
@@ -281,6 +277,12 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
         const uint64_t x = sums[c];
         before += c < own ? x : 0u;
         after += c < own ? 0u : x;
+    }
+    // after the loads, which are in bounds whatever it says: one round trip
+    // less (2^17 17.1 to 16.6 us, 2^20 38.1 to 37.7, multinomial)
+    if (st.status != MGP_OK) {
+        if (last && threadIdx.x == 0) *at<PrefixHeader>(J, J.o_hdr) = PrefixHeader{0u, 0, 0};
+        return;
     }
     uint64_t base = 0, total = 0, S = 0;
     block_exclusive_scan(before, &base);
