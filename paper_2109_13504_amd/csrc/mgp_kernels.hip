@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_finalize(const Partial* __re
                                                              mgp_stats* __restrict__ st_user,
                                                              uint32_t* __restrict__ offsets)
 {
-    finalize_one(part, nparts, a, st, st_user, offsets);
+    finalize_one<true>(part, nparts, a, st, st_user, offsets);
 }
 
 // ---------------------------------------------------------------------------

@@ -32,7 +32,7 @@
 //                     with i) mark in LDS the first output that each of them has
 // Whole calls, us, with a level of sums per input and six or seven launches /
 // now: multinomial 10^3 19 / 11, 2^16 22 / 17, 2^20 54 / 39, 2^24 626 / 571;
-// systematic 10^3 20 / 14, 2^16 24 / 19, 10^7 107 / 62, 2^24 154 / 83, 2^28
+// systematic 10^3 20 / 14, 2^16 24 / 17, 10^7 107 / 58, 2^24 154 / 81, 2^28
 // 2551 / 1250. Systematic's search by bisection in LDS, eleven reads and
 // 64-bit compares per output, took 44 us of 10^7's 75; the marks take 28.
 #include <hip/hip_runtime.h>
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_groups(PrefixJob J)
     mgp_stats st;
     if constexpr (Fin) {
         __shared__ mgp_stats st_local;
-        finalize_one(J.parts, J.nparts, J.fin, &st_local, blockIdx.x == 0 ? J.st_user : nullptr, nullptr);
+        finalize_one<true>(J.parts, J.nparts, J.fin, &st_local, blockIdx.x == 0 ? J.st_user : nullptr, nullptr);
         if (blockIdx.x == 0 && threadIdx.x == 0) *J.stats = st_local;
         st = st_local;
     } else {
