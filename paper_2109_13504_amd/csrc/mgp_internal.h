@@ -94,13 +94,15 @@ struct OutRange {
     uint64_t bytes;
 };
 bool in_place(const float* w, uint32_t n, const OutRange* outs, int count);
+bool ranges_overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes);
 // layout: kLayoutInPlace or kLayoutCopy (Megopolis with windows), else unused.
+// copy: where the reduction also writes the n weights (16-byte aligned), or null.
 int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
-                            mgp_stats* st_user, hipStream_t stream);
+                            mgp_stats* st_user, hipStream_t stream, float* copy = nullptr);
 // The reduction's partials alone, and the arguments of the finalize step that
 // the next kernel does over them.
 int enqueue_partials(const float* w, uint32_t n, const Params& p, char* ws, uint32_t* nparts, FinalizeArgs* fin,
-                     hipStream_t stream);
+                     float* copy, hipStream_t stream);
 // The accept loop (after the reduction and finalize launches); with rc.states
 // set, the particle copy x_bar_i = x_{k_i} runs as its epilogue. anc may be
 // null when rc copies the rows.

@@ -716,7 +716,7 @@ size_t workspace_bytes(uint32_t n, const Params& p)
     return b;
 }
 
-static bool ranges_overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes)
+bool ranges_overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes)
 {
     const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
     return a && b && a_bytes && b_bytes && a0 < b0 + b_bytes && b0 < a0 + a_bytes;
@@ -756,14 +756,16 @@ static FinalizeArgs finalize_args(uint32_t n, const Params& p, bool make_offsets
 
 // The reduction launch: partials and, for Megopolis with make_offsets, the
 // ends of the windows or the copy; with early > 0 also that many offsets, and
-// log(eps). Returns the number of partials through *nparts.
+// log(eps). With copy (16-byte aligned, and no windows asked for), the weights
+// too. Returns the number of partials through *nparts.
 static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout,
-                          bool early, char* ws, uint32_t* nparts, hipStream_t stream)
+                          bool early, char* ws, uint32_t* nparts, hipStream_t stream, float* copy = nullptr)
 {
     Partial* part = reinterpret_cast<Partial*>(ws + kWsPartialsOffset);
     const uint32_t g = reduce_blocks(n);
     const uint32_t chunk = reduce_chunk(n, g);
     ReduceExtra x{};
+    x.copy = copy;
     uint32_t extra = 0;
     if (make_offsets && uses_windows(n, p.variant)) {
         float* aux = reinterpret_cast<float*>(ws + windows_offset(p.b_max));
@@ -797,13 +799,13 @@ static WindowArgs window_args(const float* w, const Params& p, char* ws)
 }
 
 int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
-                            mgp_stats* st_user, hipStream_t stream)
+                            mgp_stats* st_user, hipStream_t stream, float* copy)
 {
     Partial* part = reinterpret_cast<Partial*>(ws + kWsPartialsOffset);
     mgp_stats* st = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
     uint32_t* offs = reinterpret_cast<uint32_t*>(ws + kWsOffsetsOffset);
     uint32_t g = 0;
-    int rc = enqueue_reduce(w, n, p, make_offsets, layout, false, ws, &g, stream);
+    int rc = enqueue_reduce(w, n, p, make_offsets, layout, false, ws, &g, stream, copy);
     if (rc) return rc;
     const FinalizeArgs a = finalize_args(n, p, make_offsets);
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kReduceThreads), 0, stream, part, g, a, st, st_user, offs);
@@ -811,10 +813,10 @@ int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool ma
 }
 
 int enqueue_partials(const float* w, uint32_t n, const Params& p, char* ws, uint32_t* nparts, FinalizeArgs* fin,
-                     hipStream_t stream)
+                     float* copy, hipStream_t stream)
 {
     *fin = finalize_args(n, p, false);
-    return enqueue_reduce(w, n, p, false, kLayoutInPlace, false, ws, nparts, stream);
+    return enqueue_reduce(w, n, p, false, kLayoutInPlace, false, ws, nparts, stream, copy);
 }
 
 // The accept loop's launch for m outputs from n inputs, with the finalize

@@ -776,9 +776,8 @@ using namespace mgp;
 
 // The scan room that the single-filter entry point asks for: 8 bytes per input
 // (whole chunks) and per entry of the tree down to 16 entries, 16 per chunk, 4
-// per 256 outputs. The scan itself uses a tenth of it (prefix_region); what a
-// caller's workspace must hold is kept as it was, so that the same buffers
-// are taken and refused.
+// per 256 outputs. The scan itself uses a tenth of it (prefix_region), and a
+// call whose outputs overlap its weights half of the rest for a copy of them.
 static uint64_t prefix_workspace(uint32_t n)
 {
     const uint64_t nch = ((uint64_t)n + kChunk - 1u) / kChunk;
@@ -819,7 +818,7 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     if (((uintptr_t)workspace_dev & 255u) != 0) return fail(MGP_EINVAL, "workspace must be 256-byte aligned");
     const uint32_t un = (uint32_t)n;
     PrefixJob J{};
-    prefix_region(un, &J);
+    const uint64_t region_bytes = prefix_region(un, &J);
     const size_t need = prefix_workspace(un);
     if (workspace_bytes_ < need) return fail(MGP_ERANGE, "workspace has %zu bytes, needs %zu", workspace_bytes_, need);
     char* ws = static_cast<char*>(workspace_dev);
@@ -834,20 +833,29 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     p.stream_id = stream_id;
     p.partition_bytes = 128;
     p.b_max = 1;
+    // The search reads the weights while it writes ancestors. Outputs that lie
+    // over the weights (ancestors in place, say) are written while other blocks
+    // still read there, so such a call scans and searches a copy, which the
+    // reduction makes behind the scan's region.
+    const uint64_t bytes = 4ull * un;
+    float* copy = nullptr;
+    if (ranges_overlap(w_dev, bytes, ancestors_dev, bytes) ||
+        ranges_overlap(w_dev, bytes, stats_dev, sizeof(mgp_stats)))
+        copy = reinterpret_cast<float*>(ws + workspace_bytes(1u) + align256(region_bytes));
     J.stats = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
     if (un <= kPrefixFinMaxN) {
         J.parts = reinterpret_cast<const Partial*>(ws + kWsPartialsOffset);
         J.st_user = stats_dev;
-        const int err = enqueue_partials(w_dev, un, p, ws, &J.nparts, &J.fin, s);
+        const int err = enqueue_partials(w_dev, un, p, ws, &J.nparts, &J.fin, copy, s);
         if (err) return err;
     } else {
-        const int err = enqueue_reduce_finalize(w_dev, un, p, false, kLayoutInPlace, ws, stats_dev, s);
+        const int err = enqueue_reduce_finalize(w_dev, un, p, false, kLayoutInPlace, ws, stats_dev, s, copy);
         if (err) return err;
     }
-    J.w = w_dev;
+    J.w = copy ? copy : w_dev;
     J.region = ws + workspace_bytes(1u);
     J.anc = ancestors_dev;
-    J.vec = ((uintptr_t)w_dev & 15u) == 0 ? 1u : 0u;
+    J.vec = ((uintptr_t)J.w & 15u) == 0 ? 1u : 0u;
     J.key0 = (uint32_t)seed;
     J.key1 = (uint32_t)(seed >> 32);
     J.stream0 = stream_id;
