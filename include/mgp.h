@@ -93,9 +93,10 @@ int mgp_workspace_size(int32_t n, const mgp_params* params, size_t* bytes);
  * For n <= 8192 (MGP_MEGOPOLIS) or n <= 4096 (the other variants) the three
  * steps run as one launch that keeps the weights in LDS, and for n up to 2^20
  * or 2^18 as two (step 2 inside the accept loop); the results, stats
- * included, are the same. Only mgp_compute_B prepares the workspace for a
- * following mgp_resample_prepared; after a one-launch call, and for
- * MGP_MEGOPOLIS after any with n <= 32768, such a loop writes -1.
+ * included, are the same. mgp_compute_B is what prepares the workspace for
+ * mgp_resample_prepared. A call of this kind leaves it prepared just so, except
+ * in one launch and, for MGP_MEGOPOLIS, with n <= 32768: a prepared loop
+ * writes -1 then.
  * w_dev          : n fp32 weights, device, contiguous, >= 0 and finite.
  * ancestors_dev  : n int32, device, written.
  * stats_dev      : device mgp_stats written by step 2, or NULL.
@@ -157,7 +158,7 @@ int mgp_compute_B(const float* w_dev, int32_t n, const mgp_params* params, mgp_s
  * (n, variant, seed, stream_id) written by mgp_compute_B, and on a mismatch
  * (or invalid weights) writes -1 to every ancestor. w_dev must hold the same
  * weights as in that call: with MGP_MEGOPOLIS (n <= 2^29 - 4096) the loop
- * reads the copy of them that mgp_compute_B left in the workspace,
+ * reads the copy of them that the call left in the workspace,
  * not w_dev, so weights changed in between are not seen. */
 int mgp_resample_prepared(const float* w_dev, int32_t n, const mgp_params* params, int32_t* ancestors_dev,
                           void* workspace_dev, size_t workspace_bytes, void* stream);

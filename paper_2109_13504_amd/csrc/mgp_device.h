@@ -389,9 +389,11 @@ __device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i
 // The caller's weights are read in place when they are 128-byte aligned (a
 // 32-weight segment is then one cache line; elsewhere it would straddle two,
 // three lines per wave and step instead of two) and no output overlaps them.
-// Otherwise, and for mgp_compute_B (whose prepared loop must not see weights
-// changed since), the reduction makes a copy of n + kSeam weights, the first
-// kSeam repeated at the end, which serves every window. Against the earlier
+// Otherwise, and for mgp_compute_B, the reduction makes a copy of n + kSeam
+// weights, the first kSeam repeated at the end, which serves every window. A
+// prepared loop must not see weights changed since: it always reads that copy,
+// which a single filter's loop in place completes from the weights it holds
+// anyway (`keep`: 4 bytes per weight written past the L2). Against the earlier
 // copy M[k] = w[k mod n], k < 2n, for every call, reading in place saves 8 of
 // the reduction's 12 bytes per weight (2^24 weights: 13 against 34 us) and
 // halves what the loop's reads spread over (a run of the 512-filter batch 668
@@ -441,6 +443,13 @@ __device__ __forceinline__ void write_seam(const float* __restrict__ w, uint32_t
         const uint32_t shift = n - kSeam % n;
         for (uint32_t k = threadIdx.x; k < 2u * kSeam; k += blockDim.x) seam[k] = w[(k + shift) % n];
     }
+}
+
+// Completes the copy behind a loop in place: the weight of particle i, unless
+// the reduction has written it as part of the seam (n >= kSeam).
+__device__ __forceinline__ void keep_weight(float* keep, uint32_t n, uint32_t i, float w)
+{
+    if (i < n - kSeam) __builtin_nontemporal_store(w, global_ptr(keep) + i);
 }
 
 // What the rounds of a thread's chains share (wave-uniform but the last two).
@@ -501,11 +510,13 @@ __device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t b0, u
 }
 
 // The B-step chains of a thread's particles start + threadIdx.x + BT p, p < P
-// (lanes past n run too and return some ancestor), in rounds of D steps.
+// (lanes past n run too and return some ancestor), in rounds of D steps. With
+// keep, the weights before the seam also go to keep[i].
 template <int P, int BT, int D>
 __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs, uint32_t n, uint32_t B,
                                                 uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t start,
-                                                uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u)
+                                                uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u,
+                                                float* keep = nullptr)
 {
     static_assert(BT % 64 == 0 && BT * P <= (int)kSeam, "a block's window must fit the seam");
     static_assert(4 * BT * (P - 1) < 4096, "the immediate offset of the last particle must fit 12 bits");
@@ -522,6 +533,10 @@ __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs
     for (int p = 0; p < P; ++p) {
         kk[p] = (start + t) * 4u;
         wk[p] = *(GlobalPtr<const float>)(own + t * 4u + 4u * BT * p);
+    }
+    if (keep) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) keep_weight(keep, n, start + t + BT * p, wk[p]);
     }
     uint32_t b0 = 0;
     for (; b0 + (uint32_t)D <= B; b0 += D) {

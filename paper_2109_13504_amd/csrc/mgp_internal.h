@@ -21,18 +21,19 @@ constexpr uint32_t kDefaultBMax = 65536;
 constexpr uint32_t kBMaxLimit = 1u << 24;
 
 // Workspace layout of a single-filter call (byte offsets, 256-aligned):
-//   [stats: mgp_stats][layout: u32, log(eps): f64]
+//   [stats: mgp_stats][log(eps): f64]
 //   [partials: kMaxPartials x Partial]
 //   [offsets: b_max x u32]
-//   [windows: (2n + 2048) x f32 reserved, Megopolis with n <= kWindowMaxN
-//    only: the seam (2 kSeam weights) or the copy (n + kSeam), as `layout`
-//    (kLayoutInPlace or kLayoutCopy) says]
+//   [copy: (2n + 2048) x f32 reserved, Megopolis with n <= kWindowMaxN only.
+//    copy[k] = w[k mod n], k < n + kSeam. The reduction makes it (kLayoutCopy)
+//    or, for a loop that reads the weights in place (kLayoutInPlace), its last
+//    2 kSeam entries, the seam; that loop then writes the others, for a prepared
+//    loop that may follow, which always reads the copy.]
 constexpr size_t kWsStatsOffset = 0;
-constexpr size_t kWsLayoutOffset = 128;
-constexpr size_t kWsLogEpsOffset = 136;
+constexpr size_t kWsLogEpsOffset = 128;
 constexpr size_t kWsPartialsOffset = 256;
-constexpr uint32_t kWindowReserve = 2048;  // of the reserved 2n + 2048: >= 2 kSeam, and >= kSeam - n
-static_assert(kWindowReserve >= 2 * kSeam, "the seam must fit the reserved region");
+constexpr uint32_t kWindowReserve = 2048;  // of the reserved 2n + 2048
+static_assert(kWindowReserve >= kSeam, "the copy must fit the reserved region");
 constexpr int kMegopolisPPT = 4;  // particles per thread of the large Megopolis loop
 
 struct Partial {
@@ -96,7 +97,7 @@ struct OutRange {
 bool in_place(const float* w, uint32_t n, const OutRange* outs, int count);
 bool ranges_overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes);
 // layout: kLayoutInPlace or kLayoutCopy (Megopolis with windows), else unused.
-// copy: where the reduction also writes the n weights (16-byte aligned), or null.
+// copy (other variants): where the reduction also writes the n weights (16-byte aligned), or null.
 int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
                             mgp_stats* st_user, hipStream_t stream, float* copy = nullptr);
 // The reduction's partials alone, and the arguments of the finalize step that
@@ -105,11 +106,13 @@ int enqueue_partials(const float* w, uint32_t n, const Params& p, char* ws, uint
                      float* copy, hipStream_t stream);
 // The accept loop (after the reduction and finalize launches); with rc.states
 // set, the particle copy x_bar_i = x_{k_i} runs as its epilogue. anc may be
-// null when rc copies the rows.
-int enqueue_loop(const float* w, uint32_t n, const Params& p, char* ws, int32_t* anc, hipStream_t stream,
-                 const RowCopy& rc = RowCopy{});
-// The accept loop for m outputs drawn from n weighted inputs (M != N).
-int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, char* ws, int32_t* anc,
+// null when rc copies the rows. layout: the reduction's; kLayoutCopy for a
+// prepared loop.
+int enqueue_loop(const float* w, uint32_t n, const Params& p, uint32_t layout, char* ws, int32_t* anc,
+                 hipStream_t stream, const RowCopy& rc = RowCopy{});
+// The accept loop for m outputs drawn from n weighted inputs (M != N, layout
+// kLayoutCopy: m particles do not hold all the weights).
+int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, uint32_t layout, char* ws, int32_t* anc,
                    hipStream_t stream, const RowCopy& rc = RowCopy{});
 int enqueue_gather(const float* states, uint32_t n_states, uint32_t d, const int32_t* anc, uint32_t n_out,
                    float* out, hipStream_t stream);

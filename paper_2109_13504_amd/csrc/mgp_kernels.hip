@@ -48,15 +48,13 @@ int check_launch(const char* what)
 // ---------------------------------------------------------------------------
 // What the reduction launch does beside the reduction, in blocks of their own
 // after its nparts blocks, so that they run beside those:
-//   - ends != 0: the ends of a Megopolis loop's windows (block nparts), with the
-//     layout that the loop finds there;
+//   - ends != 0: the ends of a Megopolis loop's windows (block nparts);
 //   - early_offsets > 0: offsets o_0 .. o_{early_offsets - 1} and log(eps), for
 //     a loop that does the finalize step itself. The offsets do not depend on
 //     the weights, B only says how many are used.
 struct ReduceExtra {
     float* copy;
     float* seam;
-    uint32_t* layout;
     uint32_t ends;
     uint32_t early_offsets;
     uint32_t* offsets;
@@ -78,7 +76,6 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restri
         const uint32_t e = blockIdx.x - nparts;
         if (x.ends && e == 0) {
             write_window_ends(w, n, x.copy, x.seam);
-            if (threadIdx.x == 0) *x.layout = x.seam ? kLayoutInPlace : kLayoutCopy;
         } else {
             const uint32_t first = (e - x.ends) * kOffsetsPerBlock;
             const uint32_t end = first + kOffsetsPerBlock < x.early_offsets ? first + kOffsetsPerBlock : x.early_offsets;
@@ -176,17 +173,13 @@ __global__ __launch_bounds__(kLoopThreads) void k_resample(const float* __restri
     if (rc.states) copy_row(rc, i, k);
 }
 
-// Where a single filter's Megopolis loop finds its windows.
+// Where a single filter's Megopolis loop finds its windows, and, for a loop in
+// place after which the workspace may serve a prepared loop, the copy that it
+// completes.
 struct WindowArgs {
-    const float* w;
-    const float* aux;        // the workspace's window region: the seam or the copy
-    const uint32_t* layout;  // which of the two, written by the reduction
+    Windows at;
+    float* keep;
 };
-
-__device__ __forceinline__ Windows load_windows(const WindowArgs& a, uint32_t n)
-{
-    return *a.layout == kLayoutInPlace ? windows_in_place(a.w, a.aux, n) : windows_copy(a.aux);
-}
 
 // Megopolis by windows, P particles per thread, rounds of D steps. Rows
 // selects the particle copy of the epilogue: 0 none, D4 > 0 rows of D4
@@ -212,8 +205,8 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint3
         // every lane runs, also past m (start < m <= n here): the window
         // keeps those loads in bounds, and only real outputs store
         uint32_t kc[P];
-        megopolis_chain<P, (int)kLoopThreads, D>(load_windows(wa, n), offset_ptr(offsets), n, B, key0, key1, stream_id,
-                                                 start, kc, seg_mask);
+        megopolis_chain<P, (int)kLoopThreads, D>(wa.at, offset_ptr(offsets), n, B, key0, key1, stream_id, start, kc,
+                                                 seg_mask, wa.keep);
 #pragma unroll
         for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
     }
@@ -416,8 +409,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
     const uint32_t start = blockIdx.x * 64u;
     const uint32_t la4 = (lane & ~seg_mask) * 4u;
     const uint32_t ll4 = (lane & seg_mask) * 4u;
-    Windows W{};
-    if constexpr (Mode != kSplitSmall) W = load_windows(wa, n);
+    const Windows W = wa.at;
     // the weight at a window position (byte offset v of the window from position s on)
     auto candidate = [&](uint32_t s, uint32_t v) -> float {
         if constexpr (Mode == kSplitSmall)
@@ -486,6 +478,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis_split(WindowArgs wa,
         }
     };
     float wk = candidate(start, lane * 4u);
+    if (Mode != kSplitSmall && wa.keep && q == 0) keep_weight(wa.keep, n, i, wk);
     uint32_t last = 0xFFFFFFFFu;  // the last accepted step
     if (q > 0) produce(0u, 0u);
     __syncthreads();
@@ -730,12 +723,12 @@ bool in_place(const float* w, uint32_t n, const OutRange* outs, int count)
     return true;
 }
 
-// The layout for a call that resamples n weights into m ancestors (and rows).
-static uint32_t loop_layout(const float* w, uint32_t n, uint32_t m, const int32_t* anc, const mgp_stats* st_user,
+// The layout for a call that resamples n weights into n ancestors (and rows).
+static uint32_t loop_layout(const float* w, uint32_t n, const int32_t* anc, const mgp_stats* st_user,
                             const RowCopy& rc)
 {
-    const OutRange outs[3] = {{anc, 4ull * m}, {rc.out, 4ull * m * rc.d}, {st_user, sizeof(mgp_stats)}};
-    return in_place(w, n, outs, 3) ? kLayoutInPlace : kLayoutCopy;
+    const OutRange outs[3] = {{anc, 4ull * n}, {rc.out, 4ull * n * rc.d}, {st_user, sizeof(mgp_stats)}};
+    return n >= kSeam && in_place(w, n, outs, 3) ? kLayoutInPlace : kLayoutCopy;
 }
 
 static FinalizeArgs finalize_args(uint32_t n, const Params& p, bool make_offsets)
@@ -768,10 +761,9 @@ static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make
     x.copy = copy;
     uint32_t extra = 0;
     if (make_offsets && uses_windows(n, p.variant)) {
-        float* aux = reinterpret_cast<float*>(ws + windows_offset(p.b_max));
-        x.copy = layout == kLayoutCopy ? aux : nullptr;
-        x.seam = layout == kLayoutInPlace ? aux : nullptr;
-        x.layout = reinterpret_cast<uint32_t*>(ws + kWsLayoutOffset);
+        float* at = reinterpret_cast<float*>(ws + windows_offset(p.b_max));
+        x.copy = layout == kLayoutCopy ? at : nullptr;
+        x.seam = layout == kLayoutInPlace ? at + (n - kSeam) : nullptr;
         x.ends = 1u;
         extra = 1u;
     }
@@ -790,12 +782,6 @@ static int enqueue_reduce(const float* w, uint32_t n, const Params& p, bool make
         hipLaunchKernelGGL(k_reduce<false>, grid, dim3(kReduceThreads), 0, stream, w, n, chunk, g, part, x);
     *nparts = g;
     return check_launch("reduce kernel");
-}
-
-static WindowArgs window_args(const float* w, const Params& p, char* ws)
-{
-    return WindowArgs{w, reinterpret_cast<const float*>(ws + windows_offset(p.b_max)),
-                      reinterpret_cast<const uint32_t*>(ws + kWsLayoutOffset)};
 }
 
 int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool make_offsets, uint32_t layout, char* ws,
@@ -826,6 +812,7 @@ struct LoopLaunch {
     const float* w;
     uint32_t n, m;
     const Params& p;
+    uint32_t layout;
     char* ws;
     LoopStart ls;
     int32_t* anc;
@@ -834,6 +821,13 @@ struct LoopLaunch {
     const uint32_t* offs = reinterpret_cast<const uint32_t*>(ws + kWsOffsetsOffset);
     uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
     uint32_t seg_mask = p.segment - 1u;
+
+    WindowArgs window_args() const
+    {
+        float* copy = reinterpret_cast<float*>(ws + windows_offset(p.b_max));
+        if (layout == kLayoutCopy) return WindowArgs{windows_copy(copy), nullptr};
+        return WindowArgs{windows_in_place(w, copy + (n - kSeam), n), !Fin || ls.prepares ? copy : nullptr};
+    }
 
     template <int V>
     void variant() const
@@ -853,8 +847,8 @@ struct LoopLaunch {
     void windows_rows() const
     {
         const dim3 grid((m + kLoopThreads * P - 1u) / (kLoopThreads * P));
-        hipLaunchKernelGGL((k_megopolis<P, D, Rows, Fin>), grid, dim3(kLoopThreads), 0, stream, window_args(w, p, ws),
-                           n, m, ls, offs, k0, k1, p.stream_id, seg_mask, anc, rc);
+        hipLaunchKernelGGL((k_megopolis<P, D, Rows, Fin>), grid, dim3(kLoopThreads), 0, stream, window_args(), n, m,
+                           ls, offs, k0, k1, p.stream_id, seg_mask, anc, rc);
     }
 
     // by windows, with the epilogue that fits the row copy
@@ -879,7 +873,7 @@ struct LoopLaunch {
         if (uses_windows(n, p.variant) && m <= n) {
             if (m <= kSplitMaxM)
                 hipLaunchKernelGGL(k_megopolis_split<(Fin ? kSplitFinalize : kSplitPrepared)>, dim3((m + 63u) / 64u),
-                                   dim3(kLoopThreads), 0, stream, window_args(w, p, ws), n, m, ls, offs, k0, k1,
+                                   dim3(kLoopThreads), 0, stream, window_args(), n, m, ls, offs, k0, k1,
                                    p.stream_id, seg_mask, anc, SmallArgs{}, rc);
             else if (m <= kOneMaxM)
                 windows<1, 20>();
@@ -900,20 +894,20 @@ struct LoopLaunch {
     }
 };
 
-int enqueue_loop(const float* w, uint32_t n, const Params& p, char* ws, int32_t* anc, hipStream_t stream,
-                 const RowCopy& rc)
+int enqueue_loop(const float* w, uint32_t n, const Params& p, uint32_t layout, char* ws, int32_t* anc,
+                 hipStream_t stream, const RowCopy& rc)
 {
-    return enqueue_loop_m(w, n, n, p, ws, anc, stream, rc);
+    return enqueue_loop_m(w, n, n, p, layout, ws, anc, stream, rc);
 }
 
-int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, char* ws, int32_t* anc,
+int enqueue_loop_m(const float* w, uint32_t n, uint32_t m, const Params& p, uint32_t layout, char* ws, int32_t* anc,
                    hipStream_t stream, const RowCopy& rc)
 {
     LoopStart ls{};
     ls.st = reinterpret_cast<const mgp_stats*>(ws + kWsStatsOffset);
     ls.tag = call_tag(n, p.variant, p.seed, p.stream_id);
     ls.b_cap = p.b_max;
-    return LoopLaunch<false>{w, n, m, p, ws, ls, anc, rc, stream}.run();
+    return LoopLaunch<false>{w, n, m, p, layout, ws, ls, anc, rc, stream}.run();
 }
 
 // mgp_resample with n <= kSmallMaxN (Megopolis) or kSmallMaxNOther: one
@@ -980,7 +974,7 @@ int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_
     if (n <= (p.variant == kMegopolis ? kSmallMaxN : kSmallMaxNOther))
         return enqueue_small(w, n, p, ws, st_user, anc, stream, rc);
     const bool mego = p.variant == kMegopolis;
-    const uint32_t layout = loop_layout(w, n, n, anc, st_user, rc);
+    const uint32_t layout = loop_layout(w, n, anc, st_user, rc);
     if (n <= (mego ? kFinMaxN : kFinMaxNOther) && (!mego || p.B || p.b_max <= kEarlyOffsetsMax)) {
         uint32_t g = 0;
         const int err = enqueue_reduce(w, n, p, mego, layout, true, ws, &g, stream);
@@ -994,11 +988,11 @@ int enqueue_resample(const float* w, uint32_t n, const Params& p, char* ws, mgp_
         ls.st_user = st_user;
         // up to 2^15 particles Megopolis has never left a workspace that a prepared loop takes
         ls.prepares = !mego || n > kNoPrepareMaxN ? 1u : 0u;
-        return LoopLaunch<true>{w, n, n, p, ws, ls, anc, rc, stream}.run();
+        return LoopLaunch<true>{w, n, n, p, layout, ws, ls, anc, rc, stream}.run();
     }
     int err = enqueue_reduce_finalize(w, n, p, mego, layout, ws, st_user, stream);
     if (err) return err;
-    return enqueue_loop(w, n, p, ws, anc, stream, rc);
+    return enqueue_loop(w, n, p, layout, ws, anc, stream, rc);
 }
 
 // 2^31 elements and more: 2^20 blocks, grid-stride.
@@ -1142,7 +1136,7 @@ int mgp_resample_prepared(const float* w_dev, int32_t n, const mgp_params* param
     if (rc) return rc;
     rc = check_workspace(workspace_dev, workspace_bytes_, (uint32_t)n, p);
     if (rc) return rc;
-    return enqueue_loop(w_dev, (uint32_t)n, p, static_cast<char*>(workspace_dev), ancestors_dev,
+    return enqueue_loop(w_dev, (uint32_t)n, p, kLayoutCopy, static_cast<char*>(workspace_dev), ancestors_dev,
                         static_cast<hipStream_t>(stream));
 }
 
@@ -1243,10 +1237,10 @@ int mgp_resample_m(const float* w_dev, int32_t n, int32_t m, const mgp_params* p
     if (rc) return rc;
     char* ws = static_cast<char*>(workspace_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const uint32_t layout = loop_layout(w_dev, (uint32_t)n, (uint32_t)m, ancestors_dev, stats_dev, RowCopy{});
+    const uint32_t layout = m == n ? loop_layout(w_dev, (uint32_t)n, ancestors_dev, stats_dev, RowCopy{}) : kLayoutCopy;
     rc = enqueue_reduce_finalize(w_dev, (uint32_t)n, p, p.variant == kMegopolis, layout, ws, stats_dev, s);
     if (rc) return rc;
-    return enqueue_loop_m(w_dev, (uint32_t)n, (uint32_t)m, p, ws, ancestors_dev, s);
+    return enqueue_loop_m(w_dev, (uint32_t)n, (uint32_t)m, p, layout, ws, ancestors_dev, s);
 }
 
 int mgp_gather(const float* states_dev, int32_t n_states, int32_t d, const int32_t* ancestors_dev, int32_t n_out,
@@ -1294,7 +1288,7 @@ int mgp_resample_gather_prepared(const float* w_dev, int32_t n, const mgp_params
     if (err) return err;
     err = check_workspace(workspace_dev, workspace_bytes_, (uint32_t)n, p);
     if (err) return err;
-    return enqueue_loop(w_dev, (uint32_t)n, p, static_cast<char*>(workspace_dev), ancestors_dev,
+    return enqueue_loop(w_dev, (uint32_t)n, p, kLayoutCopy, static_cast<char*>(workspace_dev), ancestors_dev,
                         static_cast<hipStream_t>(stream), rc);
 }
 
