@@ -118,7 +118,9 @@ __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats
     if (st->status == MGP_OK) {
         if constexpr (V == kMegopolis) {
             uint32_t kc[P];
-            megopolis_chain<P, BT, kBatchRound<P>>(F.windows, offset_ptr(F.offsets), n, B, F.key0, F.key1, F.stream_id, start, kc);
+            // the finalize step of the same run has drawn the offsets: no need to check them
+            megopolis_chain<P, BT, kBatchRound<P>, false>(F.windows, offset_ptr(F.offsets), n, B, F.key0, F.key1,
+                                                          F.stream_id, start, kc);
 #pragma unroll
             for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
         } else {

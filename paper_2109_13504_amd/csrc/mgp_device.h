@@ -456,35 +456,52 @@ __device__ __forceinline__ void keep_weight(float* keep, uint32_t n, uint32_t i,
 struct WindowLoop {
     Windows W;
     OffsetPtr offs;
-    uint32_t n, key0, key1, stream_id, seg_mask;
+    uint32_t key0, key1, stream_id;
     uint32_t start;     // the block's first particle
+    uint32_t last;      // n - 1
+    uint32_t start4, n4, mask4;  // start, n and the segment mask in bytes
+    uint32_t lim4;      // windows that start below it lie in W.w
     uint32_t la4, ll4;  // byte offset of the thread's segment in the window, and of its place in the segment
 };
 
-// Steps b0 .. b0 + D - 1 (Partial: b0 .. b0 + cnt - 1; b0 a multiple of 5) of
+// Steps b0 .. b0 + D - 1 (Partial: b0 .. b0 + cnt - 1), b0 = 5 blk, of
 // the chains of particles p0 .. p0 + G - 1 of a thread: candidate loads first
 // (they do not depend on the chain), then the draws, then the serial accept
-// steps.
-template <int P, int BT, int G, int D, bool Partial>
-__device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t b0, uint32_t cnt, int p0,
+// steps. A step's window takes ten or eleven scalar instructions, all in bytes:
+// window_start and window_at, with (i + o) mod S from the unmasked o. Written
+// with indices they were 17, and where few waves are in flight a wave's
+// instructions are what a step costs. us, then / now: 300 filters of 2^8 to
+// 2^12 particles 38.1 / 36.0 (256 x 1) and 65 / 61 (64 x 4); 600 of 2^9 to 2^14
+// 98 / 90 (256 x 1); a prepared loop of 100003 particles, B = 354, 38.5 / 32.5.
+// Checked: an offset of n or more (a workspace not written by this call) is
+// clamped, so that it cannot steer a load out of bounds.
+template <int P, int BT, int G, int D, bool Partial, bool Checked>
+__device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t blk, uint32_t cnt, int p0,
                                              uint32_t (&kk)[P], float (&wk)[P])
 {
     static_assert(D % 5 == 0, "a round covers whole blocks of five u draws");
-    const OffsetPtr offs = L.offs + b0;
+    const OffsetPtr offs = L.offs + 5u * blk;
     const uint32_t i0 = L.start + threadIdx.x;
+    uint32_t o[D];
     uint32_t jb[D];
     float wj[D][G];
 #pragma unroll
     for (uint32_t s = 0; s < D; ++s) {
+        if (s % 5u == 0) {
+            // five offsets at once, not one round trip per step behind its branch
+            if (Partial && s >= cnt) continue;
+#pragma unroll
+            for (uint32_t r = s; r < s + 5u; ++r) o[r] = offs[!Partial || r < cnt ? r : cnt - 1u];
+        }
         if (Partial && s >= cnt) continue;
-        uint32_t o = offs[s];
-        o = o < L.n ? o : L.n - 1u;  // a workspace not written by this call cannot steer a load out of bounds
-        const uint32_t at = window_start(L.start, o, L.seg_mask, L.n);
-        const uint32_t voff = L.la4 | ((L.ll4 + (o & L.seg_mask) * 4u) & (L.seg_mask * 4u));
-        const GlobalPtr<const char> base = window_at(L.W, at, L.n, P * BT);
+        const uint32_t o4 = (!Checked || o[s] < L.last ? o[s] : L.last) * 4u;
+        const uint32_t s4 = L.start4 + (o4 & ~L.mask4), s4n = s4 - L.n4;
+        const uint32_t at4 = s4 < s4n ? s4 : s4n;  // mod 4n: s4 - 4n wraps round below 4n
+        const uint32_t voff = L.la4 | ((L.ll4 + o4) & L.mask4);
+        const GlobalPtr<const char> base = (GlobalPtr<const char>)((at4 < L.lim4 ? L.W.w : L.W.seam) + at4);
 #pragma unroll
         for (int q = 0; q < G; ++q) wj[s][q] = *(GlobalPtr<const float>)(base + voff + 4u * BT * (p0 + q));
-        jb[s] = voff + 4u * at;
+        jb[s] = voff + at4;
     }
 #pragma unroll
     for (uint32_t g = 0; g < D / 5; ++g) {
@@ -493,7 +510,7 @@ __device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t b0, u
 #pragma unroll
         for (int q = 0; q < G; ++q) {
             const uint32_t i = (Partial && D > 5) ? pinned(i0 + BT * (p0 + q)) : i0 + BT * (p0 + q);
-            ub[q] = u_block(philox(b0 / 5u + g, kTagU, L.stream_id, i, L.key0, L.key1));
+            ub[q] = u_block(philox(blk + g, kTagU, L.stream_id, i, L.key0, L.key1));
         }
 #pragma unroll
         for (uint32_t s = 0; s < 5; ++s) {
@@ -511,8 +528,8 @@ __device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t b0, u
 
 // The B-step chains of a thread's particles start + threadIdx.x + BT p, p < P
 // (lanes past n run too and return some ancestor), in rounds of D steps. With
-// keep, the weights before the seam also go to keep[i].
-template <int P, int BT, int D>
+// keep, the weights before the seam also go to keep[i]. Checked: as above.
+template <int P, int BT, int D, bool Checked>
 __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs, uint32_t n, uint32_t B,
                                                 uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t start,
                                                 uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u,
@@ -525,7 +542,10 @@ __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs
     // scheduling barriers, 82.
     constexpr int G = P == 8 ? 2 : P;
     const uint32_t t = threadIdx.x;
-    const WindowLoop L{W, offs, n, key0, key1, stream_id, seg_mask, start, (t & ~seg_mask) * 4u, (t & seg_mask) * 4u};
+    const WindowLoop L{W,          offs,   key0,          key1,
+                       stream_id,  start,  n - 1u,        start * 4u,
+                       n * 4u,     seg_mask * 4u,         n >= (uint32_t)(P * BT) ? (n - P * BT) * 4u + 1u : 0u,
+                       (t & ~seg_mask) * 4u, (t & seg_mask) * 4u};
     uint32_t kk[P];  // ancestor as the byte offset of particle 0's position
     float wk[P];
     const GlobalPtr<const char> own = window_at(W, start, n, P * BT);
@@ -538,18 +558,18 @@ __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs
 #pragma unroll
         for (int p = 0; p < P; ++p) keep_weight(keep, n, start + t + BT * p, wk[p]);
     }
-    uint32_t b0 = 0;
-    for (; b0 + (uint32_t)D <= B; b0 += D) {
+    uint32_t blk = 0;
+    for (; 5u * blk + (uint32_t)D <= B; blk += D / 5) {
 #pragma unroll
         for (int p0 = 0; p0 < P; p0 += G) {
-            window_round<P, BT, G, D, false>(L, b0, D, p0, kk, wk);
+            window_round<P, BT, G, D, false, Checked>(L, blk, D, p0, kk, wk);
             if (P > G) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (b0 < B) {
+    if (5u * blk < B) {
 #pragma unroll
         for (int p0 = 0; p0 < P; p0 += G) {
-            window_round<P, BT, G, D, true>(L, b0, B - b0, p0, kk, wk);
+            window_round<P, BT, G, D, true, Checked>(L, blk, B - 5u * blk, p0, kk, wk);
             if (P > G) __builtin_amdgcn_sched_barrier(0);
         }
     }

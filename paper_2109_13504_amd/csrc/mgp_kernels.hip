@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint3
         // every lane runs, also past m (start < m <= n here): the window
         // keeps those loads in bounds, and only real outputs store
         uint32_t kc[P];
-        megopolis_chain<P, (int)kLoopThreads, D>(wa.at, offset_ptr(offsets), n, B, key0, key1, stream_id, start, kc,
+        megopolis_chain<P, (int)kLoopThreads, D, true>(wa.at, offset_ptr(offsets), n, B, key0, key1, stream_id, start, kc,
                                                  seg_mask, wa.keep);
 #pragma unroll
         for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
