@@ -51,8 +51,9 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_reduce(const FilterDev
     const FilterDev& F = fd[t.f];
     const float* w = in_hbm(F.w);
     float* copy = F.copy ? in_hbm(F.copy) : nullptr;
+    float* tail = F.tail ? in_hbm(F.tail) : nullptr;
     if (t.c == kEndsTile) {
-        write_window_ends(w, F.n, copy, F.seam ? in_hbm(F.seam) : nullptr);
+        write_window_ends(w, F.n, copy, F.seam ? in_hbm(F.seam) : nullptr, tail);
         return;
     }
     const uint64_t start = (uint64_t)t.c * F.chunk;
@@ -62,9 +63,9 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_reduce(const FilterDev
     double s = 0.0;
     uint32_t bad = 0;
     if (F.vec)
-        reduce_range<true>(w, start, end, copy, mx, s, bad);
+        reduce_range<true>(w, start, end, copy, tail, mx, s, bad);
     else
-        reduce_range<false>(w, start, end, copy, mx, s, bad);
+        reduce_range<false>(w, start, end, copy, tail, mx, s, bad);
     block_reduce(mx, s, bad);
     if (threadIdx.x == 0) parts[F.part_base + t.c] = Partial{s, mx, bad};
 }
@@ -120,7 +121,8 @@ __device__ __forceinline__ void process_tile(const FilterDev& F, const mgp_stats
             uint32_t kc[P];
             // the finalize step of the same run has drawn the offsets: no need to check them
             megopolis_chain<P, BT, kBatchRound<P>, false>(F.windows, offset_ptr(F.offsets), n, B, F.key0, F.key1,
-                                                          F.stream_id, start, kc);
+                                                          F.stream_id, start, kc, kSegment - 1u, nullptr,
+                                                          F.tail != nullptr);
 #pragma unroll
             for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
         } else {
@@ -755,7 +757,7 @@ int mgp_batch_plan_create(const mgp_filter_desc* filters, int32_t count, const m
         }
         for (int f = 0; f < count; ++f) {
             o_aux[f] = off;
-            off = align256(off + sizeof(float) * window_floats(inplace[f], (uint32_t)filters[f].n));
+            off = align256(off + sizeof(float) * window_floats(inplace[f], (uint32_t)filters[f].n, filters[f].B));
         }
     }
     p->dmem_bytes = off;
@@ -782,8 +784,8 @@ int mgp_batch_plan_create(const mgp_filter_desc* filters, int32_t count, const m
         F.offsets = mego ? reinterpret_cast<uint32_t*>(p->dmem + o_offs[f]) : nullptr;
         F.eps = x.epsilon;
         F.n = (uint32_t)x.n;
-        if (mego) F.set_windows(inplace[f], reinterpret_cast<float*>(p->dmem + o_aux[f]));
         F.B_user = x.B;
+        if (mego) F.set_windows(inplace[f], reinterpret_cast<float*>(p->dmem + o_aux[f]));
         F.b_max = p->b_max;
         F.key0 = (uint32_t)x.seed;
         F.key1 = (uint32_t)(x.seed >> 32);

@@ -17,6 +17,11 @@ constexpr uint32_t kNoFilter = 0xFFFFFFFFu;
 constexpr uint32_t kBatchMaxN = kWindowMaxN;
 constexpr int kMaxXcd = 8;
 
+// Whether a filter's windows have a tail: the reduction, or the SIR filter's
+// stage 1, writes it with the weights in hand, so a B still to be found counts
+// as many steps.
+inline bool record_tail(uint32_t n, uint32_t B_user) { return has_tail(n, B_user ? B_user : ~0u); }
+
 // Per-filter record in device memory (read with scalar loads).
 struct FilterDev {
     const float* w;
@@ -27,6 +32,7 @@ struct FilterDev {
     Windows windows;     // Megopolis: the accept loop's weights
     float* copy;         // Megopolis, weights not readable in place: the copy (n + kSeam floats) the reduction makes
     float* seam;         // Megopolis, weights read in place: their seam (2 kSeam floats), else null
+    float* tail;         // Megopolis, large odd sizes: the weights once more (n + kSeam floats), on behind either
     uint32_t* offsets;   // Megopolis: b_max entries, else null
     double eps;
     uint32_t n;
@@ -42,17 +48,25 @@ struct FilterDev {
     uint32_t rows4;      // the gather may use float4 rows
     uint32_t pad[3];
 
-    // The Megopolis windows: w in place with its seam at `aux`, or a copy there.
+    // The Megopolis windows: w in place with its seam at `aux`, or a copy there
+    // (w, n and B_user are set).
     void set_windows(bool in_place, float* aux)
     {
+        const bool tailed = record_tail(n, B_user);
         copy = in_place ? nullptr : aux;
-        seam = in_place ? aux : nullptr;
-        windows = in_place ? windows_in_place(w, aux, n) : windows_copy(aux);
+        // windows past n start on cache lines: the seam's middle, n, lies n mod 32 floats behind one
+        seam = in_place ? aux + (tailed ? n % 32u : 0u) : nullptr;
+        tail = !tailed ? nullptr : in_place ? seam + kSeam : copy + n;
+        windows = in_place ? windows_in_place(w, seam, n) : windows_copy(copy);
     }
 };
 
-// Floats of a filter's window region.
-inline size_t window_floats(bool in_place, uint32_t n) { return in_place ? 2u * (size_t)kSeam : (size_t)n + kSeam; }
+// Floats of a filter's window region: the seam or copy, and the tail.
+inline size_t window_floats(bool in_place, uint32_t n, uint32_t B_user)
+{
+    const size_t tail = record_tail(n, B_user) ? (size_t)n + (in_place ? 32u : 0u) : 0u;
+    return tail + (in_place ? 2u * (size_t)kSeam : (size_t)n + kSeam);
+}
 
 // A block of the batched reduction: chunk c of filter f, or (kEndsTile) the
 // ends of a Megopolis filter's windows, which run beside its chunks then

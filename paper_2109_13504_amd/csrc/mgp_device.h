@@ -398,11 +398,29 @@ __device__ __forceinline__ uint32_t run_chain(const LoopParams<W>& P, uint32_t i
 // the reduction's 12 bytes per weight (2^24 weights: 13 against 34 us) and
 // halves what the loop's reads spread over (a run of the 512-filter batch 668
 // to 626 us, an SIR step of 64 x 2^20 particles 1106 to 1043).
-// Byte offsets must fit 32 bits: 4 (n + 2 kSeam) < 2^32.
+//
+// Where n is no multiple of 32, a window that wraps begins n mod 32 weights off
+// a cache line, and each of its waves reads three lines per step instead of two:
+// about half of all windows. From kTailMinN weights and kTailMinSteps particle-
+// steps on that costs more than writing the weights once more, as a tail:
+// copy[n + k] = w[k mod n], k < n + kSeam. Windows then do not wrap but run on
+// past n, from multiples of the segment width. Whole calls, us, without / with a tail: 2^22 + 13, B = 200
+// 375 / 378, B = 354 663 / 644; 6 000 001, B = 100 304 / 313, B = 200 561 / 545,
+// B = 354 1007 / 943; 15 000 001, B = 64 537 / 540, B = 100 817 / 807, B = 354
+// 2950 / 2660; 3 000 001 (12 MB) never gains.
+// Byte offsets must fit 32 bits: 4 (2n + 2 kSeam) < 2^32.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kSeam = 1024;                  // particles per block at most
 constexpr uint32_t kWindowMaxN = (1u << 29) - 4096;
 constexpr uint32_t kLayoutInPlace = 1u, kLayoutCopy = 2u;  // where the windows lie
+constexpr uint32_t kTailMinN = 1u << 21;
+constexpr uint64_t kTailMinSteps = 1ull << 30;
+
+// Whether a loop of B steps over n weights has a tail.
+__host__ __device__ __forceinline__ bool has_tail(uint32_t n, uint32_t B)
+{
+    return n > kTailMinN && n % 32u != 0 && (uint64_t)n * B >= kTailMinSteps;
+}
 
 // Byte addresses of the weights: position k of a window that starts at s is at
 // (s + T <= n ? w : seam) + 4 k.
@@ -459,7 +477,7 @@ struct WindowLoop {
     uint32_t key0, key1, stream_id;
     uint32_t start;     // the block's first particle
     uint32_t last;      // n - 1
-    uint32_t start4, n4, mask4;  // start, n and the segment mask in bytes
+    uint32_t start4, wrap4, mask4;  // start, the place where windows wrap (n, or none) and the segment mask in bytes
     uint32_t lim4;      // windows that start below it lie in W.w
     uint32_t la4, ll4;  // byte offset of the thread's segment in the window, and of its place in the segment
 };
@@ -495,8 +513,8 @@ __device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t blk, 
         }
         if (Partial && s >= cnt) continue;
         const uint32_t o4 = (!Checked || o[s] < L.last ? o[s] : L.last) * 4u;
-        const uint32_t s4 = L.start4 + (o4 & ~L.mask4), s4n = s4 - L.n4;
-        const uint32_t at4 = s4 < s4n ? s4 : s4n;  // mod 4n: s4 - 4n wraps round below 4n
+        const uint32_t s4 = L.start4 + (o4 & ~L.mask4), s4n = s4 - L.wrap4;
+        const uint32_t at4 = s4 < s4n ? s4 : s4n;  // the difference wraps round below wrap4
         const uint32_t voff = L.la4 | ((L.ll4 + o4) & L.mask4);
         const GlobalPtr<const char> base = (GlobalPtr<const char>)((at4 < L.lim4 ? L.W.w : L.W.seam) + at4);
 #pragma unroll
@@ -528,12 +546,13 @@ __device__ __forceinline__ void window_round(const WindowLoop& L, uint32_t blk, 
 
 // The B-step chains of a thread's particles start + threadIdx.x + BT p, p < P
 // (lanes past n run too and return some ancestor), in rounds of D steps. With
-// keep, the weights before the seam also go to keep[i]. Checked: as above.
+// keep, the weights before the seam also go to keep[i]. tail: the windows run on
+// past n (has_tail). Checked: as above.
 template <int P, int BT, int D, bool Checked>
 __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs, uint32_t n, uint32_t B,
                                                 uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t start,
                                                 uint32_t (&anc_out)[P], uint32_t seg_mask = kSegment - 1u,
-                                                float* keep = nullptr)
+                                                float* keep = nullptr, bool tail = false)
 {
     static_assert(BT % 64 == 0 && BT * P <= (int)kSeam, "a block's window must fit the seam");
     static_assert(4 * BT * (P - 1) < 4096, "the immediate offset of the last particle must fit 12 bits");
@@ -544,7 +563,7 @@ __device__ __forceinline__ void megopolis_chain(const Windows& W, OffsetPtr offs
     const uint32_t t = threadIdx.x;
     const WindowLoop L{W,          offs,   key0,          key1,
                        stream_id,  start,  n - 1u,        start * 4u,
-                       n * 4u,     seg_mask * 4u,         n >= (uint32_t)(P * BT) ? (n - P * BT) * 4u + 1u : 0u,
+                       tail ? ~0u : n * 4u, seg_mask * 4u,         n >= (uint32_t)(P * BT) ? (n - P * BT) * 4u + 1u : 0u,
                        (t & ~seg_mask) * 4u, (t & seg_mask) * 4u};
     uint32_t kk[P];  // ancestor as the byte offset of particle 0's position
     float wk[P];

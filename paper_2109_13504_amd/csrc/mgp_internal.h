@@ -25,7 +25,8 @@ constexpr uint32_t kBMaxLimit = 1u << 24;
 //   [partials: kMaxPartials x Partial]
 //   [offsets: b_max x u32]
 //   [copy: (2n + 2048) x f32 reserved, Megopolis with n <= kWindowMaxN only.
-//    copy[k] = w[k mod n], k < n + kSeam. The reduction makes it (kLayoutCopy)
+//    copy[k] = w[k mod n], k < n + kSeam (2n + kSeam with a tail, which the
+//    finalize launch writes once B is known). The reduction makes it (kLayoutCopy)
 //    or, for a loop that reads the weights in place (kLayoutInPlace), its last
 //    2 kSeam entries, the seam; that loop then writes the others, for a prepared
 //    loop that may follow, which always reads the copy.]

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restri
     if (blockIdx.x >= nparts) {
         const uint32_t e = blockIdx.x - nparts;
         if (x.ends && e == 0) {
-            write_window_ends(w, n, x.copy, x.seam);
+            write_window_ends(w, n, x.copy, x.seam, nullptr);
         } else {
             const uint32_t first = (e - x.ends) * kOffsetsPerBlock;
             const uint32_t end = first + kOffsetsPerBlock < x.early_offsets ? first + kOffsetsPerBlock : x.early_offsets;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restri
     float mx = 0.0f;
     double s = 0.0;
     uint32_t bad = 0;
-    reduce_range<Vec>(w, start, end, x.copy, mx, s, bad);
+    reduce_range<Vec>(w, start, end, x.copy, nullptr, mx, s, bad);
     block_reduce(mx, s, bad);
     if (threadIdx.x == 0) part[blockIdx.x] = Partial{s, mx, bad};
 }
@@ -100,12 +100,52 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const float* __restri
 // ---------------------------------------------------------------------------
 // 2. Finalize: see finalize_one in mgp_reduce.h.
 // ---------------------------------------------------------------------------
+// Blocks beyond the first write the tail of the weights (has_tail), copy[n + k] =
+// src[k mod n], k < n + kSeam. Whether the loop wants it depends on B, so they do
+// the step for themselves: a launch of its own after this one, which returned
+// where the tail is not wanted, would cost every such call 3 us.
+struct TailArgs {
+    const float* src;
+    float* copy;
+};
+constexpr uint32_t kTailBlocks = 512;
+
+// Block b's share, by whole float4s of the copy (the first may hold up to three
+// places before n, with the values that are there already).
+__device__ __forceinline__ void write_tail(const TailArgs& t, uint32_t n, uint32_t b)
+{
+    constexpr uint32_t kAhead = 4, kStep = 4u * kTailBlocks * kReduceThreads;
+    const uint32_t end = 2u * n + kSeam;
+    uint32_t p = (n & ~3u) + 4u * (b * kReduceThreads + threadIdx.x);
+    for (; p >= n && (uint64_t)p + (kAhead - 1u) * kStep + 4u <= 2ull * n; p += kAhead * kStep) {
+        Row4 v[kAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u)
+            v[u] = *reinterpret_cast<const Unaligned4*>(t.src + (p - n) + u * kStep);
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) *reinterpret_cast<Row4*>(t.copy + p + u * kStep) = v[u];
+    }
+    for (; p < end; p += kStep) {
+        Row4 v;
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c) {
+            const uint32_t k = p + c;  // below 2n + kSeam + 3 < 3n
+            v[c] = t.src[k < n ? k : k < 2u * n ? k - n : k - 2u * n];
+        }
+        *reinterpret_cast<Row4*>(t.copy + p) = v;
+    }
+}
+
 __global__ __launch_bounds__(kReduceThreads) void k_finalize(const Partial* __restrict__ part, uint32_t nparts,
                                                              FinalizeArgs a, mgp_stats* __restrict__ st,
                                                              mgp_stats* __restrict__ st_user,
-                                                             uint32_t* __restrict__ offsets)
+                                                             uint32_t* __restrict__ offsets, TailArgs tail)
 {
-    finalize_one<true>(part, nparts, a, st, st_user, offsets);
+    __shared__ mgp_stats st_local;
+    const bool first = blockIdx.x == 0;
+    if (!first) a.make_offsets = 0u;
+    const uint32_t B = finalize_one<true>(part, nparts, a, first ? st : &st_local, first ? st_user : nullptr, offsets);
+    if (!first && has_tail(a.n, B)) write_tail(tail, a.n, blockIdx.x - 1u);
 }
 
 // ---------------------------------------------------------------------------
@@ -206,7 +246,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint3
         // keeps those loads in bounds, and only real outputs store
         uint32_t kc[P];
         megopolis_chain<P, (int)kLoopThreads, D, true>(wa.at, offset_ptr(offsets), n, B, key0, key1, stream_id, start, kc,
-                                                 seg_mask, wa.keep);
+                                                 seg_mask, wa.keep, has_tail(n, B));
 #pragma unroll
         for (int p = 0; p < P; ++p) k[p] = (int32_t)kc[p];
     }
@@ -309,9 +349,9 @@ __device__ __forceinline__ uint32_t small_prologue(const float* __restrict__ w, 
         double s = 0.0;
         uint32_t bad = 0;
         if (fold_vec)
-            reduce_range<true>(M, start, end, nullptr, mx, s, bad);
+            reduce_range<true>(M, start, end, nullptr, nullptr, mx, s, bad);
         else
-            reduce_range<false>(M, start, end, nullptr, mx, s, bad);
+            reduce_range<false>(M, start, end, nullptr, nullptr, mx, s, bad);
         block_reduce(mx, s, bad);
         if (threadIdx.x == 0) parts[p] = Partial{s, mx, bad};
         __syncthreads();
@@ -794,7 +834,14 @@ int enqueue_reduce_finalize(const float* w, uint32_t n, const Params& p, bool ma
     int rc = enqueue_reduce(w, n, p, make_offsets, layout, false, ws, &g, stream, copy);
     if (rc) return rc;
     const FinalizeArgs a = finalize_args(n, p, make_offsets);
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kReduceThreads), 0, stream, part, g, a, st, st_user, offs);
+    TailArgs tail{};
+    uint32_t blocks = 1;
+    if (make_offsets && uses_windows(n, p.variant) && has_tail(n, p.B ? p.B : p.b_max)) {
+        tail.copy = reinterpret_cast<float*>(ws + windows_offset(p.b_max));
+        tail.src = layout == kLayoutCopy ? tail.copy : w;
+        blocks += kTailBlocks;
+    }
+    hipLaunchKernelGGL(k_finalize, dim3(blocks), dim3(kReduceThreads), 0, stream, part, g, a, st, st_user, offs, tail);
     return check_launch("finalize kernel");
 }
 

@@ -55,17 +55,24 @@ __device__ __forceinline__ void block_reduce(float& mx, double& s, uint32_t& bad
     }
 }
 
-// Reduces w[start, end) into (mx, s, bad) per thread and, with a copy, writes
-// copy[i] = w[i] for the range. With Vec, w + start is 16-byte aligned.
+// Four floats at any float's address: one access, which the hardware splits
+// where it has to.
+using Unaligned4 = float __attribute__((ext_vector_type(4), aligned(4)));
+
+// Reduces w[start, end) into (mx, s, bad) per thread and, with a copy or a tail,
+// writes copy[i] = w[i], tail[i] = w[i] for the range. With Vec, w + start is
+// 16-byte aligned, as copy + start is; tail need not be.
 template <bool Vec>
 __device__ __forceinline__ void reduce_range(const float* __restrict__ w, uint64_t start, uint64_t end,
-                                             float* __restrict__ copy, float& mx, double& s, uint32_t& bad)
+                                             float* __restrict__ copy, float* __restrict__ tail, float& mx, double& s,
+                                             uint32_t& bad)
 {
     if constexpr (Vec) {
         const uint64_t end4 = start + ((end - start) & ~(uint64_t)3);
         for (uint64_t i = start + 4ull * threadIdx.x; i < end4; i += 4ull * kReduceThreads) {
             const float4 v = *reinterpret_cast<const float4*>(w + i);
             if (copy) *reinterpret_cast<float4*>(copy + i) = v;
+            if (tail) *reinterpret_cast<Unaligned4*>(tail + i) = Unaligned4{v.x, v.y, v.z, v.w};
             fold(v.x, mx, s, bad);
             fold(v.y, mx, s, bad);
             fold(v.z, mx, s, bad);
@@ -74,22 +81,33 @@ __device__ __forceinline__ void reduce_range(const float* __restrict__ w, uint64
         for (uint64_t i = end4 + threadIdx.x; i < end; i += kReduceThreads) {
             const float v = w[i];
             if (copy) copy[i] = v;
+            if (tail) tail[i] = v;
             fold(v, mx, s, bad);
         }
     } else {
         for (uint64_t i = start + threadIdx.x; i < end; i += kReduceThreads) {
             const float v = w[i];
             if (copy) copy[i] = v;
+            if (tail) tail[i] = v;
             fold(v, mx, s, bad);
         }
     }
 }
 
 // What a Megopolis loop needs beyond the reduction, by one block: the seam of
-// weights read in place, or the repeated first kSeam weights of a copy.
+// weights read in place, or the repeated first kSeam weights of a copy. With a
+// tail, which holds the seam's second half, they are the last kSeam weights and
+// those after the tail's n.
 __device__ __forceinline__ void write_window_ends(const float* __restrict__ w, uint32_t n, float* __restrict__ copy,
-                                                  float* __restrict__ seam)
+                                                  float* __restrict__ seam, float* __restrict__ tail)
 {
+    if (tail) {
+        for (uint32_t k = threadIdx.x; k < kSeam; k += kReduceThreads) {
+            if (seam) seam[k] = w[n - kSeam + k];
+            tail[(uint64_t)n + k] = w[k];
+        }
+        return;
+    }
     if (seam) write_seam(w, n, seam);
     if (copy)
         for (uint32_t k = threadIdx.x; k < kSeam; k += kReduceThreads) copy[(uint64_t)n + k] = w[k % n];

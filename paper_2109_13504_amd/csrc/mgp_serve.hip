@@ -329,6 +329,7 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
         if (s->variant == kMegopolis) {
             char* ws = s->pool_base + q.ws_off;
             F.n = n;
+            F.B_user = q.in.B;
             // outputs lie in the server's pool, which never overlaps the weights of a request it has not finished
             F.set_windows(in_place(F.w, n, nullptr, 0), reinterpret_cast<float*>(ws));
             F.offsets = reinterpret_cast<uint32_t*>(ws + window_bytes(n));

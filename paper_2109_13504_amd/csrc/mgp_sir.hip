@@ -91,6 +91,7 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_predict_update(float* __res
     const uint32_t r = blockIdx.y;
     const uint32_t m = blockIdx.x * kSirThreads + threadIdx.x;
     float* seam = fd[r].seam;
+    float* tail = fd[r].tail;
     const uint32_t part_base = fd[r].part_base;
     // the resample of this step runs under key seed + t * 2^32
     if (blockIdx.x == 0 && threadIdx.x == 0) fd[r].key1 = key1 + t;
@@ -156,6 +157,15 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_predict_update(float* __res
             // c < 2 kSeam that are i + kSeam modulo n
             for (uint32_t k = 0; k < 4 && i0 + k < n; ++k)
                 for (uint32_t c = (i0 + k + kSeam) % n; c < 2u * kSeam; c += n) seam[c] = wo[k];
+        }
+        if (tail) {  // begins at the seam's middle: what both hold, this thread writes twice
+            if (full) {
+                *reinterpret_cast<Unaligned4*>(tail + i0) = Unaligned4{wo[0], wo[1], wo[2], wo[3]};
+            } else {
+                for (uint32_t k = 0; k < 4 && i0 + k < n; ++k) tail[i0 + k] = wo[k];
+            }
+            if (i0 < kSeam)  // n > kTailMinN
+                for (uint32_t k = 0; k < 4; ++k) tail[n + i0 + k] = wo[k];
         }
     }
     block_reduce(mx, s, bad);
@@ -509,7 +519,7 @@ int mgp_sir_create(const mgp_sir_config* cfg, void* stream, mgp_sir_filter** out
     const size_t o_stats = take((size_t)f->R * sizeof(mgp_stats));
     const size_t o_q = take(sizeof(uint32_t) * 2 * (kMaxXcd + 1));
     const size_t o_lt = take(table.size() * sizeof(LTile));
-    const size_t seam_row = align256(sizeof(float) * window_floats(true, f->n));
+    const size_t seam_row = align256(sizeof(float) * window_floats(true, f->n, B_fixed));
     const size_t offs_row = align256(sizeof(uint32_t) * (size_t)offs_cap);
     const size_t o_offs = mego ? take((size_t)f->R * offs_row) : 0;
     const size_t o_seam = mego ? take((size_t)f->R * seam_row) : 0;
@@ -566,8 +576,8 @@ int mgp_sir_create(const mgp_sir_config* cfg, void* stream, mgp_sir_filter** out
         F.offsets = mego ? reinterpret_cast<uint32_t*>(f->dmem + o_offs + (size_t)r * offs_row) : nullptr;
         F.eps = cfg->epsilon;
         F.n = f->n;
-        if (mego) F.set_windows(true, reinterpret_cast<float*>(f->dmem + o_seam + (size_t)r * seam_row));  // rows are 256-byte aligned
         F.B_user = B_fixed;
+        if (mego) F.set_windows(true, reinterpret_cast<float*>(f->dmem + o_seam + (size_t)r * seam_row));  // rows are 256-byte aligned
         F.b_max = f->cfg.b_max;
         F.key0 = f->key0;
         F.key1 = f->key1;  // replaced by key1 + t at every step
