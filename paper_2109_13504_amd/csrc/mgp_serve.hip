@@ -205,10 +205,15 @@ bool device_words(const void* p, uint64_t bytes, int device)
 // both destinations there, inside their allocations, and the stream and the
 // thread on it too. Any other destination (host or managed memory, a peer, a
 // range that the runtime refuses) takes the runtime's copy, as does one beyond
-// kCopyMaxBlocks.
-bool copies_by_kernel(int device, hipStream_t st, const void* anc, uint64_t anc_bytes, const void* out,
-                      uint64_t out_bytes)
+// kCopyMaxBlocks. So do arrays that overlap (the destinations each other, or one
+// of them the other's source): the kernel moves both at once, the runtime the
+// ancestors first.
+bool copies_by_kernel(int device, hipStream_t st, const void* anc, const void* src_anc, uint64_t anc_bytes,
+                      const void* out, const void* src_out, uint64_t out_bytes)
 {
+    if (ranges_overlap(anc, anc_bytes, out, out_bytes) || ranges_overlap(anc, anc_bytes, src_out, out_bytes) ||
+        ranges_overlap(out, out_bytes, src_anc, anc_bytes))
+        return false;
     if (anc_bytes / kCopyChunk >= kCopyMaxBlocks || out_bytes / kCopyChunk >= kCopyMaxBlocks) return false;
     int current = -1;
     if (hipGetDevice(&current) != hipSuccess || current != device) return false;
@@ -765,7 +770,7 @@ int mgp_server_copy_outputs(mgp_server* s, uint64_t ticket, int32_t* anc, float*
     // after this copy
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!out || !src_out) out_bytes = 0;
-    if (copies_by_kernel(s->device, st, anc, anc_bytes, out, out_bytes)) {
+    if (copies_by_kernel(s->device, st, anc, src_anc, anc_bytes, out, src_out, out_bytes)) {
         const OutputCopy a{src_anc, anc, anc_bytes, copy_blocks(anc_bytes)};
         const OutputCopy o{src_out, out, out_bytes, copy_blocks(out_bytes)};
         hipLaunchKernelGGL(k_copy_outputs, dim3(a.blocks + o.blocks), dim3(kCopyThreads), 0, st, a, o);
