@@ -771,10 +771,13 @@ int mgp_server_copy_outputs(mgp_server* s, uint64_t ticket, int32_t* anc, float*
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!out || !src_out) out_bytes = 0;
     if (copies_by_kernel(s->device, st, anc, src_anc, anc_bytes, out, src_out, out_bytes)) {
-        const OutputCopy a{src_anc, anc, anc_bytes, copy_blocks(anc_bytes)};
-        const OutputCopy o{src_out, out, out_bytes, copy_blocks(out_bytes)};
-        hipLaunchKernelGGL(k_copy_outputs, dim3(a.blocks + o.blocks), dim3(kCopyThreads), 0, st, a, o);
-        if (hipGetLastError() != hipSuccess) return fail(MGP_EHIP, "copying the outputs failed");
+        OutputCopy a{src_anc, anc, anc_bytes, copy_blocks(anc_bytes)};
+        OutputCopy o{src_out, out, out_bytes, copy_blocks(out_bytes)};
+        void* args[] = {&a, &o};
+        // the launch's own status: the thread's last error may be an older call's
+        if (hipLaunchKernel(reinterpret_cast<const void*>(k_copy_outputs), dim3(a.blocks + o.blocks),
+                            dim3(kCopyThreads), args, 0, st) != hipSuccess)
+            return fail(MGP_EHIP, "copying the outputs failed");
         return MGP_OK;
     }
     if (hipMemcpyAsync(anc, src_anc, anc_bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)

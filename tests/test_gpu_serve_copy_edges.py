@@ -1,6 +1,9 @@
 """mgp_server_copy_outputs where its one kernel must not change what the two
 copies before it did: destinations that overlap (the ancestors are copied first,
-the states over them)."""
+the states over them), and a thread whose last HIP call failed."""
+import ctypes
+import re
+
 import numpy as np
 import pytest
 
@@ -39,3 +42,19 @@ def test_overlapping_destinations(served, gap):
                                 mgp.current_stream())
     np.testing.assert_array_equal(buf.cpu().numpy(), want)
 
+
+def test_an_older_error_is_not_this_call(served):
+    torch, mgp, srv, t, n, d, k_ref, x_ref = served
+    anc = torch.zeros(n, dtype=torch.int32, device="cuda")
+    out = torch.zeros(n * d, device="cuda")
+    torch.cuda.synchronize()
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(re.search(r"\S*/libamdhip64\.so\S*", f.read()).group(0))
+    assert hip.hipSetDevice(4096) != 0  # refused, and remembered as the thread's last error
+    try:
+        mgp.mgp_server_copy_outputs(srv.handle, t, anc.data_ptr(), out.data_ptr(), mgp.current_stream())
+    finally:
+        hip.hipGetLastError()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(anc.cpu().numpy(), k_ref)
+    np.testing.assert_array_equal(out.cpu().numpy(), x_ref)
