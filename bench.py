@@ -236,7 +236,8 @@ def pattern_ceiling(torch, mgp, n, steps):
     reads over a mirrored array of 2n + 1024 floats (the 4n-byte weights
     twice) at `steps` shared offsets, without random draws or accept steps
     (mgp_probe_pattern_read); median of 5 launches after one warm-up. Rate =
-    4 n steps bytes / time."""
+    4 n steps bytes / time. The loop reads as many lines per step, where n is a
+    multiple of 32 from one array with the windows wrapping round its end."""
     import numpy as np
     dev = torch.device("cuda:0")
     stream = torch.cuda.current_stream()
@@ -258,8 +259,9 @@ def pattern_ceiling(torch, mgp, n, steps):
     ms = float(np.median(times))
     gbs = 4.0 * n * steps / (ms * 1e-3) / 1e9
     log(f"[bench] Megopolis read pattern alone (n={n}, {steps} steps): {ms:.3f} ms, {gbs:.0f} GB/s")
-    return {"workload": f"mgp_probe_pattern_read: the four-particle Megopolis loop's candidate reads, n={n}, "
-                        f"{steps} steps, no draws or accept steps; median of 5 after one warm-up",
+    return {"workload": f"mgp_probe_pattern_read: the four-particle Megopolis loop's candidate reads over the weights "
+                        f"laid out twice, n={n}, {steps} steps, no draws or accept steps; median of 5 after one "
+                        "warm-up",
             "n": n, "steps": steps, "ms": ms, "GBs": gbs}
 
 

@@ -67,7 +67,8 @@ typedef struct mgp_params {
 
 /* Written on the device by mgp_resample / mgp_compute_B (48 bytes). */
 typedef struct mgp_stats {
-    double w_sum;     /* sum of the weights, fp64 */
+    double w_sum;     /* sum of the weights, fp64, rounded at each addition; their order, and so the last bits, depends
+                         on n and on whether w_dev is 16-byte aligned */
     double ratio;     /* E(w) / max(w), fp64 */
     double b_raw;     /* log(eps) / log(1 - ratio) before ceil / clamp; 0 when B was given */
     float w_max;      /* max(w), fp32 */
@@ -517,9 +518,10 @@ int mgp_prefix_workspace_size(int32_t n, size_t* bytes);
  * the fixed-point prefix sum, then one threshold and search per output.
  * w_dev: n fp32 weights (device), >= 0, finite, not all zero (else stats
  * status MGP_EWEIGHTS and every ancestor -1). ancestors_dev: n int32
- * (device), written. method: mgp_prefix_method. seed, stream_id: the Philox
- * key and counter word 2. workspace_dev: mgp_prefix_workspace_size bytes,
- * 256-byte aligned, caller-owned scratch. */
+ * (device), written; it may lie over w_dev, at the cost of a copy. method:
+ * mgp_prefix_method. seed, stream_id: the Philox key and counter word 2.
+ * workspace_dev: mgp_prefix_workspace_size bytes, 256-byte aligned,
+ * caller-owned scratch. */
 int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t seed, uint32_t stream_id,
                         int32_t* ancestors_dev, mgp_stats* stats_dev, void* workspace_dev, size_t workspace_bytes,
                         void* stream);

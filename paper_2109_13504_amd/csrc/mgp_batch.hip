@@ -91,12 +91,14 @@ __global__ __launch_bounds__(kReduceThreads) void k_batch_finalize(const FilterD
     if (blockIdx.x == 0 && threadIdx.x < nq) queues[threadIdx.x] = 0;
 }
 
-// Megopolis steps per round of loads: one and two particles per thread are the
-// shapes of batches too small to fill the chip, where round trips count
-// (105 filters of 2300 to 5000 particles: 37.3 us with rounds of 5, 36.6 with
-// 10, 36.3 with 20 at one particle; 44.3 against 44.2 at two).
+// Megopolis steps per round of loads: one particle per thread is the shape of
+// batches too small to fill the chip, where round trips count. us, rounds of 5 /
+// 10 / 20: 105 filters of 2300 to 5000 particles 38.1 / 36.1 / 35.6, 300 of 2^8 to
+// 2^12 43.5 / 41.4 / 40.0. (512 filters of 2^10 to 2^18 678 / - / 768, but four
+// particles take 516.) Two particles per thread, 5 / 10: 44.8 / 45.9, 50.1 / 51.6
+// and 534 / 537.
 template <int P>
-constexpr int kBatchRound = P == 1 ? 20 : P == 2 ? 10 : 5;
+constexpr int kBatchRound = P == 1 ? 20 : 5;
 
 // One tile: the chains of the block's BT * P particles from `start` on, then
 // the ancestors and the particle copy x_bar_i = x_{k_i}.

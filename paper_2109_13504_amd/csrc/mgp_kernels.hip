@@ -265,13 +265,13 @@ __global__ __launch_bounds__(kLoopThreads) void k_megopolis(WindowArgs wa, uint3
 }
 
 // Few outputs are few waves, which hide fewer round trips to memory: fewer
-// particles per thread and longer rounds then. Whole calls, us, at B = 4 / 16 /
-// 354 by particles per thread and steps per round:
+// particles per thread and longer rounds then. Calls one after the other in a
+// graph, us, at B = 4 / 16 / 354 by particles per thread and steps per round:
 //            1, 20              2, 10              4, 5
-//   2^17     8.1 /  9.9 / 45.6  7.8 /  9.5 / 51.0  -
-//   2^18     9.2 / 12.1 / 73.4  8.4 / 10.7 / 64.3  8.4 / 10.9 / 76.4 (4, 10)
-//   2^19    12.3 / 17.3 /  128  9.6 / 13.6 /  101  9.2 / 13.1 /  104
-//   2^20    18.2 / 27.8 /  235 12.4 / 20.1 /  174 11.2 / 18.0 /  165
+//   2^17     6.8 /  8.6 / 37.6  6.8 /  8.2 / 45.7  7.0 /  9.4 / 69.3
+//   2^18     8.1 / 10.5 / 59.6  7.1 /  9.2 / 54.4  7.1 /  9.6 / 68.7
+//   2^19    10.5 / 14.6 /  101  8.4 / 11.6 / 85.5  7.9 / 11.1 / 90.5
+//   2^20    15.4 / 23.9 /  188 11.0 / 17.2 /  148 10.1 / 16.4 /  150
 // Up to 2^16 k_megopolis_split is the fastest (below).
 constexpr uint32_t kOneMaxM = 1u << 17;  // one particle per thread
 constexpr uint32_t kTwoMaxM = 1u << 18;  // two
@@ -1005,8 +1005,9 @@ int enqueue_small(const float* w, uint32_t n, const Params& p, char* ws, mgp_sta
 
 // mgp_resample does the finalize step inside the loop (two launches instead of
 // three) up to these sizes; beyond, the step repeated in every block costs more
-// than the launch. Whole calls, us, three launches / two, at B = 16:
-//   Megopolis   2^15 10.6 / 9.0, 2^17 11.8 / 9.9, 2^20 19.9 / 18.0, 2^21 28.3 / 29.3
+// than the launch. Calls one after the other, us, three launches / two, at B = 16:
+//   Megopolis   2^15 8.9 / 7.5, 2^17 10.0 / 8.6, 2^20 17.9 / 16.4, 2^21 26.3 / 26.1
+//               (B = 354: 285 / 291)
 //   Metropolis  2^14 10.2 / 8.7, 2^18 26.2 / 24.9, 2^19 42.8 / 42.8, 2^20 80.6 / 84.0
 //   C1, C2      2^14 9.9 / 8.4 and 10.3 / 8.9, 2^18 12.8 / 11.8 and 13.6 / 12.6,
 //               2^19 16.5 / 17.1 and 17.9 / 18.9

@@ -12,13 +12,23 @@
 // Accuracy: worst error over 2^24 arguments of each, in units in the last
 // place against 64-bit-mantissa arithmetic, and the library function's on the
 // same arguments:
-//   neg_log_fraction  0.68 (log 0.65; mean 0.251 against 0.252)
+//   neg_log_fraction  0.68, a little more than log's 0.65 (mean 0.251, 0.252)
 //   exp_negative      0.84 (exp 0.86)    sqrt_positive 0.50 (sqrt 0.50)
 //   sincos_turn       1.84; absolute 2.2e-16, against 6.9e-16 of sincos on
-//                     the angle 2 pi b 2^-32 rounded to fp64
+//                     the angle 2 pi b 2^-32 rounded to fp64, whose relative
+//                     error has no bound near its zeros
+// What the model takes from them, the normal draw sqrt(-2 ln u1) cos or sin of
+// 2 pi u2, is off by 1.3e-15 at most and 6.0e-17 on average over 2^25 draws,
+// with the library's functions by 3.0e-15 and 1.5e-16: the angle's rounding
+// outweighs the logarithm's 0.03 units.
 // ratio() equals IEEE division on all of them. twentieth() rounds correctly.
-// The polynomials are Chebyshev interpolants of the functions named beside
-// them, computed in 60 digits; each term is the next power of the argument.
+// Methods: the logarithm's reduction to [sqrt(1/2), sqrt(2)) by the high word,
+// its form f - s (f - R) and the split of ln 2 are those of fdlibm's log (Sun
+// Microsystems, 1993; FreeBSD's and musl's); the exponential reduces by k ln 2 in
+// the same two parts (Cody and Waite); the square root is the coupled Newton
+// iteration for sqrt(x) and 1 / (2 sqrt(x)) (Goldschmidt). The polynomials are
+// this file's own: Chebyshev interpolants of the functions named beside them,
+// computed in 60 digits; each term is the next power of the argument.
 #pragma once
 
 #include <hip/hip_runtime.h>

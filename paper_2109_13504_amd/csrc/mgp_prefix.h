@@ -50,8 +50,8 @@ struct PrefixJob {
     uint64_t o_start;                  // the group each of them starts in, and the last one's end
 };
 
-// Fills the region layout and n, nch, log2n of J for runs of n particles;
-// returns the bytes of one run's region.
+// Fills the region layout and n, per, nsum, log2n of J for runs of n
+// particles; returns the bytes of one run's region.
 uint64_t prefix_region(uint32_t n, PrefixJob* J);
 
 // Enqueues the scan and search of a job: R runs, method MGP_MULTINOMIAL or

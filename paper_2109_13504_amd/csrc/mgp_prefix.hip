@@ -87,7 +87,7 @@ __device__ __forceinline__ int fixed_exponent(float w_max, int log2n_ceil)
 }
 
 // q = floor(w 2^K) for a finite w >= 0 with q < 2^62, given scale = 2^(K - 32):
-// y = w 2^(K - 32) is exact in fp64 (24 bits; K - 32 is between -98 and 179),
+// y = w 2^(K - 32) is exact in fp64 (24 bits; K - 32 is between -129 and 178),
 // its integer part is the high word and its fraction times 2^32, cut off, the
 // low word.
 __device__ __forceinline__ uint64_t fixed_weight(float w, double scale)
@@ -226,7 +226,7 @@ struct SystematicDraw {
     }
 
     // The number of outputs whose threshold is below P (0 <= P <= S), so the
-    // first output of the input that starts at P; more than N when P = S.
+    // first output of the input that starts at P; N or N + 1 when P = S.
     // P N / S - u_t is that crossing to within 2^-18 (each operation, here and in
     // threshold(), is off by 2^-53 of at most 2^31), so only the output nearest
     // to it has to be asked: those before are below P, those after are not. Its
