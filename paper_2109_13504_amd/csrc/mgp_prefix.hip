@@ -258,7 +258,10 @@ constexpr uint32_t kSysTiles = 8;
 // the sum before a group has the first output there (outputs_below), so
 // start[b], the group of output b kSysOut, is written by the thread whose group
 // has it: about one in 100 of them, against a search from the top of the tree
-// at the start of every block.
+// at the start of every block. Where a few groups have nearly all outputs, their
+// starts lie in a few waves, which write them side by side: sorted weights of
+// y = 4, us when a wave wrote one run after the other / now: 2^20 20.5 / 6.9, 2^24
+// 37.7 / 11.6.
 template <bool Sys>
 __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
 {
@@ -321,11 +324,15 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
             const uint32_t below = draw.outputs_below(run);
             const bool ends = run == S && v[e] > 0u;
             const uint32_t to = ends ? J.nsys + 1u : ((below < J.n ? below : J.n) + kSysOut - 1u) / kSysOut;
-            uint64_t mask = __ballot(to > from);
+            // two by the thread itself, which is all where no group has the
+            // outputs of three blocks; the rest of a long run by its wave
+            if (from < to) start[from] = g0 + e;
+            if (from + 1u < to) start[from + 1u] = g0 + e;
+            uint64_t mask = __ballot(from + 2u < to);
             while (mask) {
                 const int l = __ffsll((unsigned long long)mask) - 1;
                 mask &= mask - 1u;
-                const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)from, l);
+                const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)from, l) + 2u;
                 const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)to, l);
                 const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)(g0 + e), l);
                 for (uint32_t b = a + lane; b < z; b += 64u) start[b] = g;
@@ -342,34 +349,6 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_scan(PrefixJob J)
         if (threadIdx.x == 0)
             *at<PrefixHeader>(J, J.o_hdr) = PrefixHeader{base + total, fixed_exponent(st.w_max, J.log2n), 1};
     }
-}
-
-// The input whose interval holds t (t < S), by one lane on its own: down the
-// tree, then through the group's weights.
-__device__ __forceinline__ uint32_t descend(const PrefixJob& J, double scale, uint64_t t)
-{
-    const uint64_t* top = at<uint64_t>(J, J.o_level[J.top]);
-    uint32_t g = 0;
-    for (uint32_t step = J.top_span / 2u; step > 0; step >>= 1)
-        if (g + step < J.count[J.top] && top[g + step] <= t) g += step;
-    uint64_t before = top[g];
-    for (int k = J.top - 1; k >= 1; --k) {
-        const uint64_t* row = at<uint64_t>(J, J.o_level[k]) + (uint64_t)g * kFan;
-        uint32_t c = 0;
-        for (uint32_t m = 1; m < kFan; ++m)
-            if (row[m] <= t) c = m;
-        before = row[c];
-        g = g * kFan + c;
-    }
-    uint64_t q[kFan];
-    load_fixed<(int)kFan, false>(J, (uint64_t)g * kFan, scale, q);
-    uint32_t c = 0;
-#pragma unroll
-    for (uint32_t e = 0; e < kFan; ++e) {
-        before += q[e];
-        c += before <= t ? 1u : 0u;
-    }
-    return g * kFan + c;
 }
 
 // Algorithm 7: the threshold of output i of run r, u ~ U[0, S), one 64-bit draw
@@ -442,6 +421,15 @@ __device__ __forceinline__ uint64_t shuffle64(uint64_t x, int src)
            ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(x >> 32), src, 64) << 32);
 }
 
+// The top level of the tree into LDS (k_prefix_scan has run).
+__device__ __forceinline__ void load_top(const PrefixJob& J, uint64_t* top)
+{
+    const uint64_t* lv_top = at<uint64_t>(J, J.o_level[J.top]);
+    for (uint32_t k = threadIdx.x; k < J.top_span; k += kPrefixThreads)
+        top[k] = k < J.count[J.top] ? lv_top[k] : ~(uint64_t)0;
+    __syncthreads();
+}
+
 // Multinomial: 64 outputs per wave and pass. Each lane bisects the top level in
 // LDS for its own output; the rows below are read by quads, so that one load
 // instruction touches 16 lines and not 64 (a row per lane would be bound by
@@ -470,12 +458,7 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob
             if (first + p * kPrefixThreads < J.n) emit(J, first + p * kPrefixThreads, -1);
         return;
     }
-    if constexpr (!OwnScan) {
-        const uint64_t* lv_top = at<uint64_t>(J, J.o_level[J.top]);
-        for (uint32_t k = threadIdx.x; k < J.top_span; k += kPrefixThreads)
-            top[k] = k < J.count[J.top] ? lv_top[k] : ~(uint64_t)0;
-        __syncthreads();
-    }
+    if constexpr (!OwnScan) load_top(J, top);
     const double scale = ldexp(1.0, h.K - 32);
     const uint32_t quad = lane / 4u, part = lane % 4u;
     const GlobalPtr<const char> w = global_ptr(reinterpret_cast<const char*>(J.w + (uint64_t)blockIdx.y * J.w_ld));
@@ -565,6 +548,75 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob
     }
 }
 
+// The systematic outputs of a block, seven per lane side by side: down the tree,
+// then through each group's weights. The few blocks that take it are what the
+// launch then waits for, and few waves hide nothing, so the lane's seven searches
+// share their round trips down the tree (the weights of seven groups at once
+// would take registers from the blocks that do not come here). Whole calls, us,
+// sorted weights of y = 4, one search after the other / side by side: 32769
+// 36.3 / 20.6, 2^18 51.9 / 23.6, 2^20 62.5 / 27.6, 2^22 86 / 40 (the scan's part
+// included).
+__device__ __forceinline__ void search_lanes(const PrefixJob& J, const uint64_t* top, double scale,
+                                             const SystematicDraw& draw, uint32_t first)
+{
+    uint64_t t[kSysPer];
+    uint32_t g[kSysPer];
+#pragma unroll
+    for (uint32_t e = 0; e < kSysPer; ++e) {
+        const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
+        t[e] = draw.threshold(i < J.n ? i : J.n - 1u);
+        g[e] = 0;
+    }
+    for (uint32_t step = J.top_span / 2u; step > 0; step >>= 1)
+#pragma unroll
+        for (uint32_t e = 0; e < kSysPer; ++e)
+            if (top[g[e] + step] <= t[e]) g[e] += step;
+    for (int k = J.top - 1; k >= 1; --k) {
+        const GlobalPtr<const uint64_t> lv = global_ptr(at<const uint64_t>(J, J.o_level[k]));
+#pragma unroll
+        for (uint32_t e = 0; e < kSysPer; ++e) g[e] *= kFan;
+        for (uint32_t step = kFan / 2u; step > 0; step >>= 1) {
+            uint64_t x[kSysPer];
+#pragma unroll
+            for (uint32_t e = 0; e < kSysPer; ++e) x[e] = lv[g[e] + step];
+#pragma unroll
+            for (uint32_t e = 0; e < kSysPer; ++e)
+                if (x[e] <= t[e]) g[e] += step;
+        }
+    }
+    const GlobalPtr<const float> w = global_ptr(J.w + (uint64_t)blockIdx.y * J.w_ld);
+    const uint32_t whole = J.vec ? J.n / kFan : 0u;
+    const GlobalPtr<const uint64_t> x1 = global_ptr(at<const uint64_t>(J, J.o_level[1]));
+#pragma unroll
+    for (uint32_t e = 0; e < kSysPer; ++e) {
+        float v[kFan];
+        uint64_t sum = x1[g[e]];
+        if (g[e] < whole) {
+#pragma unroll
+            for (uint32_t c = 0; c < kFan; c += 4) {
+                const Row4 x = *(GlobalPtr<const Row4>)(w + (uint64_t)g[e] * kFan + c);
+#pragma unroll
+                for (uint32_t b = 0; b < 4; ++b) v[c + b] = x[b];
+            }
+        } else {
+#pragma unroll
+            for (uint32_t c = 0; c < kFan; ++c) {
+                const uint64_t j = (uint64_t)g[e] * kFan + c;
+                v[c] = j < J.n ? w[j] : 0.0f;
+            }
+        }
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t b = 0; b < kFan; ++b) {
+            sum += fixed_weight(v[b], scale);
+            c += sum <= t[e] ? 1u : 0u;
+        }
+        const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
+        if (i < J.n) emit(J, i, (int32_t)(g[e] * kFan + c));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Systematic: kSysOut outputs per block. Their thresholds rise with i, so their
 // ancestors lie between the groups of the block's first output and of the next
 // block's, which the scan has left (OwnScan: the block counts them itself over
@@ -574,12 +626,12 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob
 // once. Each input marks the first of its outputs, if it has any
 // (outputs_below of the sums before and after it), and the running maximum of
 // the marks is the ancestors. When the weights are more than kSysTiles tiles
-// (long runs of very small weights), each lane descends by itself (OwnScan:
-// never more than 16 tiles, which it adds up).
+// (long runs of very small weights), its lanes search for each output
+// (OwnScan: never more than 16 tiles, which it adds up).
 template <bool OwnScan>
 __global__ __launch_bounds__(kPrefixThreads) void k_prefix_systematic(PrefixJob J)
 {
-    __shared__ __align__(16) uint64_t stage[OwnScan ? kTopMax : kSysOut / 2u];
+    __shared__ __align__(16) uint64_t stage[kTopMax];
     __shared__ uint32_t s_cnt[kPrefixThreads / 64];
     const uint32_t first = blockIdx.x * kSysOut;
     PrefixHeader h;
@@ -625,11 +677,8 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_systematic(PrefixJob 
     const uint64_t lo = (uint64_t)g_lo * kFan, end = ((uint64_t)g_hi + 1u) * kFan;
     const double scale = ldexp(1.0, h.K - 32);
     if (!OwnScan && end - lo > (uint64_t)kSysTiles * kChunk) {  // the same for every lane of the block
-#pragma unroll 1
-        for (uint32_t e = 0; e < kSysPer; ++e) {
-            const uint32_t i = first + e * kPrefixThreads + threadIdx.x;
-            if (i < J.n) emit(J, i, (int32_t)descend(J, scale, draw.threshold(i)));
-        }
+        load_top(J, stage);
+        search_lanes(J, stage, scale, draw, first);
         return;
     }
     // mark[r]: 1 + the input (from lo on) whose outputs start at first + r, 0: none
