@@ -38,7 +38,6 @@ struct PrefixJob {
     uint32_t n;
     uint32_t per, nsum;       // chunks per block of the first kernel, its blocks
     int log2n;                // ceil(log2 n)
-    uint32_t vec;             // the weights of every run 16-byte aligned
     uint32_t key0, key1;
     uint32_t stream0;         // run r draws from stream stream0 + r
     uint64_t o_hdr, o_sum;

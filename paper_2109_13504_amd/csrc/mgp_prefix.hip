@@ -130,8 +130,7 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* t
 }
 
 // The fixed-point weights of the Per consecutive inputs from `base` on (0 past
-// n; Per and base multiples of 4). Whole: base + Per <= n is known and the
-// weights are 16-byte aligned.
+// n; Per and base multiples of 4). Whole: base + Per <= n is known.
 template <int Per, bool Whole>
 __device__ __forceinline__ void load_fixed(const PrefixJob& J, uint64_t base, double scale, uint64_t (&q)[Per])
 {
@@ -140,7 +139,7 @@ __device__ __forceinline__ void load_fixed(const PrefixJob& J, uint64_t base, do
     if (Whole) {
 #pragma unroll
         for (int e = 0; e < Per; e += 4) {
-            const Row4 x = *(GlobalPtr<const Row4>)(w + base + e);
+            const Row4 x = *(GlobalPtr<const Unaligned4>)(w + base + e);
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[e + c] = x[c];
         }
@@ -158,7 +157,7 @@ template <int Per>
 __device__ __forceinline__ void load_fixed_tile(const PrefixJob& J, uint64_t first, double scale, uint64_t (&q)[Per])
 {
     const uint64_t base = first + (uint64_t)threadIdx.x * Per;
-    if (J.vec && first + (uint64_t)Per * kPrefixThreads <= J.n)
+    if (first + (uint64_t)Per * kPrefixThreads <= J.n)
         load_fixed<Per, true>(J, base, scale, q);
     else
         load_fixed<Per, false>(J, base, scale, q);
@@ -462,7 +461,7 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob
     const double scale = ldexp(1.0, h.K - 32);
     const uint32_t quad = lane / 4u, part = lane % 4u;
     const GlobalPtr<const char> w = global_ptr(reinterpret_cast<const char*>(J.w + (uint64_t)blockIdx.y * J.w_ld));
-    const uint32_t whole = J.vec ? J.n / kFan : 0u;  // groups below it can be read by vectors
+    const uint32_t whole = J.n / kFan;  // groups below it can be read by vectors
     for (uint32_t p = 0; p < passes; ++p) {
         const uint32_t i = first + p * kPrefixThreads;
         const uint64_t t_own = multinomial_threshold(J, h.total, i < J.n ? i : J.n - 1u);
@@ -517,7 +516,7 @@ __global__ __launch_bounds__(kPrefixThreads) void k_prefix_multinomial(PrefixJob
         if (__all(inside)) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                v[r] = *(GlobalPtr<const Row4>)(w + ((Off)g[r] * (4u * kFan) + part * 16u));
+                v[r] = *(GlobalPtr<const Unaligned4>)(w + ((Off)g[r] * (4u * kFan) + part * 16u));
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -585,7 +584,7 @@ __device__ __forceinline__ void search_lanes(const PrefixJob& J, const uint64_t*
         }
     }
     const GlobalPtr<const float> w = global_ptr(J.w + (uint64_t)blockIdx.y * J.w_ld);
-    const uint32_t whole = J.vec ? J.n / kFan : 0u;
+    const uint32_t whole = J.n / kFan;
     const GlobalPtr<const uint64_t> x1 = global_ptr(at<const uint64_t>(J, J.o_level[1]));
 #pragma unroll
     for (uint32_t e = 0; e < kSysPer; ++e) {
@@ -594,7 +593,7 @@ __device__ __forceinline__ void search_lanes(const PrefixJob& J, const uint64_t*
         if (g[e] < whole) {
 #pragma unroll
             for (uint32_t c = 0; c < kFan; c += 4) {
-                const Row4 x = *(GlobalPtr<const Row4>)(w + (uint64_t)g[e] * kFan + c);
+                const Row4 x = *(GlobalPtr<const Unaligned4>)(w + (uint64_t)g[e] * kFan + c);
 #pragma unroll
                 for (uint32_t b = 0; b < 4; ++b) v[c + b] = x[b];
             }
@@ -826,7 +825,7 @@ using namespace mgp;
 // The scan room that the single-filter entry point asks for: 8 bytes per input
 // (whole chunks) and per entry of the tree down to 16 entries, 16 per chunk, 4
 // per 256 outputs. The scan itself uses a tenth of it (prefix_region), and a
-// call whose outputs overlap its weights half of the rest for a copy of them.
+// call that needs a copy of its weights half of the rest.
 static uint64_t prefix_workspace(uint32_t n)
 {
     const uint64_t nch = ((uint64_t)n + kChunk - 1u) / kChunk;
@@ -842,6 +841,12 @@ static uint64_t prefix_workspace(uint32_t n)
 // beyond, it has its own launch, which is nothing there. Systematic, us, in the
 // blocks / by itself: 2^22 39 / 40, 10^7 61.5 / 62.2, 2^24 83 / 84.
 constexpr uint32_t kPrefixFinMaxN = 1u << 24;
+
+// Multinomial reads a group of 16 weights per output from a random place: one
+// cache line where the weights are 64-byte aligned, else two for every other
+// group. From this size on that costs more than an aligned copy. us, without /
+// with a copy: 2^20 39.6 / 43.6, 2^21 68.7 / 66.7, 2^24 716 / 580 (aligned 566).
+constexpr uint32_t kAlignMinN = 1u << 21;
 
 extern "C" {
 
@@ -885,11 +890,13 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     // The search reads the weights while it writes ancestors. Outputs that lie
     // over the weights (ancestors in place, say) are written while other blocks
     // still read there, so such a call scans and searches a copy, which the
-    // reduction makes behind the scan's region.
+    // reduction makes behind the scan's region. So does a large multinomial call
+    // whose weights are not 64-byte aligned (kAlignMinN).
     const uint64_t bytes = 4ull * un;
     float* copy = nullptr;
     if (ranges_overlap(w_dev, bytes, ancestors_dev, bytes) ||
-        ranges_overlap(w_dev, bytes, stats_dev, sizeof(mgp_stats)))
+        ranges_overlap(w_dev, bytes, stats_dev, sizeof(mgp_stats)) ||
+        (method == MGP_MULTINOMIAL && un >= kAlignMinN && ((uintptr_t)w_dev & 63u) != 0))
         copy = reinterpret_cast<float*>(ws + workspace_bytes(1u) + align256(region_bytes));
     J.stats = reinterpret_cast<mgp_stats*>(ws + kWsStatsOffset);
     if (un <= kPrefixFinMaxN) {
@@ -904,7 +911,6 @@ int mgp_resample_prefix(const float* w_dev, int32_t n, int32_t method, uint64_t 
     J.w = copy ? copy : w_dev;
     J.region = ws + workspace_bytes(1u);
     J.anc = ancestors_dev;
-    J.vec = ((uintptr_t)J.w & 15u) == 0 ? 1u : 0u;
     J.key0 = (uint32_t)seed;
     J.key1 = (uint32_t)(seed >> 32);
     J.stream0 = stream_id;

@@ -558,7 +558,6 @@ int mgp_sir_create(const mgp_sir_config* cfg, void* stream, mgp_sir_filter** out
         J.rows_ld = f->ld;
         J.d = 1;
         J.vec4 = 0;
-        J.vec = 1;  // rows are 256-byte aligned
         J.key0 = f->key0;
         J.key1 = f->key1;
         J.stream0 = 0;

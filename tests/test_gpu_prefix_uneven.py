@@ -1,7 +1,8 @@
 """The prefix-sum resamplers on weights that make a block's outputs span much of
-the input (long runs of tiny weights beside a few large ones): ancestors against
-the oracle (exact integers) at sizes of each number of tree levels and on both
-sides of the size where the scan moves."""
+the input (long runs of tiny weights beside a few large ones), and at addresses
+of every alignment: ancestors against the oracle (exact integers) at sizes of
+each number of tree levels and on both sides of the sizes where the scan moves
+and where unaligned weights are copied."""
 import numpy as np
 import pytest
 
@@ -40,3 +41,11 @@ def test_systematic_long_runs(env, n, kind):
     else:
         w = np.sort(w) if kind == "rising" else np.sort(w)[::-1].copy()
     _check(env, w, "systematic", shift=n % 3)
+
+
+@pytest.mark.parametrize("method", ["multinomial", "systematic"])
+@pytest.mark.parametrize("n", [17, 5003, 40001, (1 << 21) - 1, 1 << 21, (1 << 21) + 3])
+def test_alignments(env, method, n):
+    w = inputs.gaussian_weights(n, 2.0, n % 7)
+    for shift in (0, 1, 2, 3, 4, 8, 16):
+        _check(env, w, method, shift=shift, seed=20 + shift)
