@@ -1052,8 +1052,13 @@ static uint32_t gather_blocks(uint64_t total)
 
 // Floats from which a thread of the gather takes four and not two. us, two /
 // four: 100003 rows of 3 2.1 / 2.2, 2^20 rows of 2 4.1 / 4.0, of 5 12.6 / 9.7,
-// of 33 63 / 51. float4s: two (2^22 rows of 16 floats 92.5 either way).
+// of 33 63 / 51.
 constexpr uint64_t kGatherFour = 1ull << 21;
+// float4s to a thread: two, but one from the first to the second number of them.
+// us, one / two: 300007 rows of 12 floats (0.9 M) 6.7 / 5.2, 2^20 of 12 (3 M)
+// 25.7 / 26.3, 2^23 of 4 (8 M) 98.2 / 100.9, of 8 (17 M) 142 / 146, of 12 (25 M)
+// 199 / 198, 2000003 of 64 (32 M) 163 / 157.
+constexpr uint64_t kGatherOneFrom = 5ull << 19, kGatherOneTo = 1ull << 24;
 
 // floor(t / d) = t mult >> shift for t < 2^31: with 2^L >= d > 2^(L-1),
 // mult = (2^(31+L) + e) / d for some 0 < e <= d fits 32 bits, and the quotient
@@ -1088,6 +1093,9 @@ int enqueue_gather(const float* states, uint32_t n_states, uint32_t d, const int
     } else if (wide) {
         hipLaunchKernelGGL(k_gather_scalar, dim3(gather_blocks(total)), dim3(256), 0, stream, states, n_states, d, anc,
                            total, out);
+    } else if (vec && total >= kGatherOneFrom && total <= kGatherOneTo) {
+        launch_gather<Row4, 1>(reinterpret_cast<const Row4*>(states), n_states, d / 4u, anc, total,
+                               reinterpret_cast<Row4*>(out), stream);
     } else if (vec) {
         launch_gather<Row4, 2>(reinterpret_cast<const Row4*>(states), n_states, d / 4u, anc, total,
                                reinterpret_cast<Row4*>(out), stream);

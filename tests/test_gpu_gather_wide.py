@@ -42,3 +42,10 @@ def test_around_2pow31_elements(d, n_out):
 def test_row_lengths_near_the_end(d):
     """The last whole rows below 2^31 floats (float4s for the last length)."""
     _check(d, min(((1 << 31) - 1) // d, (1 << 28)), 5, d)
+
+
+@pytest.mark.parametrize("d,n_out", [(4, (5 << 19) - 1), (4, 5 << 19), (12, 873813), (12, 873814), (4, 1 << 24),
+                                     (4, (1 << 24) + 1), (20, 3355443), (20, 3355444), (16, 1 << 22)])
+def test_float4s_per_thread(d, n_out):
+    """On both sides of the numbers of float4s where a thread takes one, not two."""
+    _check(d, n_out, 100003, d)
