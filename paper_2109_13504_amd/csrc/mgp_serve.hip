@@ -308,6 +308,14 @@ void release_out(mgp_server* s, Req& q)
     q.has_out = false;
 }
 
+// Megopolis micro-batches of up to this many particles take one particle per
+// thread and rounds of twenty steps, larger ones the server's four and five: few
+// waves wait for round trips. Tiles are 256 particles either way. us, 64 x 4 /
+// 256 x 1: 8 requests of 1000 at y = 0, 2, 4 18.8 / 19.2, 19.9 / 19.1, 73 / 40; of
+// 32768 (2^18 in all) 18.9 / 18.6, 20.7 / 20.8, 82 / 67; of 65536 19.6 / 20.6,
+// 25.4 / 24.9, 102 / 109.
+constexpr uint64_t kOneMaxParticles = 1u << 18;
+
 // Builds the slot's tables for the requests and enqueues the batch. Called
 // without the lock; the requests are RUNNING, so nobody else touches them.
 int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
@@ -361,7 +369,10 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
     if (s->variant == kMegopolis)
         for (uint32_t f = 0; f < count; ++f) sl.h_rt[nrt++] = RTile{f, kEndsTile};
     std::vector<LTile> table;
-    build_tile_table(ns, cost, s->shape, s->nxcd, table, sl.h_qoff);
+    uint64_t particles = 0;
+    for (uint32_t f = 0; f < count; ++f) particles += ns[f];
+    const LoopShape shape = s->variant == kMegopolis && particles <= kOneMaxParticles ? LoopShape{256, 1, 1} : s->shape;
+    build_tile_table(ns, cost, shape, s->nxcd, table, sl.h_qoff);
     if (table.empty()) table.push_back(LTile{kNoFilter, 0});
     if (table.size() > s->cap_lt) return fail(MGP_ERANGE, "micro-batch exceeds the slot tables");
     memcpy(sl.h_lt, table.data(), table.size() * sizeof(LTile));
@@ -371,7 +382,7 @@ int launch_batch(mgp_server* s, Slot& sl, const std::vector<Req*>& rs)
     if (hipMemcpyAsync(sl.dmem, sl.hmem, upload, hipMemcpyHostToDevice, st) != hipSuccess)
         return fail(MGP_EHIP, "uploading micro-batch tables failed");
     const uint32_t grid = (uint32_t)table.size();
-    int rc = enqueue_batch(s->variant, s->shape, sl.d_fd, count, sl.d_rt, nrt, sl.d_parts, sl.d_stats, sl.d_lt, grid,
+    int rc = enqueue_batch(s->variant, shape, sl.d_fd, count, sl.d_rt, nrt, sl.d_parts, sl.d_stats, sl.d_lt, grid,
                            sl.d_qoff, sl.d_q, (uint32_t)s->nxcd, (uint32_t)s->cfg.d, st);
     if (rc) return rc;
     if (hipMemcpyAsync(sl.h_stats, sl.d_stats, count * sizeof(mgp_stats), hipMemcpyDeviceToHost, st) != hipSuccess ||
